@@ -954,7 +954,8 @@ gsp_status gsp_unproject_count(const gsp_view *view, int32_t stride, int64_t *n)
 size_t gsp_unproject_scratch_bytes(const gsp_view *view, int32_t stride) {
     int64_t n = 0;
     if (gsp_unproject_count(view, stride, &n) != GSP_OK) return 0;
-    return (size_t)(n > 0 ? n : 1) * sizeof(float4);
+    return gsp::unproject_scratch_bytes((view->roi_w + stride - 1) / stride,
+                                        (view->roi_h + stride - 1) / stride);
 }
 
 gsp_status gsp_unproject(gsp_ctx *ctx, const gsp_view *view, const float *depth,
@@ -967,7 +968,7 @@ gsp_status gsp_unproject(gsp_ctx *ctx, const gsp_view *view, const float *depth,
     s = gsp_unproject_count(view, stride, &n);
     if (s != GSP_OK) return s;
     if (n > gsp::kMaxUnprojectPoints)
-        return fail(GSP_EINVAL, "%lld points exceed the %d the brute-force neighbour search takes; "
+        return fail(GSP_EINVAL, "%lld points exceed the %d the neighbour search takes; "
                     "use a larger stride", (long long)n, gsp::kMaxUnprojectPoints);
     if (!depth || !image || !out || !scratch) return fail(GSP_EINVAL, "null argument");
     if (!out->means || !out->log_scales || !out->quats || !out->logit_opacities || !out->sh)
@@ -999,6 +1000,7 @@ gsp_status gsp_unproject(gsp_ctx *ctx, const gsp_view *view, const float *depth,
     a.logits = out->logit_opacities;
     a.sh = out->sh;
     a.pts = static_cast<float4 *>(scratch);
+    a.box = a.pts + n;
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = stage(ctx, "unproject", st, [&] { return gsp::launch_unproject(a, st); });
     if (e != hipSuccess) return hip_fail(e, "unproject");

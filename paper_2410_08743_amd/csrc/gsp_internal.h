@@ -274,14 +274,16 @@ hipError_t launch_gauss_adam(const GaussAdamK &a, float *aniso_loss, hipStream_t
 
 // relpose.hip: scene of frame t from its depth map, and the masked L1
 // (Sec. III-D, Eq. (20)-(21)).
-constexpr int kMaxUnprojectPoints = 1 << 18;   // n^2 neighbour tests: ~2 s at the limit
+constexpr int kMaxUnprojectPoints = 1 << 18;   // where every depth is noise, n^2 neighbour tests
 struct UnprojK {
     const float *depth, *image;          // [h][w], [3][h][w] over the region of interest
     int w, h, stride, nx, ny, S, roi_x, roi_y;
     float fx, fy, cx, cy, logit;
     float *means, *log_scales, *quats, *logits, *sh;   // raw parameters out
     float4 *pts;                         // scratch: (x, y, z, valid) per point
+    float4 *box;                         // scratch: bounds (low, high) of each block of pixels
 };
+size_t unproject_scratch_bytes(int nx, int ny);
 hipError_t launch_unproject(const UnprojK &a, hipStream_t s);
 
 struct MaskViewsK {

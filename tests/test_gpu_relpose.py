@@ -47,6 +47,30 @@ def test_unproject_matches_oracle(stride, roi):
     assert np.array_equal(sh[:, 1:, :], np.zeros_like(sh[:, 1:, :]))
 
 
+# the neighbour search at the edges of its 32 x 8 blocks and 7 x 7 windows: one
+# row, one column, a block and its remainders; and where windows have to grow:
+# a depth step between every pair of pixels, wide holes, two valid points only
+@pytest.mark.parametrize("w,h,kind", [(1, 1, "smooth"), (150, 1, "smooth"), (1, 90, "steps"),
+                                      (32, 8, "smooth"), (33, 9, "steps"), (101, 67, "smooth"),
+                                      (101, 67, "steps"), (101, 67, "holes"), (64, 40, "two")])
+def test_neighbour_search_matches_oracle(w, h, kind):
+    rng = np.random.default_rng(w + h)
+    cam = S.Camera(w, h, 0.9 * w + 7.0, 0.8 * w + 9.0, 0.4 * w, 0.55 * h)
+    y, x = np.mgrid[0:h, 0:w]
+    depth = 3.0 + 0.8 * np.sin(0.07 * x) + 0.01 * y + 0.02 * rng.random((h, w))
+    if kind == "steps":
+        depth = np.where((x + y) % 2 == 0, depth, 2.5 * depth)
+    elif kind == "holes":
+        depth = np.where((x // 20 + y // 15) % 2 == 0, depth, 0.0)
+    elif kind == "two":
+        depth = np.where((y == 3) & ((x == 5) | (x == w - 2)), depth, 0.0)
+    depth = depth.astype(np.float32)
+    image = rng.uniform(0, 1, (3, h, w)).astype(np.float32)
+    raw = RP.unproject(cam, torch.tensor(depth, device=DEV), torch.tensor(image, device=DEV), 1)
+    ref = ORP.unproject(depth, image, cam, 1)
+    assert np.max(np.abs(raw.log_scales.cpu().numpy() - ref["log_scales"])) <= 1e-5
+
+
 def test_masked_l1_matches_oracle():
     sc, cam, pose = random_case(41, 1, 90, 70, 3000)
     g = R.GaussianParams.from_set(sc, DEV)
