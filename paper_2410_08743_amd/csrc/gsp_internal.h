@@ -140,10 +140,11 @@ struct Layout {
 // Counters at the start of the counters region.
 // kCntSticky keeps the OR of every overflow since the workspace was zeroed;
 // kCntWin is the number of work windows of this call; kCntItems the number of
-// backward work items.
+// backward work items; kCntOver1024 and kCntOver2048 the numbers of tile lists
+// longer than that.
 enum Counter : int {
     kCntMLo = 0, kCntMHi = 1, kCntOverflow = 2, kCntMEff = 3, kCntSticky = 4, kCntWin = 5,
-    kCntItems = 6, kCntCount = 16
+    kCntItems = 6, kCntOver1024 = 7, kCntOver2048 = 8, kCntCount = 16
 };
 
 Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views, int64_t cap);

@@ -36,20 +36,22 @@ __global__ __launch_bounds__(256) void k_ranges(const uint32_t *keys, const uint
     if (k == M - 1 || keys[k + 1] != tile) ranges[tile].y = (uint32_t)(k + 1);
 }
 
-// Launch order of the tiles: longest lists first (in buckets of 4 entries:
-// 256 buckets spread the same-address LDS atomics of the counting sort
-// four times thinner than buckets of 16), so that the longest tiles do not
-// start last and leave a tail.
+// Launch order of the tiles: longest lists first (in buckets of 4 lengths up
+// to 1024, which spread the same-address LDS atomics of the counting sort four
+// times thinner than buckets of 16, and of 64 lengths above), so that the
+// longest tiles do not start last and leave a tail.  No bucket holds lengths
+// on both sides of 1024 or of 2048: the lists longer than that are a prefix.
 // The same kernel lists the backward work items (tile, chunk), also longest
 // first by chunk length; their count goes to counters[kCntItems].  The
 // orders only decide which workgroup takes which tile or chunk; every
 // result is the same in any order.
-constexpr int kOrderBuckets = 256;
+constexpr int kOrderBuckets = 512;
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderRounds = 8;   // tiles per thread whose ranges are loaded together
 
 __host__ __device__ constexpr int order_bucket(int len) {
-    return kOrderBuckets - 1 - ((len >> 2) < kOrderBuckets - 1 ? (len >> 2) : kOrderBuckets - 1);
+    const int up = len <= 1024 ? (len + 3) >> 2 : 257 + ((len - 1025) >> 6);
+    return kOrderBuckets - 1 - (up < kOrderBuckets - 1 ? up : kOrderBuckets - 1);
 }
 
 __global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2 *ranges, int total_tiles,
@@ -99,25 +101,30 @@ __global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2 *range
         if (lane == 0 && wfull > 0) atomicAdd(&cnt[1][kFull], wfull);
     }
     __syncthreads();
-    // exclusive scans of the two bucket histograms: one wave, a bucket per lane
-    static_assert(kOrderBuckets == 4 * kWave, "four buckets per lane");
+    // exclusive scans of the two bucket histograms: one wave, eight buckets per lane
+    constexpr int kPer = kOrderBuckets / kWave;   // buckets per lane
     if (t < kWave) {
 #pragma unroll
         for (int h = 0; h < 2; h++) {
-            uint32_t c[4], s = 0;
+            uint32_t c[kPer], s = 0;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                c[j] = cnt[h][4 * lane + j];
+            for (int j = 0; j < kPer; j++) {
+                c[j] = cnt[h][kPer * lane + j];
                 s += c[j];
             }
             const uint32_t inc = wave_inclusive_scan(s);
             uint32_t e = inc - s;
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                base[h][4 * lane + j] = e;
+            for (int j = 0; j < kPer; j++) {
+                base[h][kPer * lane + j] = e;
                 e += c[j];
             }
             if (h == 1 && lane == kWave - 1) counters[kCntItems] = inc;
+        }
+        // lists in front of the bucket that ends at 1024 (2048)
+        if (lane == 0) {
+            counters[kCntOver1024] = base[0][order_bucket(1024)];
+            counters[kCntOver2048] = base[0][order_bucket(2048)];
         }
     }
     __syncthreads();

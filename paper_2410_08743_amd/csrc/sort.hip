@@ -274,46 +274,40 @@ hipError_t launch_tile_sort(const Layout &L, char *ws, hipStream_t s) {
 // which is the order of a stable sort of all instances on the 64-bit key
 // (tile << 32 | depth).  Only the values (view * n + i) move.
 //
-// One wavefront per tile (a 64-thread workgroup, so that its barriers cost
-// nothing and many tiles are in flight per CU); workgroup b takes tile b, so
-// that its first load is its range.  The keys are taken relative to the
-// run's smallest (an order-preserving shift that leaves some 25 significant
-// bits for depths in 1.5 .. 8) and sorted LSD over kTdBits-bit digits (9:
-// three passes over those 25 bits, where 8-bit digits take four),
-// skipping every pass whose digit is the same for the whole run.  A pass is a
-// stable counting sort: rounds of 64 items, each lane ranked among the
-// round's lanes with the same digit (found through a per-digit lane mask in
-// LDS) on top of a running per-digit count, then the digit counts' exclusive
-// scan added to those ranks.  Runs of up to CAP entries stay in registers
-// and LDS (CAP is picked per launch from the mean list length the instance
-// capacity allows: 1024 or 2048), one 32-bit word per item: after the first
-// pass the relative key's remaining bits sit above the item's position in
-// the run, and the values are gathered by that position once at the end (so
-// a pass scatters and reloads one word per item, and LDS holds CAP words).
-// Longer runs, and runs whose keys are too wide for that packing (depths
-// spread over some sixty binary orders of magnitude), sorted over 8-bit
-// digits (histograms of every pass from one read first), move, CAP entries at a time with every load of a chunk in
-// flight, between the sorted arrays and the tile sort's other key and value
-// buffers, the relative keys carried beside the values (the key array's
-// tile ids are restored afterwards).
-#ifndef GSP_TD_BITS
-#define GSP_TD_BITS 9
-#endif
-// digits of the runs sorted in LDS (three passes over 25 significant bits)
-constexpr int kTdBits = GSP_TD_BITS;
-constexpr int kTdBins = 1 << kTdBits;
-// digits of the long runs, whose histograms of all passes share buf
-constexpr int kTdLBits = 8;
-constexpr int kTdLBins = 1 << kTdLBits;
-constexpr int kTdLPasses = (32 + kTdLBits - 1) / kTdLBits;
-static_assert(kTdBits >= kTdLBits && kTdBins % kWave == 0, "run and msk hold either digit");
+// A workgroup sorts a run in LDS by buckets.  The keys are taken relative to
+// the run's smallest, and their top bits choose one of CAP buckets; where some
+// bucket is crowded (a wall seen in the tile: most depths within a percent),
+// every bucket is cut into as many as it has entries, by the key's next bits,
+// so that any one cluster is spread as well.  The entries go to their buckets
+// in any order, and each finds its place by comparing itself with the others
+// of its bucket by (depth, value), which is exact.  A run that stays crowded
+// (hundreds of equal depths), or one that does not fit, is sorted in global
+// memory by a stable radix sort.
+//
+// Bound by latency (loads, then some eight steps through LDS with a barrier
+// each).  An LSD radix sort in one wavefront's LDS took some 25 LDS operations
+// per entry in a chain of ranking rounds; this takes about 10, none waiting for
+// another, and a workgroup of four or eight wavefronts shares a run: 23.2 ->
+// 15.8 us at 1.5M instances in 3024 lists of 500 (pose step, 1008 x 756; 4.5 us
+// more where the kernel of the longer runs finds none), 168 -> 99 + 4.6 us at
+// 15.4M in 12096 lists of 1100-1800 (joint step), 79 -> 15.3 + 24.3 us for a
+// room with lists of up to 2400, and 706 -> 110 + 118 us for 22M in lists of up
+// to 6700 (eight views of three sizes), whose longer half one wavefront each
+// had sorted in global memory.
+constexpr int kTdCrowd = 12;          // entries of a bucket that are still just compared
+constexpr int kTdCrowdMax = 64;       // ... after the buckets were cut
+// radix sort in global memory
+constexpr int kTdBits = 8, kTdBins = 1 << kTdBits, kTdPasses = 4;
 
 struct TileDepthArgs {
     const uint2 *ranges;
+    const uint32_t *order;      // launch order of the tiles, longest first
     const uint32_t *depth;      // [vn] depth key of each view-Gaussian
-    uint32_t *keys;             // sorted tile ids (scratch for long runs, then restored)
+    uint32_t *keys;             // sorted tile ids (scratch, then restored)
     uint32_t *vals;             // sorted values, put in depth order per tile in place
     uint32_t *akeys, *avals;    // [cap] the tile sort's other buffers (scratch)
+    const uint32_t *counters;
+    int short_cap;              // longest run of the kernel over all tiles
 };
 
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
@@ -328,6 +322,195 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return v;
 }
 
+// LDS of a workgroup of THREADS threads, ROUNDS entries each at most.
+template <int THREADS, int ROUNDS>
+struct TdShared {
+    static constexpr int kCap = THREADS * ROUNDS, kWaves = THREADS / kWave;
+    union {
+        struct {
+            uint32_t item[kCap];                      // (key bits below the bucket's, position)
+            __align__(16) uint32_t bucket[kCap];      // counts, starts, ends
+        };
+        struct {                                      // radix sort in global memory
+            unsigned long long msk[kWaves][kTdBins];  // lanes of a round by digit
+            uint32_t run[kWaves][kTdBins];            // digit counts, then starts
+            uint32_t hist[kTdPasses][kTdBins];
+        };
+    };
+    uint32_t part[2 * kWaves];
+};
+
+// The block's smallest lo and largest hi.  (Here and below t is threadIdx.x,
+// made opaque once per run where a workgroup sorts several: nothing derived
+// from it then stays in registers from run to run.)
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_reduce(TdShared<THREADS, ROUNDS> &sh, int t, uint32_t &lo, uint32_t &hi) {
+    const int w = t / kWave;
+    lo = wave_min_u32(lo);
+    hi = wave_max_u32(hi);
+    if (t % kWave == 0) {
+        sh.part[2 * w] = lo;
+        sh.part[2 * w + 1] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < THREADS / kWave; v++) {
+        lo = min(lo, sh.part[2 * v]);
+        hi = max(hi, sh.part[2 * v + 1]);
+    }
+}
+
+// Bucket counts -> exclusive starts, in place; returns the largest count.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ uint32_t td_scan(TdShared<THREADS, ROUNDS> &sh, int t) {
+    constexpr int kVecs = ROUNDS / 4;
+    uint4 *const b = reinterpret_cast<uint4 *>(sh.bucket) + kVecs * t;
+    uint4 c[kVecs];
+    uint32_t big = 0, s = 0;
+#pragma unroll
+    for (int j = 0; j < kVecs; j++) {
+        c[j] = b[j];
+        big = max(big, max(max(c[j].x, c[j].y), max(c[j].z, c[j].w)));
+        s += c[j].x + c[j].y + c[j].z + c[j].w;
+    }
+    const uint32_t inc = wave_inclusive_scan(s);
+    big = wave_max_u32(big);
+    const int w = t / kWave;
+    if (t % kWave == kWave - 1) {
+        sh.part[2 * w] = inc;
+        sh.part[2 * w + 1] = big;
+    }
+    __syncthreads();
+    uint32_t e = inc - s;
+#pragma unroll
+    for (int v = 0; v < THREADS / kWave; v++) {
+        e += v < w ? sh.part[2 * v] : 0u;
+        big = max(big, sh.part[2 * v + 1]);
+    }
+#pragma unroll
+    for (int j = 0; j < kVecs; j++) {
+        b[j] = make_uint4(e, e + c[j].x, e + c[j].x + c[j].y, e + c[j].x + c[j].y + c[j].z);
+        e += c[j].x + c[j].y + c[j].z + c[j].w;
+    }
+    __syncthreads();
+    return big;
+}
+
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_zero(TdShared<THREADS, ROUNDS> &sh, int t) {
+#pragma unroll
+    for (int j = 0; j < ROUNDS / 4; j++)
+        reinterpret_cast<uint4 *>(sh.bucket)[j * THREADS + t] = make_uint4(0, 0, 0, 0);
+}
+
+// Sorts a run of at most THREADS ROUNDS entries in LDS.  Returns false, with
+// nothing changed, if a bucket stays crowded.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh,
+                                            int t, uint32_t *vf, int L) {
+    constexpr uint32_t kCap = TdShared<THREADS, ROUNDS>::kCap;
+    constexpr int kLog = 31 - __builtin_clz(kCap);   // bits of a bucket, and of a position in the run
+    static_assert(kCap == 1u << kLog, "a power of two");
+    // Which entries a thread has is worked out afresh in each phase: the lane
+    // masks of all rounds, kept through the function, do not fit the scalar
+    // registers.
+    auto phase = [&]() { asm volatile("" : "+v"(t)); };
+    // (with 16 entries per thread the values are read again at the end: held,
+    // they would cost registers spilled to memory)
+    constexpr bool kReload = ROUNDS > 8;
+    uint32_t key[ROUNDS], val[ROUNDS], bin[ROUNDS];
+    auto load_values = [&]() {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            const int k = r * THREADS + t;
+            val[r] = k < L ? vf[k] : 0u;
+        }
+    };
+    load_values();
+    td_zero(sh, t);
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            key[r] = a.depth[val[r]];
+            kmin = min(kmin, key[r]);
+            kmax = max(kmax, key[r]);
+        }
+    }
+    td_reduce(sh, t, kmin, kmax);
+    if (kmin == kmax) return true;   // one depth: nothing moves
+    // Depths lie between the near plane and infinity, so a relative key has
+    // at most 31 bits, and those below the bucket's leave room for a position
+    // in an entry's word.
+    const int B = 32 - __clz(kmax - kmin), sft = B > kLog ? B - kLog : 0;
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            key[r] -= kmin;
+            bin[r] = key[r] >> sft;
+            atomicAdd(&sh.bucket[bin[r]], 1u);
+            key[r] &= (1u << sft) - 1u;
+        }
+    }
+    __syncthreads();
+    if (td_scan(sh, t) > kTdCrowd) {
+        // cut every bucket by the key's next bits into as many as it has
+        // entries: bucket b's start on, in place of b
+        phase();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * THREADS + t < L) {
+                const uint32_t s = sh.bucket[bin[r]], e = bin[r] + 1 < kCap ? sh.bucket[bin[r] + 1] : (uint32_t)L;
+                bin[r] = s + __umulhi(sft > 0 ? key[r] << (32 - sft) : 0u, e - s);
+            }
+        }
+        __syncthreads();
+        td_zero(sh, t);
+        __syncthreads();
+        phase();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++)
+            if (r * THREADS + t < L) atomicAdd(&sh.bucket[bin[r]], 1u);
+        __syncthreads();
+        if (td_scan(sh, t) > kTdCrowdMax) return false;
+    }
+    // to the buckets, in any order; bucket[b] ends as the end of b
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            key[r] = key[r] << kLog | (uint32_t)(r * THREADS + t);
+            sh.item[atomicAdd(&sh.bucket[bin[r]], 1u)] = key[r];
+        }
+    }
+    __syncthreads();
+    // bin[r] becomes the entry's place
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            const uint32_t s = bin[r] > 0 ? sh.bucket[bin[r] - 1] : 0u, e = sh.bucket[bin[r]];
+            bin[r] = s;
+            for (uint32_t j = s; j < e; j++) bin[r] += sh.item[j] < key[r] ? 1u : 0u;
+        }
+    }
+    phase();
+    if (kReload) load_values();
+    __syncthreads();
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) sh.item[bin[r]] = val[r];
+    __syncthreads();
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) vf[r * THREADS + t] = sh.item[r * THREADS + t];
+    return true;
+}
+
 // Rank of the lane's item among the lanes of its round with the same digit,
 // plus run[d], the count of d in earlier rounds.  The lanes with digit d find
 // each other through msk[d]: each ORs its lane bit in, then reads the mask
@@ -335,9 +518,8 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 // lands before any read); the lowest of them advances run[d] and clears
 // msk[d] for the next round.  msk must be zero on entry and is zero again on
 // return.
-__device__ __forceinline__ uint32_t td_rank(bool valid, uint32_t d, uint32_t *run,
+__device__ __forceinline__ uint32_t td_rank(int lane, bool valid, uint32_t d, uint32_t *run,
                                             unsigned long long *msk) {
-    const int lane = threadIdx.x;
     const unsigned long long lt = (1ull << lane) - 1ull;
     if (valid) atomicOr(&msk[d], 1ull << lane);
     const unsigned long long peers = valid ? msk[d] : 0ull;
@@ -350,257 +532,121 @@ __device__ __forceinline__ uint32_t td_rank(bool valid, uint32_t d, uint32_t *ru
     return base + below;
 }
 
-// run[] (digit counts of BINS digits) -> exclusive starts, in place.
-template <int BINS>
-__device__ __forceinline__ void td_scan(uint32_t *run) {
-    constexpr int kTdPerLane = BINS / kWave;
-    const int lane = threadIdx.x;
-    uint32_t c[kTdPerLane], s = 0;
-#pragma unroll
-    for (int j = 0; j < kTdPerLane; j++) {
-        c[j] = run[kTdPerLane * lane + j];
-        s += c[j];
-    }
-    uint32_t e = wave_inclusive_scan(s) - s;
-#pragma unroll
-    for (int j = 0; j < kTdPerLane; j++) {
-        run[kTdPerLane * lane + j] = e;
-        e += c[j];
-    }
+// A run in global memory, sorted LSD over 8-bit digits of the relative depth
+// keys: the smallest key, then the histograms of every pass from two reads of
+// the run (keys gathered), then the passes (skipped where every digit is
+// zero), each a stable counting sort: a chunk's items counted per wavefront,
+// the counts' starts, then each wavefront's ranks on top of them.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_sort_global(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh,
+                                               int t, uint32_t rgx, uint32_t tile, int L) {
+    constexpr int kWaves = THREADS / kWave, kSeg = ROUNDS * kWave;
+    const int lane = t & (kWave - 1), w = t / kWave;
+    uint32_t *const kf = a.keys + rgx, *const vf = a.vals + rgx;
+    uint32_t kmin = 0xffffffffu, unused = 0u;
+    for (int k = t; k < L; k += THREADS) kmin = min(kmin, a.depth[vf[k]]);
     __syncthreads();
-}
-
-template <int BINS>
-__device__ __forceinline__ void td_zero(uint32_t *run) {
-    constexpr int kTdPerLane = BINS / kWave;
-#pragma unroll
-    for (int j = 0; j < kTdPerLane; j++) run[kTdPerLane * threadIdx.x + j] = 0u;
-}
-
-// An overflowing forward emits no instance and leaves every range empty, so
-// the kernel needs no overflow test.
-template <int CAP>
-__global__ __launch_bounds__(kWave) void k_tile_depth_sort(TileDepthArgs a) {
-    constexpr int kTdCap = CAP;
-    constexpr int kTdRounds = kTdCap / kWave;
-    constexpr int kIdx = CAP == 2048 ? 11 : 10;   // bits of a position in the run
-    static_assert((1 << kIdx) == kTdCap, "CAP is 1024 or 2048");
-    // the run's packed items (long runs: the histograms of all passes instead)
-    __shared__ uint32_t buf[kTdCap];
-    __shared__ uint32_t run[kTdBins];
-    __shared__ unsigned long long msk[kTdBins];
-    static_assert(kTdLPasses * kTdLBins <= kTdCap, "histograms of a long run fit in buf");
-    const uint32_t tile = blockIdx.x;
-    const uint2 rg = a.ranges[tile];
-    const int L = (int)(rg.y - rg.x);
-    if (L <= 1) return;
-    const int lane = threadIdx.x;
-    uint32_t key[kTdRounds], val[kTdRounds];
-    uint32_t *const kf = a.keys + rg.x, *const vf = a.vals + rg.x;
-#pragma unroll
-    for (int j = 0; j < kTdBins / kWave; j++) msk[kTdBins / kWave * lane + j] = 0ull;
-
-    if (L <= kTdCap) {
-#pragma unroll
-        for (int r = 0; r < kTdRounds; r++) {
-            const int k = r * kWave + lane;
-            val[r] = k < L ? vf[k] : 0u;
-        }
-        uint32_t kmin = 0xffffffffu, kmax = 0u;
-#pragma unroll
-        for (int r = 0; r < kTdRounds; r++) {
-            const int k = r * kWave + lane;
-            key[r] = k < L ? a.depth[val[r]] : 0u;
-            if (k < L) {
-                kmin = min(kmin, key[r]);
-                kmax = max(kmax, key[r]);
-            }
-        }
-        kmin = wave_min_u32(kmin);
-        kmax = wave_max_u32(kmax);
-        // significant bits of the relative keys; runs whose keys span more
-        // than 32 - kIdx + 8 bits (depths over some sixty binary orders of
-        // magnitude) take the long path below
-        const int B = kmax > kmin ? 32 - __clz(kmax - kmin) : 0;
-        if (B <= 32 - kIdx + kTdBits) {
-            // An item is one word: after the first pass, the relative key's
-            // bits above that pass's digit, shifted over the item's position
-            // in the run (kIdx bits); the values follow by that position at
-            // the end.  One LDS word per item and pass, not two.
-            uint32_t pk[kTdRounds], rk[kTdRounds];
-            bool moved = false;
-            // One counting-sort pass over digit d(r) of the items pk (the
-            // first pass's items and digits come from the relative keys).
-            auto sort_pass = [&](auto digit_of, auto item_of) {
-                uint32_t dlo = kTdBins, dhi = 0;
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++) {
-                    if (r * kWave + lane < L) {
-                        const uint32_t d = digit_of(r);
-                        dlo = min(dlo, d);
-                        dhi = max(dhi, d);
-                    }
-                }
-                if (wave_min_u32(dlo) == wave_max_u32(dhi)) {   // one digit: nothing moves
-#pragma unroll
-                    for (int r = 0; r < kTdRounds; r++) pk[r] = item_of(r);
-                    return;
-                }
-                moved = true;
-                td_zero<kTdBins>(run);
-                __syncthreads();
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++) {
-                    rk[r] = 0u;
-                    if (r * kWave >= L) continue;   // uniform
-                    const bool valid = r * kWave + lane < L;
-                    rk[r] = td_rank(valid, digit_of(r), run, msk);
-                }
-                __syncthreads();
-                td_scan<kTdBins>(run);
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++)
-                    if (r * kWave + lane < L) buf[run[digit_of(r)] + rk[r]] = item_of(r);
-                __syncthreads();
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++) {
-                    const int k = r * kWave + lane;
-                    pk[r] = k < L ? buf[k] : 0u;
-                }
-                __syncthreads();
-            };
-            // pass 0: the relative keys' low digit; items become (key bits
-            // above it, position)
-#pragma unroll
-            for (int r = 0; r < kTdRounds; r++) key[r] -= kmin;
-            sort_pass([&](int r) { return key[r] & (kTdBins - 1); },
-                      [&](int r) { return ((key[r] >> kTdBits) << kIdx) | (uint32_t)(r * kWave + lane); });
-            const int npass = (B + kTdBits - 1) / kTdBits;
-            for (int p = 1; p < npass; p++) {
-                const int sh = kIdx + kTdBits * (p - 1);
-                sort_pass([&](int r) { return (pk[r] >> sh) & (kTdBins - 1); }, [&](int r) { return pk[r]; });
-            }
-            if (moved) {
-                // every value read (by its position in the run) before any is written
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++) {
-                    const int k = r * kWave + lane;
-                    val[r] = k < L ? vf[pk[r] & (kTdCap - 1)] : 0u;
-                }
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++) {
-                    const int k = r * kWave + lane;
-                    if (k < L) vf[k] = val[r];
-                }
-            }
-            return;
-        }
-    }
-
-    // Long run.  The smallest key, then the histograms of every pass of the
-    // relative keys, from two reads of the run (keys gathered).
-    uint32_t kmin = 0xffffffffu;
-    for (int c0 = 0; c0 < L; c0 += kTdCap) {
-#pragma unroll
-        for (int r = 0; r < kTdRounds; r++) {
-            const int k = c0 + r * kWave + lane;
-            val[r] = k < L ? vf[k] : 0u;
-        }
-#pragma unroll
-        for (int r = 0; r < kTdRounds; r++) {
-            const int k = c0 + r * kWave + lane;
-            if (k < L) kmin = min(kmin, a.depth[val[r]]);
-        }
-    }
-    kmin = wave_min_u32(kmin);
-    uint32_t *const hist = buf;   // [kTdLPasses][kTdLBins]
-    for (int i = lane; i < kTdLPasses * kTdLBins; i += kWave) hist[i] = 0u;
+    td_reduce(sh, t, kmin, unused);
+    for (int i = t; i < kTdPasses * kTdBins; i += THREADS) (&sh.hist[0][0])[i] = 0u;
+    for (int i = lane; i < kTdBins; i += kWave) sh.msk[w][i] = 0ull;
     __syncthreads();
-    for (int c0 = 0; c0 < L; c0 += kTdCap) {
+    for (int k = t; k < L; k += THREADS) {
+        const uint32_t kk = a.depth[vf[k]] - kmin;
 #pragma unroll
-        for (int r = 0; r < kTdRounds; r++) {
-            const int k = c0 + r * kWave + lane;
-            val[r] = k < L ? vf[k] : 0u;
-        }
-#pragma unroll
-        for (int r = 0; r < kTdRounds; r++) {
-            const int k = c0 + r * kWave + lane;
-            if (k < L) {
-                const uint32_t kk = a.depth[val[r]] - kmin;
-#pragma unroll
-                for (int p = 0; p < kTdLPasses; p++)
-                    atomicAdd(&hist[p * kTdLBins + ((kk >> (kTdLBits * p)) & (kTdLBins - 1))], 1u);
-            }
-        }
+        for (int p = 0; p < kTdPasses; p++) atomicAdd(&sh.hist[p][(kk >> (kTdBits * p)) & (kTdBins - 1)], 1u);
     }
     __syncthreads();
     // source of the next pass: (keys gathered | skey, sval), destination (dkey, dval)
-    uint32_t *skey = nullptr, *sval = vf, *dkey = a.akeys + rg.x, *dval = a.avals + rg.x;
+    uint32_t *skey = nullptr, *sval = vf, *dkey = a.akeys + rgx, *dval = a.avals + rgx;
     bool kf_used = false;
-    for (int p = 0; p < kTdLPasses; p++) {
-        const int sh = kTdLBits * p;
-        constexpr int kTdPerLane = kTdLBins / kWave;
-        bool full = false;
-#pragma unroll
-        for (int j = 0; j < kTdPerLane; j++) {
-            const uint32_t c = hist[p * kTdLBins + kTdPerLane * lane + j];
-            full |= c == (uint32_t)L;
-            run[kTdPerLane * lane + j] = c;
-        }
-        if (wave_any(full)) continue;   // one digit: nothing moves
+    for (int p = 0; p < kTdPasses; p++) {
+        const int sft = kTdBits * p;
+        if (sh.hist[p][0] == (uint32_t)L) continue;   // all zero: nothing moves
         __syncthreads();
-        td_scan<kTdLBins>(run);
-        for (int c0 = 0; c0 < L; c0 += kTdCap) {
+        if (w == 0) {   // counts -> starts of the digits, four per lane
+            uint32_t *const h = &sh.hist[p][4 * lane];
+            const uint32_t c0 = h[0], c1 = h[1], c2 = h[2], c3 = h[3];
+            const uint32_t e = wave_inclusive_scan(c0 + c1 + c2 + c3) - (c0 + c1 + c2 + c3);
+            h[0] = e;
+            h[1] = e + c0;
+            h[2] = e + c0 + c1;
+            h[3] = e + c0 + c1 + c2;
+        }
+        auto key_of = [&](int k) { return skey ? skey[k] : a.depth[sval[k]] - kmin; };
+        for (int c0 = 0; c0 < L; c0 += THREADS * ROUNDS) {
+            const int k0 = c0 + w * kSeg, end = min(L, k0 + kSeg);
+            for (int i = lane; i < kTdBins; i += kWave) sh.run[w][i] = 0u;
+            __syncthreads();
+            for (int k = k0 + lane; k < end; k += kWave)
+                atomicAdd(&sh.run[w][(key_of(k) >> sft) & (kTdBins - 1)], 1u);
+            __syncthreads();
+            for (int d = t; d < kTdBins; d += THREADS) {
+                uint32_t e = sh.hist[p][d];
 #pragma unroll
-            for (int r = 0; r < kTdRounds; r++) {
-                const int k = c0 + r * kWave + lane;
-                val[r] = k < L ? sval[k] : 0u;
-                key[r] = k < L && skey ? skey[k] : 0u;
+                for (int v = 0; v < kWaves; v++) {
+                    const uint32_t c = sh.run[v][d];
+                    sh.run[v][d] = e;
+                    e += c;
+                }
+                sh.hist[p][d] = e;
             }
-            if (!skey) {
-#pragma unroll
-                for (int r = 0; r < kTdRounds; r++) {
-                    const int k = c0 + r * kWave + lane;
-                    key[r] = k < L ? a.depth[val[r]] - kmin : 0u;
+            __syncthreads();
+#pragma unroll 1
+            for (int r0 = k0; r0 < end; r0 += kWave) {
+                const int k = r0 + lane;
+                const uint32_t key = k < end ? key_of(k) : 0u;
+                const uint32_t pos = td_rank(lane, k < end, (key >> sft) & (kTdBins - 1), sh.run[w], sh.msk[w]);
+                if (k < end) {
+                    dkey[pos] = key;
+                    dval[pos] = sval[k];
                 }
             }
-#pragma unroll
-            for (int r = 0; r < kTdRounds; r++) {
-                if (c0 + r * kWave >= L) break;   // uniform
-                const bool valid = c0 + r * kWave + lane < L;
-                const uint32_t pos = td_rank(valid, (key[r] >> sh) & (kTdLBins - 1), run, msk);
-                if (valid) {
-                    dkey[pos] = key[r];
-                    dval[pos] = val[r];
-                }
-            }
+            __syncthreads();
         }
-        // the next pass reads what every lane wrote
-        __syncthreads();
         kf_used |= dkey == kf;
-        uint32_t *const nk = dkey == kf ? a.akeys + rg.x : kf;
-        uint32_t *const nv = dval == vf ? a.avals + rg.x : vf;
+        uint32_t *const nk = dkey == kf ? a.akeys + rgx : kf;
+        uint32_t *const nv = dval == vf ? a.avals + rgx : vf;
         skey = dkey;
         sval = dval;
         dkey = nk;
         dval = nv;
     }
-    if (sval != vf) {
-        for (int c0 = 0; c0 < L; c0 += kTdCap) {
-#pragma unroll
-            for (int r = 0; r < kTdRounds; r++) {
-                const int k = c0 + r * kWave + lane;
-                val[r] = k < L ? sval[k] : 0u;
-            }
-#pragma unroll
-            for (int r = 0; r < kTdRounds; r++) {
-                const int k = c0 + r * kWave + lane;
-                if (k < L) vf[k] = val[r];
-            }
-        }
-    }
+    if (sval != vf)
+        for (int k = t; k < L; k += THREADS) vf[k] = sval[k];
     if (kf_used)
-        for (int k = lane; k < L; k += kWave) kf[k] = tile;
+        for (int k = t; k < L; k += THREADS) kf[k] = tile;
+    __syncthreads();
+}
+
+// Workgroup b takes tile b, so that its first load is its range.  An
+// overflowing forward emits no instance and leaves every range empty, so
+// neither kernel needs an overflow test.
+template <int THREADS, int ROUNDS>
+__global__ __launch_bounds__(THREADS) void k_tile_depth_sort(TileDepthArgs a) {
+    __shared__ TdShared<THREADS, ROUNDS> sh;
+    const uint32_t tile = blockIdx.x;
+    const uint2 rg = a.ranges[tile];
+    const int L = (int)(rg.y - rg.x);
+    if (L <= 1 || L > THREADS * ROUNDS) return;
+    const int t = threadIdx.x;
+    if (!td_sort_lds(a, sh, t, a.vals + rg.x, L)) td_sort_global(a, sh, t, rg.x, tile, L);
+}
+
+// The longer runs, at the front of the launch order.
+constexpr int kTdLongThreads = 512, kTdLongRounds = 16;
+__global__ __launch_bounds__(kTdLongThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_tile_depth_sort_long(TileDepthArgs a) {
+    __shared__ TdShared<kTdLongThreads, kTdLongRounds> sh;
+    const uint32_t nlong = a.counters[a.short_cap == 1024 ? kCntOver1024 : kCntOver2048];
+    for (uint32_t r = blockIdx.x; r < nlong; r += gridDim.x) {
+        const uint32_t tile = a.order[r];
+        const uint2 rg = a.ranges[tile];
+        const int L = (int)(rg.y - rg.x);
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        __syncthreads();
+        if (L > kTdLongThreads * kTdLongRounds || !td_sort_lds(a, sh, t, a.vals + rg.x, L))
+            td_sort_global(a, sh, t, rg.x, tile, L);
+    }
 }
 
 hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s) {
@@ -608,17 +654,27 @@ hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s) {
     TileDepthArgs a;
     const bool odd = sorted_vals(L) == L.vals1;
     a.ranges = region<uint2>(ws, L.ranges);
+    a.order = region<uint32_t>(ws, L.tile_order);
     a.depth = region<uint32_t>(ws, L.depth);
     a.keys = region<uint32_t>(ws, sorted_keys(L));
     a.vals = region<uint32_t>(ws, sorted_vals(L));
     a.akeys = region<uint32_t>(ws, odd ? L.keys0 : L.keys1);
     a.avals = region<uint32_t>(ws, odd ? L.vals0 : L.vals1);
-    // lists longer than 1024 on average (at the 1.5x capacity margin) take the
-    // 2048-entry variant, whose larger LDS share lowers the waves per CU
-    if (L.cap > (int64_t)1536 * L.total_tiles)
-        hipLaunchKernelGGL(k_tile_depth_sort<2048>, dim3(L.total_tiles), dim3(kWave), 0, s, a);
+    a.counters = region<uint32_t>(ws, L.counters);
+    // Lists longer than 1024 on average (at the 1.5x capacity margin) take
+    // eight entries per thread, which keep them in this launch; for lists of
+    // 500 four per thread measured 15.8 us against 16.3, of 700 42.8 against
+    // 45.4 us.  (128 threads of eight: 15.5 and 46.9 us.)
+    const bool mid = L.cap > (int64_t)1536 * L.total_tiles;
+    a.short_cap = mid ? 2048 : 1024;
+    if (mid)
+        hipLaunchKernelGGL((k_tile_depth_sort<256, 8>), dim3(L.total_tiles), dim3(256), 0, s, a);
     else
-        hipLaunchKernelGGL(k_tile_depth_sort<1024>, dim3(L.total_tiles), dim3(kWave), 0, s, a);
+        hipLaunchKernelGGL((k_tile_depth_sort<256, 4>), dim3(L.total_tiles), dim3(256), 0, s, a);
+    // a list holds a splat once at most; two of these workgroups fit a CU
+    if (L.n > a.short_cap)
+        hipLaunchKernelGGL(k_tile_depth_sort_long, dim3(L.total_tiles < 512 ? L.total_tiles : 512),
+                           dim3(kTdLongThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -178,6 +178,40 @@ def test_depth_ties_and_long_runs_bit_exact(cap):
     assert_sorted_match(keys, vals, rkeys, rvals, fragile)
 
 
+# one tile: list lengths at the edges of the per-tile sort's kernels (1024 or
+# 2048 entries by the capacity, 8192, beyond), with depths spread evenly,
+# crowded in two thin layers, crowded in layers of a few values (equal depths),
+# spread over some thirty octaves, or all but one equal
+@pytest.mark.parametrize("n,cap", [(2, 64), (1023, 1500), (1024, 1500), (1025, 1500), (1024, 4000),
+                                   (2048, 4000), (2049, 4000), (8192, 9000), (8193, 9000)])
+@pytest.mark.parametrize("kind", ["spread", "layers", "ties", "octaves", "one"])
+def test_tile_depth_order_bit_exact(n, cap, kind):
+    rng = S.rng_for(n, 3)
+    if kind == "spread":
+        z = rng.uniform(1.5, 8.0, n)
+    elif kind == "layers":
+        z = np.where(rng.random(n) < 0.3, 2.0, 6.0) * (1 + 1e-4 * rng.standard_normal(n))
+    elif kind == "ties":
+        z = rng.choice([1.0, 3.0, 3.0000005, 7.5], n)
+    elif kind == "octaves":
+        z = np.exp2(rng.uniform(-2.0, 30.0, n))
+    else:
+        z = np.where(np.arange(n) == n // 2, 1.0, 4.0)
+    cam = f32_camera(S.Camera(16, 16, 14.0, 14.0, 8.0, 8.0))
+    sc = S.random_scene(n, n, 0, cam)
+    sc.means[:] = np.concatenate([rng.uniform(-0.3, 0.3, (n, 2)) * z[:, None], z[:, None]], 1)
+    sc.scales[:] = 0.05 * z[:, None]
+    pose = S.identity_pose()
+    run = _gpu(sc, [cam], [pose], cap=cap)
+    ref = oracle.preprocess(sc, cam, pose)
+    assert not ref["fragile"].any() and ref["rendered"].all()
+    rkeys, rvals = oracle.bin_sort([ref], [(1, 1)])
+    M, ovf = run["rast"].instances()
+    assert M == n and not ovf
+    keys, vals = _sorted_instances(run["rast"], run["g"], [cam], M)
+    assert np.array_equal(keys, rkeys) and np.array_equal(vals, rvals)
+
+
 def test_keys_bit_exact_two_views():
     sc, cam0, pose0 = random_case(16, 2, 96, 64, 700)
     cam1 = f32_camera(S.Camera(80, 48, 75.0, 70.0, 40.5, 23.75, roi=(16, 16, 50, 32)))
