@@ -56,7 +56,7 @@ KERNEL_SOURCES = {
     "raster_fwd": ["raster_fwd.hip", "raster_common.h", "gsp_internal.h"],
     "raster_bwd": ["raster_bwd.hip", "raster_common.h", "gsp_internal.h"],
     "preprocess": ["preprocess.hip"],
-    "tile_sort": ["sort.hip"],
+    "tile_sort": ["binning.hip"],
     "depth_order": ["sort.hip"],
     "preprocess_bwd": ["preprocess_bwd.hip"],
 }

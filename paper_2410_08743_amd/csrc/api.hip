@@ -197,17 +197,10 @@ Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views,
     for (int v = 0; v < V; v++) pix += (int64_t)views.v[v].roi_w * views.v[v].roi_h;
     L.total_pix = pix;
     L.nblk_pre = (int)((n + kPreprocessBlock - 1) / kPreprocessBlock);
-    L.nblk_scan = (int)((L.vn + kScanItems - 1) / kScanItems);
-    L.sort_items = sort_items_for(L.cap);
-    L.nblk_sort = (int)((L.cap + L.sort_items - 1) / L.sort_items);
-    L.nblk_emit = L.nblk_sort;   // emission blocks are the instance sort's first-pass blocks
-    L.tile_bits = tile_bits_for(views.total_tiles);
-    {
-        // packed instance-sort items when the tile id and the value fit one word
-        const int vbits = L.vn > 1 ? 64 - __builtin_clzll((unsigned long long)(L.vn - 1)) : 1;
-        L.sort_vbits = L.tile_bits > 0 && L.tile_bits + vbits <= 32 ? vbits : 0;
-    }
-    L.tile_passes = sort_passes(L.tile_bits);
+    int64_t most_tiles = 1;
+    for (int v = 0; v < V; v++) most_tiles = std::max(most_tiles, (int64_t)views.v[v].gw * views.v[v].gh);
+    L.bin_chunks = bin_chunks_for(n, V, L.cap, most_tiles, std::max(L.total_tiles, 1));
+    L.bin_chunk_splats = L.bin_chunks > 0 ? (int)((n + L.bin_chunks - 1) / L.bin_chunks) : 0;
     L.nwin_max = (int)((L.vn + L.cap + kWindow - 1) / kWindow + 1);
     const size_t vn = (size_t)L.vn, capz = (size_t)L.cap;
     size_t off = 0;
@@ -223,18 +216,14 @@ Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views,
     L.depth = take(vn * 4);
     L.tiles = take(vn * 4);
     L.offsets = take((vn + 1) * 4);
-    L.vis = take(vn * 4);
-    L.offv = take((vn + 1) * 4);
     L.wstart = take(((size_t)L.nwin_max + 1) * 8);
-    L.pstart = take(((size_t)L.nblk_emit + 1) * 4);
-    L.blocksum = take((size_t)L.nblk_scan * 8 + 8);
-    L.blockvis = take((size_t)L.nblk_scan * 4 + 4);
-    L.keys0 = take(capz * 4);
-    L.keys1 = take(capz * 4);
-    L.vals0 = take(capz * 4);
-    L.vals1 = take(capz * 4);
-    L.hist = take((size_t)kSortBins * L.nblk_sort * 4);
-    L.digit_tot = take((size_t)kSortBins * 4);
+    L.binmat = take((size_t)L.bin_chunks * L.total_tiles * 4);
+    L.tiletotal = take((size_t)L.total_tiles * 4);
+    L.groupsum = take(((size_t)L.total_tiles + 63) / 64 * 8);
+    L.chunksum = take((size_t)V * L.bin_chunks * 8);
+    L.chunkstart = take((size_t)V * L.bin_chunks * 4);
+    L.pairs = take(capz * 8);
+    L.vals = take(capz * 4);
     L.ranges = take((size_t)L.total_tiles * 8);
     L.tile_order = take((size_t)L.total_tiles * 4);
     // Every chunk in front of a cut holds kChunk entries, so there are at
@@ -429,18 +418,15 @@ gsp_status render_fwd(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gsp
              return gsp::launch_preprocess(gk, p.views, poses, p.L, ws, st);
          })) != hipSuccess)
         return hip_fail(e, "preprocess");
-    if ((e = stage(ctx, "duplicate", st, [&] {
-             return gsp::launch_offsets_and_duplicate(p.views, p.L, ws, st);
-         })) != hipSuccess)
+    if ((e = stage(ctx, "duplicate", st, [&] { return gsp::launch_bin_count(p.views, p.L, ws, st); })) !=
+        hipSuccess)
         return hip_fail(e, "duplicate");
-    if ((e = stage(ctx, "tile_sort", st, [&] { return gsp::launch_tile_sort(p.L, ws, st); })) !=
+    if ((e = stage(ctx, "ranges", st, [&] { return gsp::launch_bin_scan(p.L, ws, st); })) != hipSuccess)
+        return hip_fail(e, "ranges");
+    if ((e = stage(ctx, "tile_sort", st, [&] { return gsp::launch_bin_scatter(p.views, p.L, ws, st); })) !=
         hipSuccess)
         return hip_fail(e, "tile sort");
-    const uint32_t *keys = gsp::region<uint32_t>(ws, gsp::sorted_keys(p.L));
-    const uint32_t *vals = gsp::region<uint32_t>(ws, gsp::sorted_vals(p.L));
-    if ((e = stage(ctx, "ranges", st, [&] { return gsp::launch_ranges(p.L, ws, keys, st); })) !=
-        hipSuccess)
-        return hip_fail(e, "ranges");
+    const uint32_t *vals = gsp::region<uint32_t>(ws, p.L.vals);
     if ((e = stage(ctx, "depth_order", st, [&] { return gsp::launch_tile_depth_sort(p.L, ws, st); })) !=
         hipSuccess)
         return hip_fail(e, "depth order");
@@ -540,7 +526,7 @@ gsp_status render_bwd(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gsp
     if (lists && (s = check_lists(p.L, lists, lists_bytes, pair_capacity, &Q)) != GSP_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
-    const uint32_t *vals = gsp::region<uint32_t>(ws, gsp::sorted_vals(p.L));
+    const uint32_t *vals = gsp::region<uint32_t>(ws, p.L.vals);
     hipError_t e;
     if ((e = stage(ctx, "raster_bwd", st, [&] {
              return lists ? gsp::launch_raster_bwd_stored(p.views, p.L, ws, vals, Q,
@@ -639,8 +625,8 @@ gsp_status gsp_inspect(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gs
         {"depth", L.depth, L.vn},
         {"tiles", L.tiles, L.vn},
         {"offsets", L.offsets, L.vn},
-        {"keys", gsp::sorted_keys(L), L.cap},
-        {"values", gsp::sorted_vals(L), L.cap},
+        {"keys", L.pairs, L.cap},
+        {"values", L.vals, L.cap},
         {"ranges", L.ranges, L.total_tiles},
         {"tfinal", L.tfinal, L.total_pix},
         {"ncontrib", L.ncontrib, L.total_pix},
@@ -651,6 +637,14 @@ gsp_status gsp_inspect(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gs
     };
     for (const Entry &en : table) {
         if (std::strcmp(en.n, name) == 0) {
+            if (en.off == L.pairs) {
+                // the instances carry no tile id: written now, from the
+                // ranges that whatever stream filled
+                hipError_t e = hipDeviceSynchronize();
+                if (e == hipSuccess) e = gsp::launch_tile_ids(L, ws, nullptr);
+                if (e == hipSuccess) e = hipDeviceSynchronize();
+                if (e != hipSuccess) return hip_fail(e, "tile ids");
+            }
             *ptr = ws + en.off;
             *count = en.cnt;
             return GSP_OK;

@@ -28,29 +28,29 @@ constexpr float kTMin = 1e-4f;           // stop before transmittance drops belo
 constexpr double kLog2e = 1.4426950408889634;
 
 constexpr int kPreprocessBlock = 256;    // Gaussians per preprocess block
-constexpr int kSortThreads = 256;
-// Keys per block of the instance sort (and per emission block): 1024, or
-// 2048 above kSortLargeCap instances of capacity, where a 7-bit digit pass
-// (more than 4096 tiles) would otherwise leave runs of 8 keys per digit and
-// block, and the scatter's writes would cover half 64-byte segments
-// (measured at 1M Gaussians, 4 views: tile sort 0.296 -> 0.233 ms; at one
-// 1008 x 756 view the larger blocks cost 2 us).
-constexpr int kSortRoundsSmall = 4, kSortRoundsLarge = 8;
-constexpr int64_t kSortLargeCap = (int64_t)6 << 20;
-inline int sort_items_for(int64_t cap) {
-    return kSortThreads * (cap > kSortLargeCap ? kSortRoundsLarge : kSortRoundsSmall);
+// Chunks of a view's splats in the binning: one workgroup counts and writes the
+// instances of one chunk, one workgroup to a CU.  The chunks of all views fill
+// whole rounds of 248 CUs (the chip's 256 but for the one that orders the tiles
+// meanwhile and what whole eights of chunks leave over): two rounds, or as many
+// as it takes that the chunks of the largest view, by its share of the
+// capacity (1.25 to 1.5 times the instances), stay in LDS (kBinStage entries,
+// binning.hip).  A view has at most 248, and fewer where they would hold less
+// than 256 splats (a workgroup's fixed work is a few microseconds, and every
+// chunk has a count per tile).
+constexpr int kBinChunks = 248;
+inline int bin_chunks_for(int64_t n, int V, int64_t cap, int64_t most_tiles, int64_t total_tiles) {
+    const double need = (double)cap * (double)most_tiles / (double)total_tiles / 36000.0;
+    const int64_t rounds = (int64_t)(need * V / kBinChunks) + 1;
+    int64_t c = kBinChunks * (rounds < 2 ? 2 : rounds) / V;
+    const int64_t by_n = (n + 255) / 256;
+    if (c > by_n) c = by_n;
+    return (int)(c < kBinChunks ? c : kBinChunks);
 }
-constexpr int kSortBits = 8;             // radix digit width
-constexpr int kSortBins = 1 << kSortBits;
 constexpr int kPoseReduceBlock = 256;
 // Rows of per-wavefront pose partials per preprocess-backward block.
 constexpr int kPoseRowsPerBlock = kPoseReduceBlock / 64;
-// Instance-offset scan over the depth-sorted splats: splats per thread and
-// per block.
-constexpr int kScanPerThread = 4;
-constexpr int kScanItems = kPreprocessBlock * kScanPerThread;
-// Work windows of the instance emission and of the slot reduction: the
-// sequence of splats in depth order, each followed by its instances, is cut
+// Work windows of the slot reduction: the
+// sequence of splats in index order, each followed by its instances, is cut
 // into pieces of kWindow items, and a block takes the splats whose entry
 // falls in its piece.  Every block then sees at most kWindow splats and
 // kWindow instances plus the tail of its last splat, however unevenly the
@@ -123,14 +123,10 @@ struct ViewsK {
 // Carving of the caller's workspace.  Every region is 256-byte aligned.
 struct Layout {
     int64_t n, vn, cap, total_pix;
-    int32_t V, S, total_tiles, nblk_pre, nblk_scan, nblk_sort, nblk_emit, sort_items, tile_bits,
-        tile_passes, nwin_max;
-    // value bits of the instance sort's packed items (tile id above them),
-    // or 0 when tile and value bits exceed 32 together (key and value arrays)
-    int32_t sort_vbits;
-    size_t geom, color, rect, depth, tiles, offsets, vis, offv, wstart, pstart, blocksum, blockvis,
-        counters;
-    size_t keys0, keys1, vals0, vals1, hist, digit_tot, ranges, tile_order;
+    int32_t V, S, total_tiles, nblk_pre, bin_chunks, bin_chunk_splats, nwin_max;
+    size_t geom, color, rect, depth, tiles, offsets, wstart, counters;
+    size_t binmat, tiletotal, groupsum, chunksum, chunkstart;   // counts of the binning
+    size_t pairs, vals, ranges, tile_order;
     size_t items, ckpt, cfinal;   // backward work items, states at the cuts, final colours
     int64_t max_items;
     size_t tfinal, ncontrib, stats, slots, slot_flags, grad2d, posepart, l1part;
@@ -179,13 +175,15 @@ struct ListLayout {
 // preprocess.hip
 hipError_t launch_preprocess(const GaussiansK &g, const ViewsK &views, const float *poses,
                              const Layout &L, char *ws, hipStream_t s);
-hipError_t launch_offsets_and_duplicate(const ViewsK &views, const Layout &L, char *ws,
-                                        hipStream_t s);
+// binning.hip
+hipError_t launch_bin_count(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
+hipError_t launch_bin_scan(const Layout &L, char *ws, hipStream_t s);
+hipError_t launch_bin_scatter(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
+// Writes the tile id of every sorted instance over the pairs region.
+hipError_t launch_tile_ids(const Layout &L, char *ws, hipStream_t s);
 // sort.hip
-hipError_t launch_tile_sort(const Layout &L, char *ws, hipStream_t s);
 hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s);
 // raster_fwd.hip
-hipError_t launch_ranges(const Layout &L, char *ws, const uint32_t *keys, hipStream_t s);
 // l1: each view's img receives dL/dimage of the L1 loss against the target
 // its dl points to; with `loss`, the loss of each view goes there as well.
 hipError_t launch_raster_fwd(const ViewsK &views, const Layout &L, char *ws,
@@ -301,25 +299,5 @@ hipError_t launch_masked_l1(const MaskViewsK &a, float *loss, void *scratch, hip
 
 template <typename T>
 inline T *region(char *ws, size_t off) { return reinterpret_cast<T *>(ws + off); }
-
-inline int tile_bits_for(int total_tiles) {
-    int tile_bits = 0;
-    while ((1ll << tile_bits) < (long long)total_tiles) tile_bits++;
-    return tile_bits;
-}
-
-// Passes of a radix sort on `bits` key bits, and the digit width of each:
-// the bits are shared out evenly (12 bits: two 6-bit passes rather than 8 +
-// 4), which keeps the digit runs of the first pass long enough for
-// full-line stores.
-inline int sort_passes(int bits) { return (bits + kSortBits - 1) / kSortBits; }
-inline int digit_bits(int bits) {
-    const int p = sort_passes(bits);
-    return p > 0 ? (bits + p - 1) / p : 0;
-}
-
-// Buffers holding the result of the two sorts (depth: 4 passes, even).
-inline size_t sorted_keys(const Layout &L) { return (L.tile_passes & 1) ? L.keys1 : L.keys0; }
-inline size_t sorted_vals(const Layout &L) { return (L.tile_passes & 1) ? L.vals1 : L.vals0; }
 
 }  // namespace gsp

@@ -1,5 +1,4 @@
-// preprocess.hip -- projection of every Gaussian into every view of a call,
-// and duplication of each projected splat into its tile instances.
+// preprocess.hip -- projection of every Gaussian into every view of a call.
 //
 // Sec. III-A: Sigma = R(q) diag(s)^2 R(q)^T (Eq. (1)); mu_hat = pi(K T mu);
 // Sigma_hat = [J R_c Sigma R_c^T J^T]_2x2 (Eq. (2)) plus a 0.3 px^2
@@ -176,262 +175,6 @@ __global__ __launch_bounds__(kPreprocessBlock) void k_preprocess(PreArgs a, View
     }
 }
 
-// Per-block sums of the tile counts of the view-Gaussians in index order
-// (kScanItems per block, kScanPerThread consecutive ones per thread), and
-// the number of them with at least one instance.
-__global__ __launch_bounds__(kPreprocessBlock) void k_blocksums(const uint32_t *tiles,
-                                                                unsigned long long *bs,
-                                                                uint32_t *bvis, int vn) {
-    __shared__ unsigned long long red[kPreprocessBlock / kWave];
-    const int k0 = blockIdx.x * kScanItems + kScanPerThread * threadIdx.x;
-    unsigned long long cnt = 0, vis = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPerThread; j++) {
-        const uint32_t c = k0 + j < vn ? tiles[k0 + j] : 0u;
-        cnt += c;
-        vis += c > 0 ? 1ull : 0ull;
-    }
-    const unsigned long long s = block_sum<unsigned long long, kPreprocessBlock>(cnt, red);
-    const unsigned long long v = block_sum<unsigned long long, kPreprocessBlock>(vis, red);
-    if (threadIdx.x == 0) {
-        bs[blockIdx.x] = s;
-        bvis[blockIdx.x] = (uint32_t)v;
-    }
-}
-
-struct DupArgs {
-    const uint2 *rect;
-    const uint32_t *tiles;
-    uint32_t *offsets;             // [vn + 1] first emission position of each view-Gaussian, then M
-    uint32_t *vis;                 // [vn] the view-Gaussians with instances, in index order
-    uint32_t *offv;                // [vn + 1] first emission position of each of those, then M
-    uint2 *wstart;                 // [windows + 1] first view-Gaussian of each work window and its first slot
-    uint32_t *pstart;              // [emission blocks + 1] rank in vis owning each block's start
-    const unsigned long long *blocksum;  // [nblk] per-block tile counts in index order
-    const uint32_t *blockvis;      // [nblk] per-block counts of view-Gaussians with instances
-    uint32_t *counters;
-    uint32_t *keys;
-    uint32_t *vals;
-    uint32_t *hist;                // [kSortBins][eblk] low-digit counts of each emission block
-    uint32_t mask0;                // low digit of the instance sort's first pass
-    uint32_t *ranges;              // [2 * total_tiles], cleared here
-    uint8_t *slot_flags;           // [cap][kSplitBwd], cleared here for positions < M
-    unsigned long long cap;
-    int vn, nblk, eblk, total_tiles;
-    int sort_items;                // instance positions per emission (and sort) block
-    int vbits;                     // > 0: emit packed (tile << vbits | value) into keys only
-};
-
-// Exclusive offsets of the splats' instance runs in index order (the
-// emission positions, which are also the backward's gradient slots), the
-// list of the splats with instances (vis, with their offsets offv), the work
-// windows and the emission blocks.  Each block first sums the block sums
-// before it (and all of them, for M and the overflow flag; block 0 writes
-// the counters).  Splat k's entry sits at position h = k + offsets[k] of the
-// sequence (splat, its instances, next splat, ...), the next at h + 1 + cnt;
-// window b starts at the first splat whose entry is at or after b * kWindow.
-// Emission block p covers instance positions [p, p + 1) * items (items =
-// the sort's block size) and starts at the splat of vis whose run holds
-// position p * items; entry ceil(M / items) is the last of vis.  The
-// emission works on vis, not on all splats: the positions of one block then
-// belong to at most items + 1 splats, however many culled splats lie
-// between them.
-__global__ __launch_bounds__(kPreprocessBlock) void k_offsets(DupArgs a) {
-    __shared__ unsigned long long scratch[kPreprocessBlock / kWave];
-    const int t = threadIdx.x;
-    unsigned long long before = 0, all = 0, vbefore = 0;
-    for (int j = t; j < a.nblk; j += kPreprocessBlock) {
-        const unsigned long long x = a.blocksum[j];
-        all += x;
-        if (j < (int)blockIdx.x) {
-            before += x;
-            vbefore += a.blockvis[j];
-        }
-    }
-    before = block_sum<unsigned long long, kPreprocessBlock>(before, scratch);
-    all = block_sum<unsigned long long, kPreprocessBlock>(all, scratch);
-    vbefore = block_sum<unsigned long long, kPreprocessBlock>(vbefore, scratch);
-    const bool ovf = all > a.cap;
-    if (blockIdx.x == 0 && t == 0) {
-        a.counters[kCntMLo] = (uint32_t)(all & 0xffffffffull);
-        a.counters[kCntMHi] = (uint32_t)(all >> 32);
-        a.counters[kCntOverflow] = ovf ? 1u : 0u;
-        a.counters[kCntMEff] = ovf ? 0u : (uint32_t)all;
-        if (ovf) a.counters[kCntSticky] = 1u;
-        if (a.vn == 0) a.counters[kCntWin] = 0u;
-    }
-    const int k0 = blockIdx.x * kScanItems + kScanPerThread * t;
-    uint32_t cnt[kScanPerThread];
-    unsigned long long local = 0, vlocal = 0;
-#pragma unroll
-    for (int j = 0; j < kScanPerThread; j++) {
-        cnt[j] = k0 + j < a.vn ? a.tiles[k0 + j] : 0u;
-        local += cnt[j];
-        vlocal += cnt[j] > 0 ? 1ull : 0ull;
-    }
-    unsigned long long total;
-    unsigned long long excl =
-        block_exclusive_scan<unsigned long long, kPreprocessBlock>(local, scratch, &total) + before;
-    unsigned long long vexcl =
-        block_exclusive_scan<unsigned long long, kPreprocessBlock>(vlocal, scratch, &total) + vbefore;
-    if (ovf) return;
-#pragma unroll
-    for (int j = 0; j < kScanPerThread; j++) {
-        const int k = k0 + j;
-        if (k >= a.vn) break;
-        a.offsets[k] = (uint32_t)excl;
-        const unsigned long long h = (unsigned long long)k + excl, h1 = h + 1 + cnt[j];
-        const unsigned long long e1 = excl + cnt[j];
-        if (k == 0) a.wstart[0] = make_uint2(0u, 0u);
-        for (unsigned long long b = h / kWindow + 1; b * kWindow <= h1; b++)
-            a.wstart[b] = make_uint2((uint32_t)k + 1, (uint32_t)e1);
-        if (cnt[j] > 0) {
-            a.vis[vexcl] = (uint32_t)k;
-            a.offv[vexcl] = (uint32_t)excl;
-            const unsigned long long items = (unsigned long long)a.sort_items;
-            for (unsigned long long p = (excl + items - 1) / items; p * items < e1; p++)
-                a.pstart[p] = (uint32_t)vexcl;
-            if (e1 == all) {
-                a.pstart[(all + items - 1) / items] = (uint32_t)vexcl;
-                a.offv[vexcl + 1] = (uint32_t)all;
-            }
-            vexcl++;
-        }
-        if (k == a.vn - 1) {
-            const unsigned long long nwin = (h1 + kWindow - 1) / kWindow;
-            if (nwin * kWindow > h1) a.wstart[nwin] = make_uint2((uint32_t)a.vn, (uint32_t)e1);
-            a.offsets[a.vn] = (uint32_t)e1;
-            a.counters[kCntWin] = (uint32_t)nwin;
-        }
-        excl = e1;
-    }
-}
-
-#ifndef GSP_EMIT_THREADS
-#define GSP_EMIT_THREADS 256
-#endif
-constexpr int kEmitThreads = GSP_EMIT_THREADS;
-static_assert(kEmitThreads >= kSortBins && kEmitThreads <= 1024 && kEmitThreads % kWave == 0,
-              "emission block size");
-
-// Emits one (tile, view * n + i) pair per tile of each splat's rect, rows
-// outer and columns inner, at the splat's offset; a stable sort of these
-// pairs by tile then yields every tile's list in index order, which the
-// per-tile depth sort turns into (depth, index) order.
-// Block p writes instance positions [p, p + 1) * ITEMS, which are the
-// keys of block p of the first pass of that sort, so it also writes their
-// low-digit histogram (zeros past M); each thread finds the splat owning a
-// position by binary search over the block's offsets in LDS.  The blocks
-// also clear the tile ranges and the backward's slot flags of their
-// positions, which the later stages of this forward and of its backward
-// fill in.
-template <int ITEMS>
-__global__ __launch_bounds__(kEmitThreads) void k_emit(DupArgs a, ViewsK views, int n) {
-    static_assert(kEmitThreads % kSortBins == 0, "whole histograms per block");
-    constexpr int kMaxSplats = ITEMS + 1;
-    __shared__ uint32_t s_off[kMaxSplats + 1];
-    __shared__ uint32_t s_idx[kMaxSplats];
-    __shared__ uint2 s_rect[kMaxSplats];
-    __shared__ uint32_t s_hist[kSortBins];
-    const int b = blockIdx.x, t = threadIdx.x;
-    for (int i = b * kEmitThreads + t; i < 2 * a.total_tiles; i += gridDim.x * kEmitThreads)
-        a.ranges[i] = 0u;
-    if (t < kSortBins) s_hist[t] = 0u;
-    // pstart has eblk + 1 entries; they are read before M is known (those of
-    // blocks past M are stale and unused)
-    const uint32_t kb = a.pstart[b], kn = a.pstart[b + 1];
-    const uint32_t M = a.counters[kCntMEff];
-    const uint32_t p0 = (uint32_t)b * ITEMS;
-    if (p0 < M) {
-        const uint32_t p1 = min(p0 + (uint32_t)ITEMS, M);
-        const int nk = min((int)(kn + 1 - kb), kMaxSplats);
-        for (int j = t; j < nk; j += kEmitThreads) {
-            const uint32_t idx = a.vis[kb + j];
-            s_off[j] = a.offv[kb + j];
-            s_idx[j] = idx;
-            s_rect[j] = a.rect[idx];
-        }
-        if (t == 0) s_off[nk] = a.offv[kb + nk];
-        __syncthreads();
-        // Each thread emits kPer consecutive positions: a binary search for
-        // the first, then a walk along the splats' tiles (rows outer,
-        // columns inner), with no division per position.
-        constexpr int kPer = ITEMS / kEmitThreads;
-        static_assert(ITEMS % kEmitThreads == 0, "whole runs of positions per thread");
-        const uint32_t e0 = p0 + (uint32_t)t * kPer;
-        if (e0 < p1) {
-            // largest j with s_off[j] <= e0; s_off[0] <= p0 <= e0 < p1 <= s_off[nk]
-            int lo = 0, hi = nk;
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (s_off[mid] <= e0) lo = mid; else hi = mid;
-            }
-            uint32_t next = 0, idx = 0, w = 1, x0 = 0, y0 = 0, tbase = 0, gw = 0, tx = 0, ty = 0;
-            // the splat at entry lo, and the tile of position e in it
-            auto enter = [&](uint32_t e) {
-                next = s_off[lo + 1];
-                const uint2 r = s_rect[lo];
-                x0 = r.x & 0xffff;
-                y0 = r.x >> 16;
-                w = (r.y & 0xffff) - x0;
-                idx = s_idx[lo];
-                const ViewK &vw = views.v[idx / (uint32_t)n];
-                tbase = (uint32_t)vw.tile_base;
-                gw = (uint32_t)vw.gw;
-                const uint32_t local = e - s_off[lo];
-                ty = local / w;
-                tx = local - ty * w;
-            };
-            enter(e0);
-            const int cnt = (int)min((uint32_t)kPer, p1 - e0);
-            uint32_t kk[kPer], vv[kPer];
-#pragma unroll
-            for (int q = 0; q < kPer; q++) {
-                if (q < cnt) {
-                    const uint32_t e = e0 + (uint32_t)q;
-                    if (e >= next) {   // a later splat: the last one whose offset is <= e
-                        do lo++;
-                        while (s_off[lo + 1] <= e);
-                        enter(e);
-                    }
-                    const uint32_t key = tbase + (y0 + ty) * gw + x0 + tx;
-                    kk[q] = a.vbits > 0 ? (key << a.vbits) | idx : key;
-                    vv[q] = idx;
-                    atomicAdd(&s_hist[key & a.mask0], 1u);
-                    if (++tx == w) {
-                        tx = 0;
-                        ty++;
-                    }
-                }
-            }
-            // e0 is a multiple of kPer and the regions are 256-byte aligned,
-            // so a full run is stored as 16-byte vectors
-            static_assert(kPer % 4 == 0, "vector stores of a run");
-            if (cnt == kPer) {
-#pragma unroll
-                for (int q = 0; q < kPer; q += 4)
-                    *reinterpret_cast<uint4 *>(a.keys + e0 + q) = make_uint4(kk[q], kk[q + 1], kk[q + 2], kk[q + 3]);
-                if (a.vbits == 0) {
-#pragma unroll
-                    for (int q = 0; q < kPer; q += 4)
-                        *reinterpret_cast<uint4 *>(a.vals + e0 + q) = make_uint4(vv[q], vv[q + 1], vv[q + 2], vv[q + 3]);
-                }
-#pragma unroll
-                for (int q = 0; q < kSplitBwd * kPer / 4; q++)
-                    reinterpret_cast<uint32_t *>(a.slot_flags + (size_t)kSplitBwd * e0)[q] = 0u;
-            } else {
-                for (int q = 0; q < cnt; q++) {
-                    a.keys[e0 + q] = kk[q];
-                    if (a.vbits == 0) a.vals[e0 + q] = vv[q];
-                    for (int k = 0; k < kSplitBwd; k++) a.slot_flags[(size_t)kSplitBwd * (e0 + q) + k] = 0;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if ((uint32_t)t <= a.mask0) a.hist[(size_t)t * a.eblk + b] = s_hist[t];   // rows of used digits
-}
-
 hipError_t launch_preprocess(const GaussiansK &g, const ViewsK &views, const float *poses,
                              const Layout &L, char *ws, hipStream_t s) {
     if (g.n == 0) return hipSuccess;
@@ -450,48 +193,6 @@ hipError_t launch_preprocess(const GaussiansK &g, const ViewsK &views, const flo
         case 2: hipLaunchKernelGGL(k_preprocess<2>, grid, block, 0, s, a, views); break;
         default: hipLaunchKernelGGL(k_preprocess<3>, grid, block, 0, s, a, views); break;
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_offsets_and_duplicate(const ViewsK &views, const Layout &L, char *ws,
-                                        hipStream_t s) {
-    DupArgs a;
-    a.rect = region<uint2>(ws, L.rect);
-    a.tiles = region<uint32_t>(ws, L.tiles);
-    a.offsets = region<uint32_t>(ws, L.offsets);
-    a.vis = region<uint32_t>(ws, L.vis);
-    a.offv = region<uint32_t>(ws, L.offv);
-    a.blockvis = region<uint32_t>(ws, L.blockvis);
-    a.wstart = region<uint2>(ws, L.wstart);
-    a.pstart = region<uint32_t>(ws, L.pstart);
-    a.blocksum = region<unsigned long long>(ws, L.blocksum);
-    a.counters = region<uint32_t>(ws, L.counters);
-    a.keys = region<uint32_t>(ws, L.keys0);
-    a.vals = region<uint32_t>(ws, L.vals0);
-    a.hist = region<uint32_t>(ws, L.hist);
-    a.mask0 = (1u << digit_bits(L.tile_bits)) - 1u;
-    a.ranges = region<uint32_t>(ws, L.ranges);
-    a.slot_flags = region<uint8_t>(ws, L.slot_flags);
-    a.cap = (unsigned long long)L.cap;
-    a.vn = (int)L.vn;
-    a.nblk = L.nblk_scan;
-    a.eblk = L.nblk_emit;
-    a.total_tiles = L.total_tiles;
-    a.sort_items = L.sort_items;
-    a.vbits = L.sort_vbits;
-    if (a.vn > 0) {
-        hipLaunchKernelGGL(k_blocksums, dim3(L.nblk_scan), dim3(kPreprocessBlock), 0, s, a.tiles,
-                           region<unsigned long long>(ws, L.blocksum),
-                           region<uint32_t>(ws, L.blockvis), a.vn);
-    }
-    hipLaunchKernelGGL(k_offsets, dim3(L.nblk_scan > 0 ? L.nblk_scan : 1), dim3(kPreprocessBlock),
-                       0, s, a);
-    if (L.sort_items == kSortThreads * kSortRoundsLarge)
-        hipLaunchKernelGGL(k_emit<kSortThreads * kSortRoundsLarge>, dim3(L.nblk_emit),
-                           dim3(kEmitThreads), 0, s, a, views, (int)L.n);
-    else
-        hipLaunchKernelGGL(k_emit<kSortThreads * kSortRoundsSmall>, dim3(L.nblk_emit),
-                           dim3(kEmitThreads), 0, s, a, views, (int)L.n);
     return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-// raster_fwd.hip -- per-tile instance ranges and the forward rasterizer.
+// raster_fwd.hip -- the forward rasterizer.
 //
 // Sec. III-A, Eq. (3)-(4): every pixel composites, front to back in
 // (depth, Gaussian index) order, the splats whose tile rectangle contains its
@@ -25,146 +25,6 @@ namespace gsp {
 
 constexpr int kSplit = kSplitFwd;
 constexpr int kPixPerLane = 4 / kSplit;   // pixels per lane, one column
-
-__global__ __launch_bounds__(256) void k_ranges(const uint32_t *keys, const uint32_t *counters,
-                                                uint2 *ranges) {
-    const uint32_t M = counters[kCntMEff];
-    const size_t k = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= M) return;
-    const uint32_t tile = keys[k];
-    if (k == 0 || keys[k - 1] != tile) ranges[tile].x = (uint32_t)k;
-    if (k == M - 1 || keys[k + 1] != tile) ranges[tile].y = (uint32_t)(k + 1);
-}
-
-// Launch order of the tiles: longest lists first (in buckets of 4 lengths up
-// to 1024, which spread the same-address LDS atomics of the counting sort four
-// times thinner than buckets of 16, and of 64 lengths above), so that the
-// longest tiles do not start last and leave a tail.  No bucket holds lengths
-// on both sides of 1024 or of 2048: the lists longer than that are a prefix.
-// The same kernel lists the backward work items (tile, chunk), also longest
-// first by chunk length; their count goes to counters[kCntItems].  The
-// orders only decide which workgroup takes which tile or chunk; every
-// result is the same in any order.
-constexpr int kOrderBuckets = 512;
-constexpr int kOrderThreads = 1024;
-constexpr int kOrderRounds = 8;   // tiles per thread whose ranges are loaded together
-
-__host__ __device__ constexpr int order_bucket(int len) {
-    const int up = len <= 1024 ? (len + 3) >> 2 : 257 + ((len - 1025) >> 6);
-    return kOrderBuckets - 1 - (up < kOrderBuckets - 1 ? up : kOrderBuckets - 1);
-}
-
-__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const uint2 *ranges, int total_tiles,
-                                                             uint32_t *order, uint32_t *items,
-                                                             uint32_t *counters) {
-    // Full chunks all fall into one bucket; a wave adds its tiles' full
-    // chunks there with one atomic (same-address LDS atomics serialise).
-    constexpr int kFull = order_bucket(kChunk);
-    __shared__ uint32_t cnt[2][kOrderBuckets], base[2][kOrderBuckets];
-    const int t = threadIdx.x, lane = t & (kWave - 1);
-    if (t < kOrderBuckets) cnt[0][t] = cnt[1][t] = 0;
-    __syncthreads();
-    constexpr int kStep = kOrderThreads * kOrderRounds;
-    // lengths of this thread's tiles in the group starting at k0 (-1 past the last tile)
-    auto load = [&](int k0, int (&len)[kOrderRounds]) {
-#pragma unroll
-        for (int r = 0; r < kOrderRounds; r++) {
-            const int k = k0 + r * kOrderThreads + t;
-            const uint2 rg = k < total_tiles ? ranges[k] : make_uint2(1u, 0u);
-            len[r] = (int)(rg.y - rg.x);
-        }
-    };
-    const int wave0 = t - lane;   // first thread of this wave
-    // the first group's lengths serve both passes (a call with at most kStep
-    // tiles loads its ranges once)
-    int len_first[kOrderRounds];
-    load(0, len_first);
-    for (int k0 = 0; k0 < total_tiles; k0 += kStep) {
-        int len[kOrderRounds];
-        if (k0 == 0) {
-#pragma unroll
-            for (int r = 0; r < kOrderRounds; r++) len[r] = len_first[r];
-        } else {
-            load(k0, len);
-        }
-        uint32_t full = 0;   // this thread's full chunks in the round
-#pragma unroll
-        for (int r = 0; r < kOrderRounds; r++) {
-            if (k0 + r * kOrderThreads + wave0 >= total_tiles) break;   // whole wave past the end
-            if (len[r] < 0) continue;
-            const int nch = chunks_of(len[r]);
-            atomicAdd(&cnt[0][order_bucket(len[r])], 1u);
-            atomicAdd(&cnt[1][order_bucket(len[r] - (nch - 1) * kChunk)], 1u);
-            full += (uint32_t)(nch - 1);
-        }
-        const uint32_t wfull = wave_sum(full);
-        if (lane == 0 && wfull > 0) atomicAdd(&cnt[1][kFull], wfull);
-    }
-    __syncthreads();
-    // exclusive scans of the two bucket histograms: one wave, eight buckets per lane
-    constexpr int kPer = kOrderBuckets / kWave;   // buckets per lane
-    if (t < kWave) {
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            uint32_t c[kPer], s = 0;
-#pragma unroll
-            for (int j = 0; j < kPer; j++) {
-                c[j] = cnt[h][kPer * lane + j];
-                s += c[j];
-            }
-            const uint32_t inc = wave_inclusive_scan(s);
-            uint32_t e = inc - s;
-#pragma unroll
-            for (int j = 0; j < kPer; j++) {
-                base[h][kPer * lane + j] = e;
-                e += c[j];
-            }
-            if (h == 1 && lane == kWave - 1) counters[kCntItems] = inc;
-        }
-        // lists in front of the bucket that ends at 1024 (2048)
-        if (lane == 0) {
-            counters[kCntOver1024] = base[0][order_bucket(1024)];
-            counters[kCntOver2048] = base[0][order_bucket(2048)];
-        }
-    }
-    __syncthreads();
-    for (int k0 = 0; k0 < total_tiles; k0 += kStep) {
-        int len[kOrderRounds];
-        if (k0 == 0) {
-#pragma unroll
-            for (int r = 0; r < kOrderRounds; r++) len[r] = len_first[r];
-        } else {
-            load(k0, len);
-        }
-        uint32_t full = 0;
-#pragma unroll
-        for (int r = 0; r < kOrderRounds; r++) full += len[r] >= 0 ? (uint32_t)(chunks_of(len[r]) - 1) : 0u;
-        const uint32_t wfull = wave_sum(full);
-        uint32_t wb = 0;
-        if (lane == 0 && wfull > 0) wb = atomicAdd(&base[1][kFull], wfull);
-        wb = __shfl(wb, 0, kWave);   // the wave's first full-chunk item
-        const unsigned long long below = (1ull << lane) - 1ull;
-#pragma unroll
-        for (int r = 0; r < kOrderRounds; r++) {
-            if (k0 + r * kOrderThreads + wave0 >= total_tiles) break;
-            const uint32_t k = (uint32_t)(k0 + r * kOrderThreads + t);
-            const int nch = len[r] >= 0 ? chunks_of(len[r]) : 1;
-            if (len[r] >= 0) {
-                order[atomicAdd(&base[0][order_bucket(len[r])], 1u)] = k;
-                items[atomicAdd(&base[1][order_bucket(len[r] - (nch - 1) * kChunk)], 1u)] =
-                    k * kMaxChunks + (uint32_t)(nch - 1);
-            }
-            // full chunks j of the wave's tiles, compacted by ballot so that
-            // each store covers consecutive items
-            for (int j = 0; j < kMaxChunks - 1; j++) {
-                const unsigned long long m = __ballot(j < nch - 1);
-                if (m == 0ull) break;
-                if (j < nch - 1) items[wb + (uint32_t)__popcll(m & below)] = k * kMaxChunks + (uint32_t)j;
-                wb += (uint32_t)__popcll(m);
-            }
-        }
-    }
-}
 
 struct FwdArgs {
     const uint32_t *order;
@@ -423,19 +283,6 @@ __global__ __launch_bounds__(256) void k_l1_fused_final(ViewsK views, const doub
     for (int64_t k = threadIdx.x; k < n; k += 256) s += l1part[b0 + k];
     s = block_sum<double, 256>(s, red);
     if (threadIdx.x == 0) loss[blockIdx.x] = (float)(s / (double)(3 * (int64_t)vw.roi_w * vw.roi_h));
-}
-
-hipError_t launch_ranges(const Layout &L, char *ws, const uint32_t *keys, hipStream_t s) {
-    uint2 *ranges = region<uint2>(ws, L.ranges);   // cleared by the emission
-    const int64_t blocks = (L.cap + 255) / 256;
-    hipLaunchKernelGGL(k_ranges, dim3((unsigned)blocks), dim3(256), 0, s, keys,
-                       region<uint32_t>(ws, L.counters), ranges);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || L.total_tiles == 0) return e;
-    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(kOrderThreads), 0, s, ranges, L.total_tiles,
-                       region<uint32_t>(ws, L.tile_order), region<uint32_t>(ws, L.items),
-                       region<uint32_t>(ws, L.counters));
-    return hipGetLastError();
 }
 
 hipError_t launch_raster_fwd(const ViewsK &views, const Layout &L, char *ws, const uint32_t *vals,

@@ -178,6 +178,37 @@ def test_depth_ties_and_long_runs_bit_exact(cap):
     assert_sorted_match(keys, vals, rkeys, rvals, fragile)
 
 
+# the binning at its edges: one splat, one chunk of splats and its remainders, as
+# many chunks as a view has; windows of tile rows (more than 4096 tiles) and of
+# pieces of a row (more than 4096 in a row); splats over whole windows, whose
+# chunks exceed what a workgroup stages; views of several sizes
+@pytest.mark.parametrize("n,sizes,scale", [
+    (1, [(40, 30)], 0.3), (255, [(64, 48)], 0.2), (257, [(64, 48)], 0.2), (70001, [(200, 130)], 0.02),
+    (3000, [(1040, 1024)], 0.1), (700, [(65600, 24)], 0.3), (400, [(1040, 1030)], 30.0),
+    (2500, [(130, 70), (33, 17), (1040, 1024)], 0.05)])
+def test_binning_bit_exact(n, sizes, scale):
+    cams = [f32_camera(S.Camera(w, h, 0.9 * w, 0.9 * w, 0.5 * w, 0.5 * h)) for w, h in sizes]
+    sc = S.random_scene(n, n, 0, max(cams, key=lambda c: c.height / c.width), depth=(0.1, 6.0),
+                        log_scale=(np.log(0.1 * scale), np.log(scale)))
+    poses = [S.random_pose_near_identity(n + k, 3.0, 0.1) for k in range(len(cams))]
+    run = _gpu(sc, cams, poses)
+    refs = [oracle.preprocess(sc, c, p) for c, p in zip(cams, poses)]
+    grids = [oracle.tiles_of(c) for c in cams]
+    rkeys, rvals = oracle.bin_sort(refs, grids)
+    M, ovf = run["rast"].instances()
+    assert not ovf
+    keys, vals = _sorted_instances(run["rast"], run["g"], cams, M)
+    fragile = np.concatenate([np.nonzero(r["fragile"])[0] + k * n for k, r in enumerate(refs)])
+    print(f"{n}: {M} instances, {len(fragile)} fragile")
+    assert_sorted_match(keys, vals, rkeys, rvals, fragile.astype(np.uint32))
+    insp = lambda name: run["rast"].inspect(run["g"], cams, name, torch.int32).cpu().numpy().view(np.uint32)
+    tiles = insp("tiles").astype(np.int64)
+    assert np.array_equal(insp("offsets"), (np.cumsum(tiles) - tiles).astype(np.uint32))
+    if len(fragile) == 0:
+        assert np.array_equal(insp("ranges").reshape(-1, 2),
+                              oracle.tile_ranges(rkeys, sum(w * h for w, h in grids)))
+
+
 # one tile: list lengths at the edges of the per-tile sort's kernels (1024 or
 # 2048 entries by the capacity, 8192, beyond), with depths spread evenly,
 # crowded in two thin layers, crowded in layers of a few values (equal depths),
