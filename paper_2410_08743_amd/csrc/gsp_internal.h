@@ -60,21 +60,14 @@ constexpr int kPoseRowsPerBlock = kPoseReduceBlock / 64;
 #endif
 constexpr int kWindow = GSP_WINDOW;
 constexpr int kWindowThreads = 256;
-// Workgroups per 16 x 16 tile in the forward and per work item in the
-// backward rasterizer (each takes a strip of 16 / split rows); every
-// instance has one 9-float gradient slot per backward part.  The backward
+// Wavefronts per 16 x 16 tile in the forward rasterizer (one per 8 x 8
+// quadrant), and 9-float gradient slots per instance: one, since the backward
 // takes whole tiles (one wave, four pixels per lane): its chunked work
 // items already fill the chip, and one wave per entry reduces the nine sums
-// once instead of once per strip and halves the slots (measured: split 2
-// 0.544 ms, split 1 0.503 ms per single-view step).
-#ifndef GSP_SPLIT_FWD
-#define GSP_SPLIT_FWD 4
-#endif
-#ifndef GSP_SPLIT_BWD
-#define GSP_SPLIT_BWD 1
-#endif
-constexpr int kSplitFwd = GSP_SPLIT_FWD;
-constexpr int kSplitBwd = GSP_SPLIT_BWD;
+// once instead of once per strip and halves the slots (measured: two strips
+// 0.544 ms, whole tiles 0.503 ms per single-view step).
+constexpr int kSplitFwd = 4;
+constexpr int kSplitBwd = 1;
 // Backward work items: a tile's list longer than kChunk entries is cut at
 // multiples of kChunk into at most kMaxChunks chunks (the last one takes the
 // rest), each walked by its own workgroups, so that no work item is long

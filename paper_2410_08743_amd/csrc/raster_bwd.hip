@@ -15,20 +15,19 @@
 // (T, accumulated colour) at every cut.  The work items are (tile, chunk)
 // pairs, so that no workgroup walks more than a chunk of a list that is cut
 // (the longest lists would otherwise run alone at the end of the launch);
-// kSplit wavefronts per item (one by default, the whole tile), each a strip
-// of rows, walk the chunk back to front from the largest contributor count
-// of their pixels inside it,
-// recovering T_i = T_{i+1} / (1 - alpha_i) with the forward's exact
-// evaluation, and skip (per lane-parallel bound, as in the forward) the
-// entries that reach 1/255 nowhere in their rows.  Each lane
-// sums its pixels in registers; the nine sums are reduced over the 64 lanes
-// in two steps: v_permlane32_swap and v_permlane16_swap leave each as 16
-// partial sums in one row of lanes (16 VALU operations for the nine), which
-// wait in LDS; every kPend entries, 63 lanes each add up the 16 partials of
-// one (entry, component) in a fixed order and store it into the strip's part
-// of the instance's own slot (its position in emission order), flagging it
-// written.  No atomics: the per-splat sum over its slots happens later in a
-// fixed order, so gradients are bit-reproducible.
+// one wavefront per item walks the chunk back to front from the largest
+// contributor count of its pixels inside it, recovering
+// T_i = T_{i+1} / (1 - alpha_i) with the forward's exact evaluation, and
+// skips (per lane-parallel bound, as in the forward) the entries that reach
+// 1/255 nowhere in the tile.  Each lane sums its pixels in registers; the
+// nine sums are reduced over the 64 lanes in two steps: v_permlane32_swap
+// and v_permlane16_swap leave each as 16 partial sums in one row of lanes (16
+// VALU operations for the nine), which wait in LDS; every kPend entries, 63
+// lanes each add up the 16 partials of one (entry, component) in a fixed
+// order and store it into the instance's own slot (its position among the
+// instances splat by splat), flagging it written.  No atomics: the per-splat
+// sum over its slots happens later in a fixed order, so gradients are
+// bit-reproducible.
 #include <cstring>
 #include <type_traits>
 
@@ -37,8 +36,7 @@
 
 namespace gsp {
 
-constexpr int kSplit = kSplitBwd;
-constexpr int kPixPerLane = 4 / kSplit;   // pixels per lane, one column
+constexpr int kPixPerLane = 4;   // pixels per lane, one column
 
 struct BwdArgs {
     const uint32_t *items;   // work items tile * kMaxChunks + chunk, longest first
@@ -54,8 +52,8 @@ struct BwdArgs {
     const uint32_t *offsets;
     const float *tfinal;
     const uint32_t *ncontrib;
-    float *slots;          // [cap][kSplit][9]
-    uint8_t *slot_flags;   // [cap][kSplit]: 1 where this kernel wrote the slot
+    float *slots;          // [cap][9]
+    uint8_t *slot_flags;   // [cap]: 1 where this kernel wrote the slot
     // stored-list variant only
     const uint32_t *order;     // tiles, longest list first
     const uint32_t *loff;      // [total_pix + 1] first pair of each pixel
@@ -81,7 +79,7 @@ static_assert(GSP_BWD_PEND >= 1 && 9 * GSP_BWD_PEND <= 64, "one flush lane per (
 #define GSP_BWD_PREFETCH 0
 #endif
 
-// Slot of the instance of splat `id` in tile (tx, ty): its emission position.
+// Slot of the instance of splat `id` in tile (tx, ty): its position splat by splat.
 __device__ __forceinline__ uint32_t slot_of(const BwdArgs &a, uint32_t id, int tx, int ty) {
     const uint2 r = a.rect[id];
     const int x0 = r.x & 0xffff, y0 = r.x >> 16, x1 = r.y & 0xffff;
@@ -123,8 +121,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     __shared__ float sP[kPend * kEntryStride];
     __shared__ uint32_t sPs[kPend];
     __shared__ float sPi[kPend];
-    int rank, part;
-    part_of_block<kSplit>(blockIdx.x, rank, part);
+    const int rank = blockIdx.x;
     uint32_t item;
     if (STORED) {
         if (rank >= a.total_tiles || a.lhdr[kListOverflow]) return;
@@ -142,9 +139,6 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     const int lx = lane & 15, ly = lane >> 4;
     const int rx = kTile * tx + lx;
     const int P = vw.roi_w * vw.roi_h;
-    const int row0 = part * (kTile / kSplit);   // first tile row of this part
-    float *const pslots = a.slots + 9 * part;   // this part's slot of each instance
-    uint8_t *const pflags = a.slot_flags + part;
 
     // In a flush, lane k < 9 kPend sums component pc of pending entry pe,
     // whose row partials start at poff within the entry's area; pscale is
@@ -169,8 +163,8 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             const uint32_t slot = sPs[pe];
             if (slot != kNoSlot) {
                 const float f = pc == 5 ? sPi[pe] : pscale;
-                pslots[9 * kSplit * (size_t)slot + pc] = OPA || pc != 5 ? sum * f : 0.f;
-                if (pc == 0) pflags[kSplit * (size_t)slot] = 1;
+                a.slots[9 * (size_t)slot + pc] = OPA || pc != 5 ? sum * f : 0.f;
+                if (pc == 0) a.slot_flags[slot] = 1;
             }
         }
         __syncthreads();   // before the next entries overwrite the area
@@ -199,7 +193,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     int maxlast = 0;
 #pragma unroll
     for (int q = 0; q < kPixPerLane; q++) {
-        const int ryl = row0 + ly + 4 * q;
+        const int ryl = ly + 4 * q;
         const int ry = kTile * ty + ryl;
         const bool in = rx < vw.roi_w && ry < vw.roi_h;
         const size_t pix = (size_t)ry * vw.roi_w + rx;
@@ -271,11 +265,11 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     for (int hi = maxlast; hi > clo; hi -= kBatch) {
         const int lo = hi - kBatch;
         // Stage, in list order, the entries that can reach 1/255 somewhere in
-        // this part's rows; a dropped entry blends nowhere there, and its slot
+        // the tile; a dropped entry blends nowhere there, and its slot
         // stays unwritten (flag 0, read as zero).
         const float u = rel_coord(g0.x, g0.z, px0), v = rel_coord(g0.y, g0.w, py0);
         const uint32_t mask =
-            gslot != kNoSlot ? band_mask<kSplit>(u, v, g1.x, g1.y, g1.z, g1.w, row0) : 0u;
+            gslot != kNoSlot ? band_mask(u, v, g1.x, g1.y, g1.z, g1.w) : 0u;
         const unsigned long long kept = __ballot(mask != 0u);
         const int nk = __popcll(kept);
         // an opacity below exp2(kLoNoClamp) keeps o exp(power) below the
@@ -491,16 +485,16 @@ hipError_t launch_raster_bwd(const ViewsK &views, const Layout &L, char *ws, con
     a.ncontrib = region<uint32_t>(ws, L.ncontrib);
     a.slots = region<float>(ws, L.slots);
     a.slot_flags = region<uint8_t>(ws, L.slot_flags);
-    // Slots that no entry writes keep the flag 0 that the forward's emission
+    // Slots that no entry writes keep the flag 0 that the forward
     // stored and count as zero.  The set of written slots depends only on the
     // forward's state, so repeated backwards of one forward agree on it.
-    // one workgroup per part of each possible work item; those past the
+    // one workgroup per possible work item; those past the
     // item count of this call exit at once
     if (want_opacity)
-        hipLaunchKernelGGL((k_raster_bwd<false, true>), dim3(raster_blocks<kSplit>((int)L.max_items)),
+        hipLaunchKernelGGL((k_raster_bwd<false, true>), dim3((unsigned)L.max_items),
                            dim3(kRasterThreads), 0, s, a, views);
     else
-        hipLaunchKernelGGL((k_raster_bwd<false, false>), dim3(raster_blocks<kSplit>((int)L.max_items)),
+        hipLaunchKernelGGL((k_raster_bwd<false, false>), dim3((unsigned)L.max_items),
                            dim3(kRasterThreads), 0, s, a, views);
     return hipGetLastError();
 }
@@ -527,8 +521,8 @@ hipError_t launch_raster_bwd_stored(const ViewsK &views, const Layout &L, char *
     a.pairs = region<PairRec>(lw, Q.pairs);
     a.lhdr = region<uint32_t>(lw, Q.hdr);
     a.total_tiles = L.total_tiles;
-    // one workgroup per part of each tile, in the forward's launch order
-    hipLaunchKernelGGL((k_raster_bwd<true, true>), dim3(raster_blocks<kSplit>(L.total_tiles)),
+    // one workgroup per tile, in the forward's launch order
+    hipLaunchKernelGGL((k_raster_bwd<true, true>), dim3(L.total_tiles),
                        dim3(kRasterThreads), 0, s, a, views);
     return hipGetLastError();
 }

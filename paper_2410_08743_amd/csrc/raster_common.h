@@ -20,13 +20,12 @@
 
 namespace gsp {
 
-// SPLIT wavefronts (64 lanes each) rasterize one 16 x 16 tile, each a
-// horizontal strip of 16 / SPLIT rows; in part h, lane l owns pixels
-// (l % 16, 16 h / SPLIT + l / 16 + 4 q) for q < 4 / SPLIT, so the q-th
-// pixels of all lanes form the 16 x 4 band 4 h / SPLIT + q of the tile.
-// The parts of a tile are independent workgroups: more of them keep the
-// SIMDs busy (a 1008 x 756 view has only 3024 tiles) and each walks, culls
-// and stops for its own rows.
+// The forward gives each 8 x 8 quadrant of a 16 x 16 tile to a wavefront, one
+// pixel per lane; the backward the whole tile, lane l owning pixels
+// (l % 16, l / 16 + 4 q) for q < 4, so that its q-th pixels form the 16 x 4
+// band q of the tile.  The forward's quadrants keep the SIMDs busy (a 1008 x
+// 756 view has only 3024 tiles), and each walks, culls and stops for its own
+// pixels.
 constexpr int kRasterThreads = 64;
 constexpr int kBatch = 64;          // list entries staged in LDS at a time
 static_assert(kChunk % kBatch == 0, "the backward's chunks start at batch boundaries");
@@ -92,36 +91,50 @@ __device__ __forceinline__ float splat_alpha_pre(float p2, float lo) {
     return __builtin_amdgcn_exp2f(p2 + lo);
 }
 
-// Bit q of the result is set when some pixel of rows row0 + 4q .. row0 + 4q + 3
-// of the tile (q < 4 / SPLIT) may reach alpha >= 1/255, i.e. when the rasterizer's own candidate test
-// (p2 >= kLog2AlphaMinLoose - lo) may pass there; a clear bit is a proof that
-// it fails at every pixel of those rows.  Per pixel row, p2 is a concave
-// quadratic in dx whose maximum over the row's dx range [u - 15, u] is taken
-// at the clamped stationary point.  The margin covers the float32 rounding of
-// both this bound and the rasterizer's evaluation: 0.02 plus 1e-5 times the
-// largest magnitude the three terms of p2 take in the row, some forty times
-// the error of either three-operation evaluation.
-template <int SPLIT>
-__device__ __forceinline__ uint32_t band_mask(float u, float v, float A2, float B2, float C2,
-                                              float lo, int row0) {
-    constexpr int kRows = kTile / SPLIT;
-    if (!(A2 < 0.f) || !(C2 < 0.f)) return (1u << (4 / SPLIT)) - 1u;   // not negative definite
-    const float xa = u - (float)(kTile - 1), xb = u;
-    const float dxm = fmaxf(fabsf(xa), fabsf(xb));
-    const float half_inv = -0.5f / A2;
-    const float thr = kLog2AlphaMinLoose - lo;
-    const float adxm2 = fabsf(A2) * dxm * dxm;
+// A splat's quadratic form over rectangles of offsets (dx, dy) from its centre.
+// p2 is homogeneous of degree two, so from a point with p2 <= 0 it only grows
+// towards the centre: over a rectangle it is largest at the centre if that
+// lies inside, and otherwise on the one or two edges that face it, where
+// A, C < 0 make it concave and largest at the edge's clamped stationary point
+// (this holds too where rounding left a long thin form indefinite, since a
+// pixel with p2 > 0 is never blended).
+// reaches() is true when some pixel of the rectangle may reach alpha >= 1/255,
+// i.e. when the rasterizer's own candidate test (p2 >= kLog2AlphaMinLoose - lo)
+// may pass there; false is a proof that it fails at every pixel.  The margin
+// covers the float32 rounding of the conic, of this bound and of the
+// rasterizer's evaluation: 0.02 plus 1e-5 times the largest magnitude the three
+// terms of p2 take in the rectangle, some forty times the error of either
+// three-operation evaluation.  (Bounding every pixel row of a band by itself
+// took 40 operations per 16 x 4 band where this takes 16.)
+struct SplatForm {
+    float A2, B2, C2, thr, kx, ky;   // dx = kx dy (dy = ky dx): stationary in dx (dy)
+    bool any;                        // not concave along the edges: no bound
+    __device__ __forceinline__ SplatForm(float A, float B, float C, float lo) : A2(A), B2(B), C2(C) {
+        any = !(A < 0.f) || !(C < 0.f);
+        thr = kLog2AlphaMinLoose - lo;
+        kx = -0.5f * B * __builtin_amdgcn_rcpf(A);
+        ky = -0.5f * B * __builtin_amdgcn_rcpf(C);
+    }
+    // over dx in [xa, xb], dy in [ya, yb]
+    __device__ __forceinline__ bool reaches(float xa, float xb, float ya, float yb) const {
+        const float x0 = fminf(fmaxf(0.f, xa), xb), y0 = fminf(fmaxf(0.f, ya), yb);
+        const float ys = fminf(fmaxf(ky * x0, ya), yb), xs = fminf(fmaxf(kx * y0, xa), xb);
+        const float fx = fmaf(fmaf(C2, ys, B2 * x0), ys, A2 * x0 * x0);   // on the edge dx = x0
+        const float fy = fmaf(fmaf(A2, xs, B2 * y0), xs, C2 * y0 * y0);   // on the edge dy = y0
+        const float xm = fmaxf(fabsf(xa), fabsf(xb)), ym = fmaxf(fabsf(ya), fabsf(yb));
+        const float mag = fabsf(A2) * xm * xm + fabsf(B2) * xm * ym + fabsf(C2) * ym * ym;
+        return any || fmaxf(fx, fy) + fmaf(1e-5f, mag, 0.02f) >= thr;
+    }
+};
+
+// Bit q of the result is set when some pixel of the 16 x 4 band q of the tile
+// may be reached; u, v: the centre relative to the tile's first pixel.
+__device__ __forceinline__ uint32_t band_mask(float u, float v, float A2, float B2, float C2, float lo) {
+    const SplatForm f(A2, B2, C2, lo);
     uint32_t mask = 0u;
 #pragma unroll
-    for (int r = 0; r < kRows; r++) {
-        const float dy = v - (float)(row0 + r);
-        const float bdy = B2 * dy;
-        const float cdy2 = C2 * dy * dy;
-        const float xs = fminf(fmaxf(bdy * half_inv, xa), xb);
-        const float m = fmaf(fmaf(A2, xs, bdy), xs, cdy2);
-        const float mag = adxm2 + fabsf(bdy) * dxm + fabsf(cdy2);
-        if (m + fmaf(1e-5f, mag, 0.02f) >= thr) mask |= 1u << (r >> 2);
-    }
+    for (int q = 0; q < 4; q++)
+        mask |= f.reaches(u - (float)(kTile - 1), u, v - (float)(4 * q + 3), v - (float)(4 * q)) ? 1u << q : 0u;
     return mask;
 }
 
@@ -132,28 +145,18 @@ __device__ __forceinline__ int kept_rank(unsigned long long kept) {
                                           __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
 }
 
-// Workgroup -> (rank of the tile in launch order, part).  The SPLIT parts
-// of one tile go to workgroups 8 apart, which the dispatcher places on the
-// same XCD (workgroups are dealt round-robin over the 8 XCDs), so the later
-// parts find the tile's splat records in that XCD's L2.
-template <int SPLIT>
-__device__ __forceinline__ void part_of_block(int b, int &rank, int &part) {
-    if (SPLIT == 1) {
-        rank = b;
-        part = 0;
-    } else {
-        const int grp = b / (8 * SPLIT), r = b % (8 * SPLIT);
-        rank = grp * 8 + (r & 7);
-        part = r >> 3;
-    }
+// Forward workgroup -> (rank of the tile in launch order, half).  The two
+// halves of a tile go to workgroups 8 apart, which the dispatcher places
+// on the same XCD (workgroups are dealt round-robin over the 8 XCDs), so the
+// later one finds the tile's splat records in that XCD's L2.
+__device__ __forceinline__ void half_of_block(int b, int &rank, int &half) {
+    rank = (b >> 4) * 8 + (b & 7);
+    half = (b >> 3) & 1;
 }
 
-// Workgroups of a rasterizer launch over `tiles` tiles (a multiple of
-// 8 SPLIT when split; the extra ones exit at once).
-template <int SPLIT>
-inline int raster_blocks(int tiles) {
-    return SPLIT == 1 ? tiles : ((tiles + 7) / 8) * 8 * SPLIT;
-}
+// Workgroups of a forward launch over `tiles` tiles (whole groups of 8; the
+// extra ones exit at once).
+inline int raster_fwd_blocks(int tiles) { return ((tiles + 7) / 8) * 16; }
 
 __device__ __forceinline__ int view_of_tile(const ViewsK &views, int tile) {
     int v = 0;

@@ -6,16 +6,25 @@
 // alpha < 1/255 are skipped; compositing stops before a splat that would
 // take the transmittance below 1e-4; colour = sum c alpha T + T_final bg.
 //
-// MI355X design: kSplit wavefronts per 16 x 16 tile, each a strip of rows
-// with the pixels of a lane in one column so that they share the splat's dx
-// terms.  A wave stages 64 list entries at a time in LDS (list ids read
-// coalesced, splat records gathered one batch ahead), keeping only the
-// entries that can reach 1/255 in its rows (each lane bounds its own entry,
-// then a ballot compacts the batch), and its inner loop runs the kept
-// entries a few at a time, each a broadcast LDS read that feeds the lane's
-// pixel evaluations of two FMAs and one v_exp_f32.  The waves of a tile need
-// no barrier between them, and each leaves as soon as its pixels are
-// saturated.
+// MI355X design: a wavefront per 8 x 8 quadrant of a 16 x 16 tile, one pixel
+// per lane, and a workgroup of two wavefronts per half tile.  A wave stages 64
+// list entries at a time in LDS (list ids read coalesced, splat records
+// gathered one batch ahead), keeping only the entries that can reach 1/255 in
+// its quadrant (each lane bounds its own entry, then a ballot compacts the
+// batch), and its inner loop runs the kept entries a few at a time, each a
+// broadcast LDS read that feeds the lane's pixel evaluation of two FMAs and one
+// v_exp_f32.  The waves walk the list independently and each stops as soon as
+// its pixels are saturated; they meet once, to exchange their results through
+// LDS, so that each writes four rows of 16 pixels.
+//
+// Bound by VALU issue.  A square quadrant meets fewer splats than a 16 x 4
+// strip (539 against 601 kept entries per tile and part at the benchmark view, 507
+// against 552 of them with a hit): 98.5 -> 89.2 us at 640 x 480 with 100k
+// splats, 83 -> 76 us over 500k splats, 36 -> 31 us at 320 x 240, 666 -> 598 us
+// over 16 views of 640 x 480; 426 -> 428 us over 8 views in which the outputs'
+// traffic weighs more.  Without the exchange a wave writes rows of 8 pixels,
+// and those half lines cost more than the square saves once the outputs
+// outgrow the L2 (515 us over the 8 views, 728 us over the 16).
 #include <type_traits>
 
 #include "block_ops.h"
@@ -23,8 +32,15 @@
 
 namespace gsp {
 
-constexpr int kSplit = kSplitFwd;
-constexpr int kPixPerLane = 4 / kSplit;   // pixels per lane, one column
+constexpr int kQuad = kTile / 2;   // edge of a quadrant
+constexpr int kFwdThreads = 2 * kWave;   // the two quadrants of a half tile
+
+// Orders a wavefront's LDS accesses before this point against those after it
+// for the compiler (the hardware executes them in program order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
 struct FwdArgs {
     const uint32_t *order;
@@ -40,61 +56,51 @@ struct FwdArgs {
     float *cfinal;      // [3][total_pix]: final colour, for tiles with cuts
     // L1-fused forward: each view's img holds dL/dimage of the mean absolute
     // error against the target its dl points to (instead of the image), and
-    // with l1part each wave leaves its FP64 sum of |image - target| at
-    // [tile * kSplit + part]
+    // with l1part each wave leaves the FP64 sum of |image - target| over the
+    // 16 x 4 strip it writes at [tile * kSplitFwd + strip]
     double *l1part;
     int total_pix;
     int total_tiles;
     bool l1;
 };
 
-template <int N>
-__device__ __forceinline__ bool any_active(const float (&fy)[N]) {
-    bool a = false;
-#pragma unroll
-    for (int q = 0; q < N; q++) a |= fy[q] != kInactiveRow;
-    return wave_any(a);
-}
-
 // STATS = true is a measurement variant that also counts, per pixel, the
 // evaluated and blended (pixel, splat) pairs of the algorithm -- every list
 // entry up to the pixel's stop counts as evaluated, culled or not; the work
 // counts define the kernel's algorithmic operation count.
 template <bool STATS>
-__global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_raster_fwd(FwdArgs a, ViewsK views) {
-    __shared__ StagedA sA[kBatch];
-    __shared__ StagedB sB[kBatch];
-    __shared__ StagedF sF[kBatch];
-    int rank, part;
-    part_of_block<kSplit>(blockIdx.x, rank, part);
+__global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_raster_fwd(FwdArgs a, ViewsK views) {
+    __shared__ StagedA stA[2][kBatch];
+    __shared__ StagedB stB[2][kBatch];
+    __shared__ StagedF stF[2][kBatch];
+    __shared__ float out[4][kFwdThreads];   // colour, transmittance of the half's pixels, row by row
+    __shared__ int out_last[kFwdThreads];
+    int rank, half;
+    half_of_block(blockIdx.x, rank, half);
     if (rank >= a.total_tiles) return;
+    const int wv = threadIdx.x / kWave, quad = 2 * half + wv;
+    StagedA *const sA = stA[wv];
+    StagedB *const sB = stB[wv];
+    StagedF *const sF = stF[wv];
     const int tile = (int)a.order[rank];
     const ViewK &vw = views.v[view_of_tile(views, tile)];
     const int lt = tile - vw.tile_base;
     const int tx = lt % vw.gw, ty = lt / vw.gw;
     const int px0 = vw.roi_x + kTile * tx, py0 = vw.roi_y + kTile * ty;
-    const int lane = threadIdx.x;
-    const int lx = lane & 15, ly = lane >> 4;
-    const int rx = kTile * tx + lx;
-    const int row0 = part * (kTile / kSplit);   // first tile row of this part
+    const int lane = threadIdx.x & (kWave - 1);
+    const int qx = kQuad * (quad & 1), qy = kQuad * (quad >> 1);   // the quadrant's first pixel in the tile
+    const int lx = qx + (lane & (kQuad - 1)), ly = qy + lane / kQuad;
+    const int rx = kTile * tx + lx, ry = kTile * ty + ly;
 
     // A pixel composites while its row offset fy is finite; one that stopped
     // (or lies outside the region) gets kInactiveRow, so that no later splat
     // is a candidate there.
-    float T[kPixPerLane], cr[kPixPerLane], cg[kPixPerLane], cb[kPixPerLane], fy[kPixPerLane];
-    int last[kPixPerLane];
-    uint32_t ne[kPixPerLane], nb[kPixPerLane];
-#pragma unroll
-    for (int q = 0; q < kPixPerLane; q++) {
-        ne[q] = nb[q] = 0;
-        const int ryl = row0 + ly + 4 * q;
-        const bool in = rx < vw.roi_w && kTile * ty + ryl < vw.roi_h;
-        T[q] = 1.f;
-        cr[q] = cg[q] = cb[q] = 0.f;
-        last[q] = 0;
-        fy[q] = in ? (float)ryl : kInactiveRow;
-    }
+    float T = 1.f, cr = 0.f, cg = 0.f, cb = 0.f;
+    int last = 0;
+    uint32_t ne = 0, nb = 0;
     const float fxl = (float)lx;
+    float fy = rx < vw.roi_w && ry < vw.roi_h ? (float)ly : kInactiveRow;
 
     const uint2 rg = a.ranges[tile];
     const int len = (int)(rg.y - rg.x);
@@ -121,7 +127,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     int cuts_done = 0;
     gather(lane);
     for (int b0 = 0; b0 < len; b0 += kBatch) {
-        if (!any_active(fy)) break;
+        if (!wave_any(fy != kInactiveRow)) break;
         if (cuts_done < ncut && b0 == (cuts_done + 1) * kChunk) {
             // The lane index is read here, not reused from the kernel's
             // start, so that no per-lane record address stays live through
@@ -129,24 +135,23 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             // per SIMD).
             uint32_t ln;
             asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-#pragma unroll
-            for (int q = 0; q < kPixPerLane; q++) {
-                const int ryl = row0 + (int)(ln >> 4) + 4 * q;
-                if (fy[q] != kInactiveRow)   // still compositing (so inside the region)
-                    a.ckpt[(size_t)((rg.x + (uint32_t)b0) / kChunk) * (kTile * kTile) +
-                           (uint32_t)(ryl * kTile) + (ln & 15)] = make_float4(T[q], cr[q], cg[q], cb[q]);
-            }
+            if (fy != kInactiveRow)   // still compositing (so inside the region)
+                a.ckpt[(size_t)((rg.x + (uint32_t)b0) / kChunk) * (kTile * kTile) +
+                       (uint32_t)((qy + (int)(ln / kQuad)) * kTile + qx) + (ln & (kQuad - 1))] =
+                    make_float4(T, cr, cg, cb);
             cuts_done++;
         }
-        // Stage the entries that can reach 1/255 somewhere in this part's
-        // rows, in list order; the others cannot change any of its pixels.
+        // Stage the entries that can reach 1/255 somewhere in this quadrant,
+        // in list order; the others cannot change any of its pixels.
         const float u = rel_coord(g0.x, g0.z, px0), v = rel_coord(g0.y, g0.w, py0);
         const int k = b0 + lane;
-        const uint32_t mask = k < len ? band_mask<kSplit>(u, v, g1.x, g1.y, g1.z, g1.w, row0) : 0u;
-        const unsigned long long kept = __ballot(mask != 0u);
+        const float ul = u - (float)qx, vl = v - (float)qy;
+        const bool keep = k < len && SplatForm(g1.x, g1.y, g1.z, g1.w)
+                                         .reaches(ul - (float)(kQuad - 1), ul, vl - (float)(kQuad - 1), vl);
+        const unsigned long long kept = __ballot(keep);
         const int nk = __popcll(kept);
-        const bool nc_batch = __ballot(mask != 0u && !(g1.w <= kLoNoClamp)) == 0ull;
-        if (mask != 0u) {
+        const bool nc_batch = __ballot(keep && !(g1.w <= kLoNoClamp)) == 0ull;
+        if (keep) {
             const int r = kept_rank(kept);
             sA[r] = StagedA{u, v, g1.x, g1.y};
             sB[r] = StagedB{g1.z, g1.w, gc.x, gc.y};
@@ -158,11 +163,11 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             sB[lane] = StagedB{-1.f, -INFINITY, 0.f, 0.f};
             sF[lane] = StagedF{0.f, 0u};
         }
-        __syncthreads();
+        wave_sync();
         gather(b0 + kBatch + lane);
         // NC: no staged entry of the batch can reach the 0.99 clamp (same
         // alphas, one operation fewer per pixel); false once every pixel of
-        // the part has stopped
+        // the quadrant has stopped
         auto walk = [&](auto nc_c) __attribute__((always_inline)) {
             constexpr bool NC = decltype(nc_c)::value;
             for (int j0 = 0; j0 < nk; j0 += kUnroll) {
@@ -179,65 +184,70 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                 for (int u2 = 0; u2 < kUnroll; u2++) {
                     const int jp1 = (int)ef[u2].jp1;   // list position + 1
                     const ColTerms ct = col_terms(es[u2], fxl);
-                    // hits: pixels still compositing (finite fy; the others get
-                    // p2 = -inf and alpha = 0) with power <= 0 and alpha >= 1/255.
-                    // (No separate p2 bound first: the staging cull already
-                    // dropped the entries that reach 1/255 nowhere in these rows,
-                    // and the backward's looser bound on p2 accepts every hit.)
-                    float alpha[kPixPerLane];
-                    bool hit[kPixPerLane];
-                    bool any = false;
-    #pragma unroll
-                    for (int q = 0; q < kPixPerLane; q++) {
-                        const float p2 = splat_p2(ct, et[u2].C2, es[u2].v - fy[q]);
-                        const float apre = splat_alpha_pre(p2, et[u2].lo);
-                        alpha[q] = NC ? apre : fminf(kAlphaMax, apre);   // NC: below the clamp
-                        hit[q] = (p2 <= 0.f) & (alpha[q] >= kAlphaMin);
-                        any |= hit[q];
+                    // hit: still compositing (finite fy; otherwise p2 = -inf and
+                    // alpha = 0) with power <= 0 and alpha >= 1/255.  (No
+                    // separate p2 bound first: the staging cull already dropped
+                    // the entries that reach 1/255 nowhere in the quadrant, and
+                    // the backward's looser bound on p2 accepts every hit.)
+                    const float p2 = splat_p2(ct, et[u2].C2, es[u2].v - fy);
+                    const float apre = splat_alpha_pre(p2, et[u2].lo);
+                    const float alpha = NC ? apre : fminf(kAlphaMax, apre);   // NC: below the clamp
+                    const bool hit = (p2 <= 0.f) & (alpha >= kAlphaMin);
+                    if (!wave_any(hit)) continue;   // nothing to do for the quadrant
+                    const float aT = alpha * T;
+                    const float testT = T - aT;   // T (1 - alpha)
+                    const bool blend = hit && testT >= kTMin;
+                    const bool stop = hit && !(testT >= kTMin);
+                    if (STATS) {
+                        nb += blend ? 1u : 0u;
+                        ne = stop ? (uint32_t)jp1 : ne;
                     }
-                    // no pixel of this part reaches 1/255: nothing to do
-                    if (!wave_any(any)) continue;
-    #pragma unroll
-                    for (int q = 0; q < kPixPerLane; q++) {
-                        const float aT = alpha[q] * T[q];
-                        const float testT = T[q] - aT;   // T (1 - alpha)
-                        const bool blend = hit[q] && testT >= kTMin;
-                        const bool stop = hit[q] && !(testT >= kTMin);
-                        if (STATS) {
-                            nb[q] += blend ? 1u : 0u;
-                            ne[q] = stop ? (uint32_t)jp1 : ne[q];
-                        }
-                        const float wgt = blend ? aT : 0.f;
-                        cr[q] = fmaf(et[u2].r, wgt, cr[q]);
-                        cg[q] = fmaf(et[u2].g, wgt, cg[q]);
-                        cb[q] = fmaf(ef[u2].b, wgt, cb[q]);
-                        last[q] = blend ? jp1 : last[q];
-                        T[q] = blend ? testT : T[q];
-                        fy[q] = stop ? kInactiveRow : fy[q];
-                    }
+                    const float wgt = blend ? aT : 0.f;
+                    cr = fmaf(et[u2].r, wgt, cr);
+                    cg = fmaf(et[u2].g, wgt, cg);
+                    cb = fmaf(ef[u2].b, wgt, cb);
+                    last = blend ? jp1 : last;
+                    T = blend ? testT : T;
+                    fy = stop ? kInactiveRow : fy;
                 }
-                if (!any_active(fy)) return false;
+                if (!wave_any(fy != kInactiveRow)) return false;
             }
             return true;
         };
         const bool more = nc_batch ? walk(std::true_type{}) : walk(std::false_type{});
         if (!more) break;
-        __syncthreads();
+        wave_sync();
     }
 
+    if (STATS && rx < vw.roi_w && ry < vw.roi_h) {
+        const size_t pix = (size_t)vw.pix_base + (size_t)ry * vw.roi_w + rx;
+        // a pixel that never stopped evaluated the whole list
+        a.neval[pix] = fy == kInactiveRow ? ne : (uint32_t)len;
+        a.nblend[pix] = nb;
+    }
+    // Every wave of the half gets here (each loop above ends for itself), and
+    // each writes a 16 x 4 strip of it.
+    {
+        const int at = (lane / kQuad) * kTile + lx;
+        out[0][at] = cr + T * vw.bg[0];
+        out[1][at] = cg + T * vw.bg[1];
+        out[2][at] = cb + T * vw.bg[2];
+        out[3][at] = T;
+        out_last[at] = last;
+    }
+    __syncthreads();
+    const int ox = kTile * tx + (int)(threadIdx.x % kTile);
+    const int oy = kTile * ty + kQuad * half + (int)(threadIdx.x / kTile);
     const int P = vw.roi_w * vw.roi_h;
     // L1-fused: sign(image - target) / (3 P), as gsp_loss_l1 writes it
     const float l1_inv = 1.0f / (float)(3 * (int64_t)P);
     double l1sum = 0.0;
-#pragma unroll
-    for (int q = 0; q < kPixPerLane; q++) {
-        const int ry = kTile * ty + row0 + ly + 4 * q;
-        if (rx >= vw.roi_w || ry >= vw.roi_h) continue;
-        const size_t pix = (size_t)ry * vw.roi_w + rx;
-        const float Tf = T[q];
+    if (ox < vw.roi_w && oy < vw.roi_h) {
+        const size_t pix = (size_t)oy * vw.roi_w + ox;
         float *img = vw.img;
-        const float fr = cr[q] + Tf * vw.bg[0], fg = cg[q] + Tf * vw.bg[1],
-                    fb = cb[q] + Tf * vw.bg[2];
+        const float fr = out[0][threadIdx.x], fg = out[1][threadIdx.x], fb = out[2][threadIdx.x];
+        const float Tf = out[3][threadIdx.x];
+        const int lastf = out_last[threadIdx.x];
         if (a.l1) {
             const float *tg = vw.dl;
             const float c3[3] = {fr, fg, fb};
@@ -252,23 +262,18 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             img[(size_t)P + pix] = fg;
             img[2 * (size_t)P + pix] = fb;
         }
-        if (last[q] > kChunk) {   // the backward's chunks derive the colour behind a cut from it
+        if (lastf > kChunk) {   // the backward's chunks derive the colour behind a cut from it
             a.cfinal[vw.pix_base + pix] = fr;
             a.cfinal[(size_t)a.total_pix + vw.pix_base + pix] = fg;
             a.cfinal[2 * (size_t)a.total_pix + vw.pix_base + pix] = fb;
         }
         a.tfinal[vw.pix_base + pix] = Tf;
-        a.ncontrib[vw.pix_base + pix] = (uint32_t)last[q];
+        a.ncontrib[vw.pix_base + pix] = (uint32_t)lastf;
         if (vw.alpha) vw.alpha[pix] = 1.f - Tf;
-        if (STATS) {
-            // a pixel that never stopped evaluated the whole list
-            a.neval[vw.pix_base + pix] = fy[q] == kInactiveRow ? ne[q] : (uint32_t)len;
-            a.nblend[vw.pix_base + pix] = nb[q];
-        }
     }
     if (a.l1part) {
         l1sum = wave_sum(l1sum);
-        if (lane == 0) a.l1part[(size_t)tile * kSplit + part] = l1sum;
+        if (lane == 0) a.l1part[(size_t)tile * kSplitFwd + quad] = l1sum;   // strip 2 half + wv
     }
 }
 
@@ -278,7 +283,7 @@ __global__ __launch_bounds__(256) void k_l1_fused_final(ViewsK views, const doub
                                                         float *loss) {
     __shared__ double red[256 / kWave];
     const ViewK &vw = views.v[blockIdx.x];
-    const int64_t b0 = (int64_t)vw.tile_base * kSplit, n = (int64_t)vw.gw * vw.gh * kSplit;
+    const int64_t b0 = (int64_t)vw.tile_base * kSplitFwd, n = (int64_t)vw.gw * vw.gh * kSplitFwd;
     double s = 0.0;
     for (int64_t k = threadIdx.x; k < n; k += 256) s += l1part[b0 + k];
     s = block_sum<double, 256>(s, red);
@@ -304,11 +309,11 @@ hipError_t launch_raster_fwd(const ViewsK &views, const Layout &L, char *ws, con
     a.cfinal = region<float>(ws, L.cfinal);
     a.total_pix = (int)L.total_pix;
     a.total_tiles = L.total_tiles;
-    const dim3 grid(raster_blocks<kSplit>(L.total_tiles));
+    const dim3 grid(raster_fwd_blocks(L.total_tiles));
     if (stats)
-        hipLaunchKernelGGL(k_raster_fwd<true>, grid, dim3(kRasterThreads), 0, s, a, views);
+        hipLaunchKernelGGL(k_raster_fwd<true>, grid, dim3(kFwdThreads), 0, s, a, views);
     else
-        hipLaunchKernelGGL(k_raster_fwd<false>, grid, dim3(kRasterThreads), 0, s, a, views);
+        hipLaunchKernelGGL(k_raster_fwd<false>, grid, dim3(kFwdThreads), 0, s, a, views);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !a.l1part) return e;
     hipLaunchKernelGGL(k_l1_fused_final, dim3(views.count), dim3(256), 0, s, views, a.l1part, loss);

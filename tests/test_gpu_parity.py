@@ -293,6 +293,30 @@ def test_image_parity(name):
     assert np.mean(nc[ok] == ref["n_contrib"][ok]) >= 0.999
 
 
+# the forward's 8 x 8 quadrants and the halves that write them: regions that end
+# inside, at and just past a quadrant, with lists that are cut; splats from
+# needles through the whole region to a fraction of a pixel, up close
+@pytest.mark.parametrize("size", [(1, 1), (8, 8), (9, 7), (7, 9), (16, 8), (17, 9), (25, 24), (24, 33)])
+@pytest.mark.parametrize("kind", ["deep", "thin"])
+def test_forward_at_quadrant_edges(size, kind):
+    w, h = size
+    if kind == "deep":
+        sc, cam, pose = random_case(17, 1, 64, 48, 9000, depth=(1.0, 8.0), roi=(16, 0, w, h))
+    else:
+        sc, cam, pose = random_case(19, 1, 64, 48, 900, depth=(0.1, 3.0), roi=(16, 0, w, h))
+        rng = S.rng_for(19, 9)
+        sc.scales[np.arange(sc.n), rng.integers(0, 3, sc.n)] *= np.float32(30.0)
+        sc.opacities[:] = rng.uniform(0.005, 0.6, sc.n).astype(np.float32)
+    run = _gpu(sc, [cam], [pose])
+    ref = oracle.render(sc, cam, pose)
+    _image_check(run["images"][0], ref, f"{kind} {w}x{h}")
+    ok = ~ref["straddle"]
+    alpha = run["alpha"].reshape(ref["T_final"].shape)
+    assert ok.any() and np.max(np.abs((1 - alpha)[ok] - ref["T_final"][ok])) <= 1e-5
+    nc = run["rast"].inspect(run["g"], [cam], "ncontrib", torch.int32).cpu().numpy()
+    assert np.array_equal(nc.reshape(ok.shape)[ok], ref["n_contrib"][ok])
+
+
 @pytest.mark.parametrize("name", CASES)
 def test_backward_parity(name):
     sc, cam, pose = _case(name)
