@@ -235,6 +235,7 @@ Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views,
     L.cfinal = take((size_t)pix * 12);
     L.tfinal = take((size_t)pix * 4);
     L.ncontrib = take((size_t)pix * 4);
+    L.tile_last = take((size_t)L.total_tiles * kSplitFwd * 4);
     L.stats = take((size_t)pix * 8);
     L.slots = take(9 * (size_t)kSplitBwd * capz * 4);
     L.slot_flags = take(((size_t)kSplitBwd * capz + 3) & ~size_t(3));

@@ -122,7 +122,7 @@ struct Layout {
     size_t pairs, vals, ranges, tile_order;
     size_t items, ckpt, cfinal;   // backward work items, states at the cuts, final colours
     int64_t max_items;
-    size_t tfinal, ncontrib, stats, slots, slot_flags, grad2d, posepart, l1part;
+    size_t tfinal, ncontrib, tile_last, stats, slots, slot_flags, grad2d, posepart, l1part;
     size_t total;
 };
 

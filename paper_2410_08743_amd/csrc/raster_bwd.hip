@@ -52,6 +52,7 @@ struct BwdArgs {
     const uint32_t *offsets;
     const float *tfinal;
     const uint32_t *ncontrib;
+    const uint4 *tile_last;   // per tile: largest contributor count of each quadrant
     float *slots;          // [cap][9]
     uint8_t *slot_flags;   // [cap]: 1 where this kernel wrote the slot
     // stored-list variant only
@@ -184,13 +185,48 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     const float4 *const ck =
         chunk < nch - 1 ? a.ckpt + (size_t)((rg.x + (uint32_t)chi) / kChunk) * (kTile * kTile)
                         : nullptr;
+    int maxlast = 0;
+    if (!STORED) {
+        // The largest contributor count of the tile's pixels in this chunk; none
+        // when every pixel stopped in front of it, as in half of the items of
+        // the joint and pose steps' long lists (they leave here, before their
+        // pixels' state is read: 804 -> 783 us over 4 views of 1008 x 756,
+        // 1027 -> 972 us over 8 views of three sizes).
+        const uint4 tl = a.tile_last[tile];
+        maxlast = min((int)max(max(tl.x, tl.y), max(tl.z, tl.w)), chi);
+        if (maxlast <= clo) return;
+    }
+    // Batches of 64 entries ending at hi, walked back to front; positions
+    // below clo are absent.  Records are gathered one batch ahead, by ids read
+    // two batches ahead (so that no wave waits for the one to issue the other).
+    float4 g0, g1, gc;
+    uint32_t gslot, id = 0;
+    auto read_id = [&](int k) {
+        if (k >= clo) id = a.vals[rg.x + k];
+    };
+    auto gather = [&](int k) {
+        g0 = make_float4(0.f, 0.f, 0.f, 0.f);
+        g1 = make_float4(-1.f, 0.f, -1.f, -INFINITY);
+        gc = make_float4(0.f, 0.f, 0.f, 0.f);
+        gslot = kNoSlot;
+        if (k >= clo) {
+            g0 = a.geom[2 * (size_t)id];
+            g1 = a.geom[2 * (size_t)id + 1];
+            gc = a.color[id];
+            gslot = slot_of(a, id, tx, ty);
+        }
+    };
+    if (!STORED) {
+        read_id(maxlast - kBatch + lane);
+        gather(maxlast - kBatch + lane);
+        read_id(maxlast - 2 * kBatch + lane);
+    }
     float T[kPixPerLane], G[kPixPerLane][3], GS[kPixPerLane], fy[kPixPerLane];
     int last[kPixPerLane];
     // stored lists: the pixel's next pair back to front (position, alpha, T)
     // and its index; pbase is the pixel's first pair
     uint32_t npos[kPixPerLane], pidx[kPixPerLane], pbase[kPixPerLane];
     float nal[kPixPerLane];
-    int maxlast = 0;
 #pragma unroll
     for (int q = 0; q < kPixPerLane; q++) {
         const int ryl = ly + 4 * q;
@@ -234,9 +270,16 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             last[q] = chi;
         }
         GS[q] = G[q][0] * S0 + G[q][1] * S1 + G[q][2] * S2;
-        maxlast = max(maxlast, last[q]);
+        if (STORED) maxlast = max(maxlast, last[q]);
     }
-    maxlast = wave_max(maxlast);
+    if (STORED) {
+        maxlast = wave_max(maxlast);
+        if (maxlast > clo) {
+            read_id(maxlast - kBatch + lane);
+            gather(maxlast - kBatch + lane);
+            read_id(maxlast - 2 * kBatch + lane);
+        }
+    }
     // largest contributor count of each band: an entry at or past it has no
     // candidate pixel in the band
     int blast[kPixPerLane];
@@ -244,24 +287,6 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     for (int q = 0; q < kPixPerLane; q++) blast[q] = __builtin_amdgcn_readfirstlane(wave_max(last[q]));
     const float fxl = (float)lx;
 
-    // batches of 64 entries ending at hi, walked back to front; positions
-    // below clo are absent.  Records are gathered one batch ahead.
-    float4 g0, g1, gc;
-    uint32_t gslot;
-    auto gather = [&](int k) {
-        g0 = make_float4(0.f, 0.f, 0.f, 0.f);
-        g1 = make_float4(-1.f, 0.f, -1.f, -INFINITY);
-        gc = make_float4(0.f, 0.f, 0.f, 0.f);
-        gslot = kNoSlot;
-        if (k >= clo) {
-            const uint32_t id = a.vals[rg.x + k];
-            g0 = a.geom[2 * (size_t)id];
-            g1 = a.geom[2 * (size_t)id + 1];
-            gc = a.color[id];
-            gslot = slot_of(a, id, tx, ty);
-        }
-    };
-    if (maxlast > clo) gather(maxlast - kBatch + lane);
     for (int hi = maxlast; hi > clo; hi -= kBatch) {
         const int lo = hi - kBatch;
         // Stage, in list order, the entries that can reach 1/255 somewhere in
@@ -272,9 +297,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             gslot != kNoSlot ? band_mask(u, v, g1.x, g1.y, g1.z, g1.w) : 0u;
         const unsigned long long kept = __ballot(mask != 0u);
         const int nk = __popcll(kept);
-        // an opacity below exp2(kLoNoClamp) keeps o exp(power) below the
-        // clamp wherever power <= 0
-        const bool nc_batch = __ballot(mask != 0u && !(g1.w <= kLoNoClamp)) == 0ull;
+        const bool plain_batch = __ballot(mask != 0u && !plain_splat(g1.x, g1.y, g1.z, g1.w)) == 0ull;
         if (mask != 0u) {
             const int r = kept_rank(kept);
             sA[r] = StagedA{u, v, g1.x, g1.y};
@@ -290,11 +313,15 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             sM[lane] = 0u;
         }
         __syncthreads();
-        if (lo > clo) gather(lo - kBatch + lane);
-        // NC: no staged entry of the batch can reach the 0.99 clamp, whose
-        // tests then drop out of the walk (same results, fewer operations)
-        auto walk = [&](auto nc_c) __attribute__((always_inline)) {
-            constexpr bool NC = decltype(nc_c)::value;
+        if (lo > clo) {
+            gather(lo - kBatch + lane);
+            read_id(lo - 2 * kBatch + lane);
+        }
+        // PLAIN: no staged entry of the batch can reach the 0.99 clamp or a
+        // positive power, whose tests then drop out of the walk (same results,
+        // fewer operations)
+        auto walk = [&](auto plain_c) __attribute__((always_inline)) {
+            constexpr bool PLAIN = decltype(plain_c)::value;
             StagedA es[kBwdUnroll];
             StagedB et[kBwdUnroll];
             StagedC ew[kBwdUnroll];
@@ -368,8 +395,8 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                         } else {
                             const float p2 = splat_p2(ct, t.C2, dy);
                             apre = splat_alpha_pre(p2, t.lo);
-                            a0 = NC ? apre : fminf(kAlphaMax, apre);   // NC: below the clamp
-                            cand = (pos < last[q]) & (p2 <= 0.f) & (a0 >= kAlphaMin);
+                            a0 = PLAIN ? apre : fminf(kAlphaMax, apre);
+                            cand = (pos < last[q]) & (PLAIN | (p2 <= 0.f)) & (a0 >= kAlphaMin);
                         }
                         if (__builtin_amdgcn_ballot_w64(cand) == 0ull) continue;
                         blended = true;
@@ -387,7 +414,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                             // and the sums (plus 0) exactly as they are.
                             valid = cand;
                             alpha = valid ? a0 : 0.f;
-                            unclamped = NC || apre <= kAlphaMax;
+                            unclamped = PLAIN || apre <= kAlphaMax;
                             T[q] = T[q] * __builtin_amdgcn_rcpf(1.f - alpha);
                             wgt = alpha * T[q];
                         }
@@ -458,7 +485,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                 }
             }
         };
-        if (!STORED && nc_batch) walk(std::true_type{});
+        if (!STORED && plain_batch) walk(std::true_type{});
         else walk(std::false_type{});
         __syncthreads();
     }
@@ -483,6 +510,7 @@ hipError_t launch_raster_bwd(const ViewsK &views, const Layout &L, char *ws, con
     a.offsets = region<uint32_t>(ws, L.offsets);
     a.tfinal = region<float>(ws, L.tfinal);
     a.ncontrib = region<uint32_t>(ws, L.ncontrib);
+    a.tile_last = region<uint4>(ws, L.tile_last);
     a.slots = region<float>(ws, L.slots);
     a.slot_flags = region<uint8_t>(ws, L.slot_flags);
     // Slots that no entry writes keep the flag 0 that the forward

@@ -127,6 +127,16 @@ struct SplatForm {
     }
 };
 
+// True for a splat whose opacity keeps o exp(power) below the 0.99 clamp
+// wherever power <= 0, and whose form is definite enough that splat_p2 is never
+// positive in float32: with B^2 <= 4 A C (1 - 1e-4), the sum in it stays
+// negative under the relative errors (2^-24 each) of its three roundings, and
+// the last rounding keeps the sign.  The rasterizers walk a batch of such splats
+// without the two tests.
+__device__ __forceinline__ bool plain_splat(float A2, float B2, float C2, float lo) {
+    return (lo <= kLoNoClamp) & (A2 < 0.f) & (C2 < 0.f) & (B2 * B2 <= 3.9996f * (A2 * C2));
+}
+
 // Bit q of the result is set when some pixel of the 16 x 4 band q of the tile
 // may be reached; u, v: the centre relative to the tile's first pixel.
 __device__ __forceinline__ uint32_t band_mask(float u, float v, float A2, float B2, float C2, float lo) {

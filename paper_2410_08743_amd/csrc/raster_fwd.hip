@@ -18,13 +18,20 @@
 // LDS, so that each writes four rows of 16 pixels.
 //
 // Bound by VALU issue.  A square quadrant meets fewer splats than a 16 x 4
-// strip (539 against 601 kept entries per tile and part at the benchmark view, 507
-// against 552 of them with a hit): 98.5 -> 89.2 us at 640 x 480 with 100k
-// splats, 83 -> 76 us over 500k splats, 36 -> 31 us at 320 x 240, 666 -> 598 us
-// over 16 views of 640 x 480; 426 -> 428 us over 8 views in which the outputs'
-// traffic weighs more.  Without the exchange a wave writes rows of 8 pixels,
-// and those half lines cost more than the square saves once the outputs
-// outgrow the L2 (515 us over the 8 views, 728 us over the 16).
+// strip (539 against 601 kept entries per tile, summed over its four parts, at
+// the benchmark view; 507 against 552 of them with a hit): 98.5 -> 89.2 us at
+// 1008 x 756 with 200k splats, 83 -> 76 us at 1200 x 680 with 500k, 36 -> 31 us
+// at 320 x 240 with 50k, 666 -> 598 us over 8 views of 1008 x 756 to 320 x 240
+// with 1M; 426 -> 428 us over 4 views of 1008 x 756, where the outputs' traffic
+// weighs more.  Without the exchange a wave writes rows of 8 pixels, and those
+// half lines cost more than the square saves once the outputs outgrow the L2
+// (515 us over the 4 views, 728 us over the 8).
+//
+// The inner loop tests only what can be: no clamp and no sign of the power in a
+// batch of plain splats, and the two selects of a pixel that stops only when
+// one does (428 -> 410 us over the 4 views, 598 -> 549 us over the 8).  More
+// entries per step (4: 439 us) or fewer (1: 426 us) lose more in registers or
+// LDS round trips; so do fewer resident waves (6 per SIMD: 422 us).
 #include <type_traits>
 
 #include "block_ops.h"
@@ -50,6 +57,7 @@ struct FwdArgs {
     const float4 *color;
     float *tfinal;
     uint32_t *ncontrib;
+    uint32_t *tile_last;   // [total_tiles][kSplitFwd]: largest contributor count of the quadrant
     uint32_t *neval;    // STATS only: entries evaluated per pixel (up to the stop)
     uint32_t *nblend;   // STATS only: entries blended per pixel
     float4 *ckpt;       // per cut and tile pixel: (T, colour in front of the cut)
@@ -125,9 +133,10 @@ void k_raster_fwd(FwdArgs a, ViewsK views) {
     // for pixels that blend past the cut that ends its chunk.
     const int ncut = chunks_of(len) - 1;
     int cuts_done = 0;
+    bool alive = wave_any(fy != kInactiveRow);   // some pixel still composites
     gather(lane);
     for (int b0 = 0; b0 < len; b0 += kBatch) {
-        if (!wave_any(fy != kInactiveRow)) break;
+        if (!alive) break;
         if (cuts_done < ncut && b0 == (cuts_done + 1) * kChunk) {
             // The lane index is read here, not reused from the kernel's
             // start, so that no per-lane record address stays live through
@@ -150,7 +159,7 @@ void k_raster_fwd(FwdArgs a, ViewsK views) {
                                          .reaches(ul - (float)(kQuad - 1), ul, vl - (float)(kQuad - 1), vl);
         const unsigned long long kept = __ballot(keep);
         const int nk = __popcll(kept);
-        const bool nc_batch = __ballot(keep && !(g1.w <= kLoNoClamp)) == 0ull;
+        const bool plain_batch = __ballot(keep && !plain_splat(g1.x, g1.y, g1.z, g1.w)) == 0ull;
         if (keep) {
             const int r = kept_rank(kept);
             sA[r] = StagedA{u, v, g1.x, g1.y};
@@ -165,11 +174,11 @@ void k_raster_fwd(FwdArgs a, ViewsK views) {
         }
         wave_sync();
         gather(b0 + kBatch + lane);
-        // NC: no staged entry of the batch can reach the 0.99 clamp (same
-        // alphas, one operation fewer per pixel); false once every pixel of
-        // the quadrant has stopped
-        auto walk = [&](auto nc_c) __attribute__((always_inline)) {
-            constexpr bool NC = decltype(nc_c)::value;
+        // PLAIN: no staged entry of the batch can reach the 0.99 clamp or a
+        // positive power (same alphas and hits, two operations fewer per
+        // pixel); false once every pixel of the quadrant has stopped
+        auto walk = [&](auto plain_c) __attribute__((always_inline)) {
+            constexpr bool PLAIN = decltype(plain_c)::value;
             for (int j0 = 0; j0 < nk; j0 += kUnroll) {
                 StagedA es[kUnroll];
                 StagedB et[kUnroll];
@@ -191,30 +200,38 @@ void k_raster_fwd(FwdArgs a, ViewsK views) {
                     // the backward's looser bound on p2 accepts every hit.)
                     const float p2 = splat_p2(ct, et[u2].C2, es[u2].v - fy);
                     const float apre = splat_alpha_pre(p2, et[u2].lo);
-                    const float alpha = NC ? apre : fminf(kAlphaMax, apre);   // NC: below the clamp
-                    const bool hit = (p2 <= 0.f) & (alpha >= kAlphaMin);
+                    const float alpha = PLAIN ? apre : fminf(kAlphaMax, apre);
+                    const bool hit = (PLAIN | (p2 <= 0.f)) & (alpha >= kAlphaMin);
                     if (!wave_any(hit)) continue;   // nothing to do for the quadrant
-                    const float aT = alpha * T;
-                    const float testT = T - aT;   // T (1 - alpha)
-                    const bool blend = hit && testT >= kTMin;
-                    const bool stop = hit && !(testT >= kTMin);
-                    if (STATS) {
-                        nb += blend ? 1u : 0u;
-                        ne = stop ? (uint32_t)jp1 : ne;
+                    // A pixel without a hit takes alpha = 0, which leaves its T
+                    // and colour exactly as they are.
+                    float ahit = hit ? alpha : 0.f;
+                    float testT = T - ahit * T;   // T (1 - alpha)
+                    bool blend = hit;
+                    // T >= 1e-4 until here, so only a hit can take it below: once
+                    // in a pixel's walk, handled aside
+                    const bool stop = !(testT >= kTMin);
+                    if (wave_any(stop)) {
+                        ahit = stop ? 0.f : ahit;
+                        testT = stop ? T : testT;
+                        blend = blend && !stop;
+                        fy = stop ? kInactiveRow : fy;
+                        if (STATS) ne = stop ? (uint32_t)jp1 : ne;
+                        alive = wave_any(fy != kInactiveRow);
                     }
-                    const float wgt = blend ? aT : 0.f;
+                    if (STATS) nb += blend ? 1u : 0u;
+                    const float wgt = ahit * T;
                     cr = fmaf(et[u2].r, wgt, cr);
                     cg = fmaf(et[u2].g, wgt, cg);
                     cb = fmaf(ef[u2].b, wgt, cb);
                     last = blend ? jp1 : last;
-                    T = blend ? testT : T;
-                    fy = stop ? kInactiveRow : fy;
+                    T = testT;
                 }
-                if (!wave_any(fy != kInactiveRow)) return false;
+                if (!alive) return false;
             }
             return true;
         };
-        const bool more = nc_batch ? walk(std::true_type{}) : walk(std::false_type{});
+        const bool more = plain_batch ? walk(std::true_type{}) : walk(std::false_type{});
         if (!more) break;
         wave_sync();
     }
@@ -225,6 +242,8 @@ void k_raster_fwd(FwdArgs a, ViewsK views) {
         a.neval[pix] = fy == kInactiveRow ? ne : (uint32_t)len;
         a.nblend[pix] = nb;
     }
+    const int deepest = wave_max(last);
+    if (lane == 0) a.tile_last[(size_t)tile * kSplitFwd + quad] = (uint32_t)deepest;
     // Every wave of the half gets here (each loop above ends for itself), and
     // each writes a 16 x 4 strip of it.
     {
@@ -303,6 +322,7 @@ hipError_t launch_raster_fwd(const ViewsK &views, const Layout &L, char *ws, con
     a.color = region<float4>(ws, L.color);
     a.tfinal = region<float>(ws, L.tfinal);
     a.ncontrib = region<uint32_t>(ws, L.ncontrib);
+    a.tile_last = region<uint32_t>(ws, L.tile_last);
     a.neval = region<uint32_t>(ws, L.stats);
     a.nblend = a.neval + L.total_pix;
     a.ckpt = region<float4>(ws, L.ckpt);
