@@ -22,12 +22,17 @@
 // 1/255 nowhere in the tile.  Each lane sums its pixels in registers; the
 // nine sums are reduced over the 64 lanes in two steps: v_permlane32_swap
 // and v_permlane16_swap leave each as 16 partial sums in one row of lanes (16
-// VALU operations for the nine), which wait in LDS; every kPend entries, 63
+// VALU operations for the nine), which wait in LDS; every kPend entries, 9 kPend
 // lanes each add up the 16 partials of one (entry, component) in a fixed
 // order and store it into the instance's own slot (its position among the
 // instances splat by splat), flagging it written.  No atomics: the per-splat
 // sum over its slots happens later in a fixed order, so gradients are
 // bit-reproducible.
+//
+// Bound by VALU issue: the VALUs are busy 93 % of the time over 4 views of
+// 1008 x 756; 77 % over one, whose last items leave the chip half empty for the
+// last 40 of its 170 us (chunks of 64 entries shorten that, but cost 10 % more
+// over several views, whose items all read their pixels' state).
 #include <cstring>
 #include <type_traits>
 
@@ -65,21 +70,6 @@ struct BwdArgs {
 
 constexpr uint32_t kNoSlot = 0xffffffffu;
 
-#ifndef GSP_BWD_UNROLL
-#define GSP_BWD_UNROLL 2
-#endif
-constexpr int kBwdUnroll = GSP_BWD_UNROLL;   // entries whose LDS records are read together
-// Entries whose row partials wait in LDS before a flush (at most 7: nine
-// lanes per entry in the flush).
-#ifndef GSP_BWD_PEND
-#define GSP_BWD_PEND 7
-#endif
-static_assert(GSP_BWD_PEND >= 1 && 9 * GSP_BWD_PEND <= 64, "one flush lane per (entry, component)");
-// 1: each group's records are read while the group before it is processed
-#ifndef GSP_BWD_PREFETCH
-#define GSP_BWD_PREFETCH 0
-#endif
-
 // Slot of the instance of splat `id` in tile (tx, ty): its position splat by splat.
 __device__ __forceinline__ uint32_t slot_of(const BwdArgs &a, uint32_t id, int tx, int ty) {
     const uint2 r = a.rect[id];
@@ -87,9 +77,6 @@ __device__ __forceinline__ uint32_t slot_of(const BwdArgs &a, uint32_t id, int t
     return a.offsets[id] + (uint32_t)((ty - y0) * (x1 - x0) + (tx - x0));
 }
 
-#ifndef GSP_BWD_WAVES
-#define GSP_BWD_WAVES 4
-#endif
 // Pixel with no stored pair left, and the list position of padding records
 // (never a pixel's next pair; below every pixel's count as a signed int, and
 // the padding's empty band mask skips it in either walk).
@@ -105,17 +92,28 @@ constexpr uint32_t kPadPos = 0xfffffffeu;
 // wave reduces eight sums per entry instead of nine (the opacity sum, which
 // only the opacity gradient needs, is left out) and the slot's opacity
 // component is written as zero.
-template <bool STORED, bool OPA>
-__global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(GSP_BWD_WAVES))) void k_raster_bwd(BwdArgs a, ViewsK views) {
+// MANY chooses between two shapes of the same walk, with the same results: for
+// many tiles one entry per step and five pending entries, which fit 84
+// registers and 7.5 KB of LDS, five waves per SIMD; for few, where waves run
+// alone and latency counts, two entries per step and seven pending ones (113
+// registers, 9.1 KB, four waves).  (The stored-list variant spills with either's
+// registers, and takes the first at four waves.)
+template <bool STORED, bool OPA, bool MANY>
+__global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(MANY && !STORED ? 5 : 4)))
+void k_raster_bwd(BwdArgs a, ViewsK views) {
+    constexpr int kUnroll = MANY ? 1 : 2;   // entries whose LDS records are read together
+    // Entries whose row partials wait in LDS before a flush (at most 7: nine
+    // lanes per entry in the flush).
+    constexpr int kPend = MANY ? 5 : 7;
+    static_assert(9 * kPend <= kWave, "one flush lane per (entry, component)");
     __shared__ StagedA sA[kBatch];
     __shared__ StagedB sB[kBatch];
     __shared__ StagedC sC[kBatch];
     __shared__ uint32_t sM[kBatch];   // bands the entry may reach (band_mask)
     // Row partials of the nine sums of up to kPend entries (wave_sum9_rows),
-    // register-major, rows kRowStride floats apart so that the 63 lanes of a
+    // register-major, rows kRowStride floats apart so that the lanes of a
     // flush, each reading its own row, spread over the banks; and the slot
     // and 1/o of each pending entry.
-    constexpr int kPend = GSP_BWD_PEND;
     constexpr int kRowStride = 17;
     constexpr int kRegStride = 4 * kRowStride;
     constexpr int kEntryStride = 3 * kRegStride;
@@ -305,7 +303,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
             sC[r] = StagedC{gc.z, __builtin_amdgcn_exp2f(-g1.w), gslot, (uint32_t)(lo + lane)};
             sM[r] = mask;
         }
-        const int nkr = (nk + kBwdUnroll - 1) & ~(kBwdUnroll - 1);
+        const int nkr = (nk + kUnroll - 1) & ~(kUnroll - 1);
         if (lane >= nk && lane < nkr) {   // padding up to the unroll width: reaches no band
             sA[lane] = StagedA{0.f, 0.f, -1.f, 0.f};
             sB[lane] = StagedB{-1.f, -INFINITY, 0.f, 0.f};
@@ -322,49 +320,34 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
         // fewer operations)
         auto walk = [&](auto plain_c) __attribute__((always_inline)) {
             constexpr bool PLAIN = decltype(plain_c)::value;
-            StagedA es[kBwdUnroll];
-            StagedB et[kBwdUnroll];
-            StagedC ew[kBwdUnroll];
-            uint32_t em[kBwdUnroll];
-            auto load_group = [&](int j0, StagedA (&ra)[kBwdUnroll], StagedB (&rb)[kBwdUnroll],
-                                  StagedC (&rc)[kBwdUnroll], uint32_t (&rm)[kBwdUnroll]) {
-    #pragma unroll
-                for (int u = 0; u < kBwdUnroll; u++) {
-                    ra[u] = sA[j0 + u];
-                    rb[u] = sB[j0 + u];
-                    rc[u] = sC[j0 + u];
-                    rm[u] = sM[j0 + u];
+            for (int j0 = nkr - kUnroll; j0 >= 0; j0 -= kUnroll) {
+                StagedA es[kUnroll];
+                StagedB et[kUnroll];
+                StagedC ew[kUnroll];
+                uint32_t em[kUnroll];
+#pragma unroll
+                for (int u = 0; u < kUnroll; u++) {
+                    es[u] = sA[j0 + u];
+                    et[u] = sB[j0 + u];
+                    ew[u] = sC[j0 + u];
+                    em[u] = sM[j0 + u];
                 }
-            };
-            if (GSP_BWD_PREFETCH && nkr > 0) load_group(nkr - kBwdUnroll, es, et, ew, em);
-            for (int j0 = nkr - kBwdUnroll; j0 >= 0; j0 -= kBwdUnroll) {
-                // the next group's records (one group ahead: the LDS round trip
-                // overlaps this group's work), or this group's
-                StagedA es_n[kBwdUnroll];
-                StagedB et_n[kBwdUnroll];
-                StagedC ew_n[kBwdUnroll];
-                uint32_t em_n[kBwdUnroll];
-                if (GSP_BWD_PREFETCH) {
-                    load_group(j0 >= kBwdUnroll ? j0 - kBwdUnroll : 0, es_n, et_n, ew_n, em_n);
-                } else {
-                    load_group(j0, es, et, ew, em);
-                    // All records of the group are wanted in registers here: the
-                    // compiler would otherwise sink the later entries' loads
-                    // below the band test, a second LDS round trip per entry.
-                    // (Not in the stored-list variant, where it would cost spills.)
-    #pragma unroll
-                    for (int u = 0; u < (STORED ? 0 : kBwdUnroll); u++)
-                        asm volatile("" ::"v"(es[u].u), "v"(es[u].v), "v"(es[u].A2), "v"(es[u].B2),
-                                     "v"(et[u].C2), "v"(et[u].lo), "v"(et[u].r), "v"(et[u].g), "v"(ew[u].b),
-                                     "v"(ew[u].inv_o), "v"(ew[u].slot));
-                }
-    #pragma unroll
-                for (int u = kBwdUnroll - 1; u >= 0; u--) {
+                // All records of the group are wanted in registers here: the
+                // compiler would otherwise sink the later entries' loads
+                // below the band test, a second LDS round trip per entry.
+                // (Not in the stored-list variant, where it would cost spills.)
+#pragma unroll
+                for (int u = 0; u < (STORED ? 0 : kUnroll); u++)
+                    asm volatile("" ::"v"(es[u].u), "v"(es[u].v), "v"(es[u].A2), "v"(es[u].B2),
+                                 "v"(et[u].C2), "v"(et[u].lo), "v"(et[u].r), "v"(et[u].g), "v"(ew[u].b),
+                                 "v"(ew[u].inv_o), "v"(ew[u].slot));
+#pragma unroll
+                for (int u = kUnroll - 1; u >= 0; u--) {
                     // the bands this entry may reach that still have pixels
                     // compositing at its list position (wave-uniform)
                     const int pos = __builtin_amdgcn_readfirstlane((int)ew[u].pm);
                     uint32_t bands = __builtin_amdgcn_readfirstlane(em[u]);
-    #pragma unroll
+#pragma unroll
                     for (int q = 0; q < kPixPerLane; q++)
                         if (pos >= blast[q]) bands &= ~(1u << q);
                     if (bands == 0u) continue;
@@ -381,7 +364,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                     // band with no candidate pixel is skipped as a whole; inside a
                     // band the update is branch-free, pixels that do not blend
                     // adding exact zeros.
-    #pragma unroll
+#pragma unroll
                     for (int q = 0; q < kPixPerLane; q++) {
                         if (!((bands >> q) & 1u)) continue;
                         const float dy = s.v - fy[q];
@@ -420,7 +403,7 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                         }
                         const float Gc = fmaf(G[q][2], col3[2], fmaf(G[q][1], col3[1], G[q][0] * col3[0]));
                         const float diff = Gc - GS[q];
-    #pragma unroll
+#pragma unroll
                         for (int ch = 0; ch < 3; ch++) gc[ch] = fmaf(G[q][ch], wgt, gc[ch]);
                         GS[q] = STORED ? (valid ? fmaf(alpha, diff, GS[q]) : GS[q]) : fmaf(alpha, diff, GS[q]);
                         // dL/dpower; zero where alpha is clamped at 0.99
@@ -474,15 +457,6 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
                         if (++npend == kPend) flush();
                     }
                 }
-                if (GSP_BWD_PREFETCH) {
-    #pragma unroll
-                    for (int u = 0; u < kBwdUnroll; u++) {
-                        es[u] = es_n[u];
-                        et[u] = et_n[u];
-                        ew[u] = ew_n[u];
-                        em[u] = em_n[u];
-                    }
-                }
             }
         };
         if (!STORED && plain_batch) walk(std::true_type{});
@@ -491,6 +465,15 @@ __global__ __launch_bounds__(kRasterThreads) __attribute__((amdgpu_waves_per_eu(
     }
     if (npend > 0) flush();
 }
+
+// Launches of more tiles than this take the MANY shape: -5 % over 4 views of
+// 1008 x 756 and 1M splats (764 -> 730 us), -5 % over 8 views of three sizes
+// (955 -> 905 us), and of whole pose steps -1.7 % for 5376 tiles (8 of 480 x
+// 336), -1.6 % for 4800, -0.8 % for 3600, within 1 % either way for 6048.  Fewer
+// tiles lose: +2 % for 3024 (a step at 1008 x 756), +3 % for 1200, +8 % of the
+// kernel at 128 x 128, and +5 to 8 % where few tiles have lists so long that
+// their last chunks run alone (8 views of 320 x 240 with 1M splats).
+constexpr int kManyTiles = 4096;
 
 hipError_t launch_raster_bwd(const ViewsK &views, const Layout &L, char *ws, const uint32_t *vals,
                              bool want_opacity, hipStream_t s) {
@@ -518,12 +501,10 @@ hipError_t launch_raster_bwd(const ViewsK &views, const Layout &L, char *ws, con
     // forward's state, so repeated backwards of one forward agree on it.
     // one workgroup per possible work item; those past the
     // item count of this call exit at once
-    if (want_opacity)
-        hipLaunchKernelGGL((k_raster_bwd<false, true>), dim3((unsigned)L.max_items),
-                           dim3(kRasterThreads), 0, s, a, views);
-    else
-        hipLaunchKernelGGL((k_raster_bwd<false, false>), dim3((unsigned)L.max_items),
-                           dim3(kRasterThreads), 0, s, a, views);
+    const bool many = L.total_tiles > kManyTiles;
+    auto *kernel = want_opacity ? (many ? k_raster_bwd<false, true, true> : k_raster_bwd<false, true, false>)
+                                : (many ? k_raster_bwd<false, false, true> : k_raster_bwd<false, false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)L.max_items), dim3(kRasterThreads), 0, s, a, views);
     return hipGetLastError();
 }
 
@@ -550,7 +531,7 @@ hipError_t launch_raster_bwd_stored(const ViewsK &views, const Layout &L, char *
     a.lhdr = region<uint32_t>(lw, Q.hdr);
     a.total_tiles = L.total_tiles;
     // one workgroup per tile, in the forward's launch order
-    hipLaunchKernelGGL((k_raster_bwd<true, true>), dim3(L.total_tiles),
+    hipLaunchKernelGGL((k_raster_bwd<true, true, true>), dim3(L.total_tiles),
                        dim3(kRasterThreads), 0, s, a, views);
     return hipGetLastError();
 }

@@ -404,6 +404,32 @@ def test_batched_views_with_and_without_long_lists():
     assert Ms[0] > 1000 * len(_tiles(big)) and Ms[1] < Ms[0] // 10
 
 
+@pytest.mark.parametrize("want", [(), ("opacities",)])
+@pytest.mark.parametrize("opaque", [False, True])
+def test_backward_shapes_give_the_same_bits(want, opaque):
+    """A view's backward alone (1200 tiles, the shape for few) and among four
+    (4800, the shape for many) give the same 2D gradients and pose gradient,
+    with splats that reach the 0.99 clamp and without."""
+    sc, cam, pose = random_case(48, 1, 640, 480, 20000, depth=(1.0, 8.0))
+    if opaque:
+        sc.opacities[:] = S.rng_for(48, 9).uniform(0.9, 0.999, sc.n).astype(np.float32)
+    up = _upstream(48, cam)
+    outs = []
+    for V in (1, 4):
+        g = R.GaussianParams.from_set(sc, DEV)
+        P = torch.tensor(np.stack([pose] * V), device=DEV, dtype=torch.float32)
+        rast = R.Rasterizer(0)
+        rast.forward(g, [cam] * V, P)
+        dl = torch.tensor(np.concatenate([up.ravel()] * V), device=DEV)
+        gr = rast.backward(g, [cam] * V, P, dl, want=want, pose=True)
+        g2 = rast.inspect(g, [cam] * V, "grad2d").cpu().numpy().reshape(V, -1, 9)
+        outs.append((gr["pose"].cpu().numpy(), g2))
+    (p1, a1), (p4, a4) = outs
+    assert np.any(a1 != 0)
+    for v in range(4):
+        assert np.array_equal(p4[v], p1[0]) and np.array_equal(a4[v], a1[0])
+
+
 def test_pose_gradient_without_opacity_sum_is_bit_identical():
     """A backward that wants no opacity gradient reduces eight sums per
     entry instead of nine; every other 2D gradient component, and the pose
