@@ -144,6 +144,44 @@ __device__ __forceinline__ void wave_sum8_rows(const float v[8], float &a, float
     b = pair_sum16(pair_sum32(v[4], v[5]), pair_sum32(v[6], v[7]));
 }
 
+// The same steps on doubles, then the sums over each row: six sums over the
+// wave, each the value wave_sum gives (its butterfly adds the same pairs in the
+// same order, and a row that repeats with period 2 k reads lane ^ k by a
+// rotation of k).  a rows 0..3 = v0, v2, v1, v3; b rows 0, 1 = v4, rows 2, 3 = v5.
+// 46 VALU operations, where six wave_sum's take 72 LDS permutations in a chain
+// of six.
+template <bool B32>
+__device__ __forceinline__ double pair_sum_f64(double a, double b) {
+    const uint32_t al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+    const auto lo = B32 ? __builtin_amdgcn_permlane32_swap(al, bl, false, false)
+                        : __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+    const auto hi = B32 ? __builtin_amdgcn_permlane32_swap(ah, bh, false, false)
+                        : __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+
+template <int K>   // x + x rotated by K lanes within each row
+__device__ __forceinline__ double row_ror_add(double x) {
+    constexpr int kRor = 0x120 + K;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kRor, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kRor, 0xF, 0xF, true);
+    return x + __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ void wave_sum6(const double v[6], double &a, double &b) {
+    const double w = pair_sum_f64<true>(v[4], v[5]);
+    a = pair_sum_f64<false>(pair_sum_f64<true>(v[0], v[1]), pair_sum_f64<true>(v[2], v[3]));
+    b = pair_sum_f64<false>(w, w);
+    a = row_ror_add<8>(a);
+    b = row_ror_add<8>(b);
+    a = row_ror_add<4>(a);
+    b = row_ror_add<4>(b);
+    a = row_ror_add<2>(a);
+    b = row_ror_add<2>(b);
+    a = row_ror_add<1>(a);
+    b = row_ror_add<1>(b);
+}
+
 // Row of the 16-lane row partials that hold value k (register k >> 2 for
 // k < 8, register 2 for k = 8).
 __host__ __device__ constexpr int sum9_row(int k) {
