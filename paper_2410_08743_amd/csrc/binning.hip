@@ -20,8 +20,8 @@
 // A radix sort by tile id (scan, emission, two passes of three kernels, ranges
 // and launch order: eleven launches that wrote and read every entry three
 // times) took 66 us at 1.5M instances in one 1008 x 756 view, 414 us at 15.4M
-// in four and 657 us at 22M in eight views; the three kernels here take 8.5 +
-// 5.0 + 17.0, 25 + 7 + 121 and 47 + 8 + 220 us.  The first is bound by latency
+// in four and 657 us at 22M in eight views; the three kernels here take 7.0 +
+// 5.0 + 16.3, 25 + 6 + 117 and 45 + 8 + 213 us.  The first is bound by latency
 // and its row atomics, the last by the LDS atomic, the depth's gather and the
 // scattered store that each entry takes.
 #include "block_ops.h"
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kBinCountThreads) void k_bin_count(BinArgs a, Views
             const int x = x0 + lane;
             const int v = run + wave_inclusive_scan(x < cols ? diff[y * cols + x] : 0);
             if (x < cols) out[y * cols + x] = (uint32_t)v;
-            run = __shfl(v, kWave - 1, kWave);
+            run = wave_lane(v, kWave - 1);
         }
     }
     if (w.x0 == 0 && w.y0 == 0) {   // the view's first window
@@ -308,7 +308,7 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
                 const unsigned long long x = g < a.groups && !ovf ? a.gsum[g] : 0ull;
                 const unsigned long long inc = wave_inclusive_scan(x);
                 s.gstart[g0 + lane] = run + inc - x;
-                run += __shfl(inc, kWave - 1, kWave);
+                run += wave_lane(inc, kWave - 1);
             }
             if (lane == 0) s.carry = run;
         }
@@ -367,7 +367,7 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
         const uint32_t wfull = wave_sum(full);
         uint32_t wb = 0;
         if (lane == 0 && wfull > 0) wb = atomicAdd(&s.base[1][kFull], wfull);
-        wb = __shfl(wb, 0, kWave);   // the wave's first full-chunk item
+        wb = wave_lane(wb, 0);   // the wave's first full-chunk item
         const unsigned long long below = (1ull << lane) - 1ull;
 #pragma unroll
         for (int r = 0; r < kOrderRounds; r++) {

@@ -1,6 +1,8 @@
 // block_ops.h -- wavefront (64 lanes) and block reductions and scans used by
-// the gfx950 kernels.  Lane exchange goes through __shfl_* (ds_bpermute /
-// DPP); block-level steps go through LDS.
+// the gfx950 kernels.  Lanes exchange values in the VALU (v_permlane32_swap,
+// v_permlane16_swap and DPP moves), each step a few cycles instead of an LDS
+// round trip (ds_bpermute); block-level steps go through LDS.  All lanes of the
+// wavefront must be active.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -14,33 +16,86 @@ constexpr int kWave = 64;
 // (no round trip of the predicate through a vector register).
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
+// A 4- or 8-byte value through a 32-bit lane exchange.
+template <typename T, typename F>
+__device__ __forceinline__ T by_words(T v, F exchange) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "whole registers");
+    if constexpr (sizeof(T) == 4) {
+        return __builtin_bit_cast(T, exchange(__builtin_bit_cast(uint32_t, v)));
+    } else {
+        const uint64_t x = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = exchange((uint32_t)x), hi = exchange((uint32_t)(x >> 32));
+        return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+    }
+}
+
+// v of one lane (the same in all lanes).
+template <typename T>
+__device__ __forceinline__ T wave_lane(T v, int lane) {
+    return by_words(v, [=](uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, lane); });
+}
+
+// v moved by a DPP control within the rows of 16 lanes; lanes without a source
+// (and rows not in ROWS) get zero.
+template <int CTRL, int ROWS = 0xF, typename T>
+__device__ __forceinline__ T dpp_move(T v) {
+    return by_words(v, [](uint32_t x) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, true);
+    });
+}
+constexpr int kDppRowShr = 0x110, kDppRowRor = 0x120;   // + lanes
+constexpr int kDppRowBcast15 = 0x142;   // lane 15 of each row to the next row
+constexpr int kDppRowBcast31 = 0x143;   // lane 31 to rows 2 and 3
+
+// The values of lanes l < 32 (WHICH 0) or l >= 32 (WHICH 1) for both l and
+// l ^ 32, and the same for 16 within halves: op(WHICH 0, WHICH 1) combines
+// every lane with its partner.
+template <int WHICH, typename T>
+__device__ __forceinline__ T half_of_pair32(T v) {
+    return by_words(v, [](uint32_t x) { return (uint32_t)__builtin_amdgcn_permlane32_swap(x, x, false, false)[WHICH]; });
+}
+template <int WHICH, typename T>
+__device__ __forceinline__ T half_of_pair16(T v) {
+    return by_words(v, [](uint32_t x) { return (uint32_t)__builtin_amdgcn_permlane16_swap(x, x, false, false)[WHICH]; });
+}
+
+// v of all lanes combined by a commutative op, in the pairs of a butterfly over
+// lane ^ 32, 16, 8, 4, 2, 1 (after step k the row repeats with period k, so
+// that a rotation by k / 2 reads lane ^ k / 2).
+template <typename T, typename Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op) {
+    v = op(half_of_pair32<0>(v), half_of_pair32<1>(v));
+    v = op(half_of_pair16<0>(v), half_of_pair16<1>(v));
+    v = op(v, dpp_move<kDppRowRor + 8>(v));
+    v = op(v, dpp_move<kDppRowRor + 4>(v));
+    v = op(v, dpp_move<kDppRowRor + 2>(v));
+    return op(v, dpp_move<kDppRowRor + 1>(v));
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    return wave_reduce(v, [](T a, T b) { return a + b; });
 }
-
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        T o = __shfl_xor(v, off, kWave);
-        v = o > v ? o : v;
-    }
-    return v;
+    return wave_reduce(v, [](T a, T b) { return a > b ? a : b; });
+}
+template <typename T>
+__device__ __forceinline__ T wave_min(T v) {
+    return wave_reduce(v, [](T a, T b) { return a < b ? a : b; });
 }
 
-// Inclusive scan across the wave.
+// Inclusive scan of integers across the wave: within the rows, then the totals
+// of the rows in front.
 template <typename T>
 __device__ __forceinline__ T wave_inclusive_scan(T v) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        T o = __shfl_up(v, off, kWave);
-        if (lane >= off) v += o;
-    }
-    return v;
+    static_assert(T(1) / T(2) == T(0), "whole numbers: the sums are grouped by rows");
+    v += dpp_move<kDppRowShr + 1>(v);
+    v += dpp_move<kDppRowShr + 2>(v);
+    v += dpp_move<kDppRowShr + 4>(v);
+    v += dpp_move<kDppRowShr + 8>(v);
+    v += dpp_move<kDppRowBcast15, 0xA>(v);
+    return v + dpp_move<kDppRowBcast31, 0xC>(v);
 }
 
 // Exclusive scan over a block of NT threads; returns the block total in *total.
@@ -145,11 +200,9 @@ __device__ __forceinline__ void wave_sum8_rows(const float v[8], float &a, float
 }
 
 // The same steps on doubles, then the sums over each row: six sums over the
-// wave, each the value wave_sum gives (its butterfly adds the same pairs in the
-// same order, and a row that repeats with period 2 k reads lane ^ k by a
-// rotation of k).  a rows 0..3 = v0, v2, v1, v3; b rows 0, 1 = v4, rows 2, 3 = v5.
-// 46 VALU operations, where six wave_sum's take 72 LDS permutations in a chain
-// of six.
+// wave, each the value wave_sum gives (the same pairs in the same order), in
+// half its operations.  a rows 0..3 = v0, v2, v1, v3; b rows 0, 1 = v4, rows 2,
+// 3 = v5.
 template <bool B32>
 __device__ __forceinline__ double pair_sum_f64(double a, double b) {
     const uint32_t al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
@@ -160,26 +213,18 @@ __device__ __forceinline__ double pair_sum_f64(double a, double b) {
     return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
 }
 
-template <int K>   // x + x rotated by K lanes within each row
-__device__ __forceinline__ double row_ror_add(double x) {
-    constexpr int kRor = 0x120 + K;
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), kRor, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), kRor, 0xF, 0xF, true);
-    return x + __hiloint2double(hi, lo);
-}
-
 __device__ __forceinline__ void wave_sum6(const double v[6], double &a, double &b) {
     const double w = pair_sum_f64<true>(v[4], v[5]);
     a = pair_sum_f64<false>(pair_sum_f64<true>(v[0], v[1]), pair_sum_f64<true>(v[2], v[3]));
     b = pair_sum_f64<false>(w, w);
-    a = row_ror_add<8>(a);
-    b = row_ror_add<8>(b);
-    a = row_ror_add<4>(a);
-    b = row_ror_add<4>(b);
-    a = row_ror_add<2>(a);
-    b = row_ror_add<2>(b);
-    a = row_ror_add<1>(a);
-    b = row_ror_add<1>(b);
+    a += dpp_move<kDppRowRor + 8>(a);
+    b += dpp_move<kDppRowRor + 8>(b);
+    a += dpp_move<kDppRowRor + 4>(a);
+    b += dpp_move<kDppRowRor + 4>(b);
+    a += dpp_move<kDppRowRor + 2>(a);
+    b += dpp_move<kDppRowRor + 2>(b);
+    a += dpp_move<kDppRowRor + 1>(a);
+    b += dpp_move<kDppRowRor + 1>(b);
 }
 
 // Row of the 16-lane row partials that hold value k (register k >> 2 for

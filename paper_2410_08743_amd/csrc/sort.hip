@@ -21,10 +21,10 @@
 // each).  An LSD radix sort in one wavefront's LDS took some 25 LDS operations
 // per entry in a chain of ranking rounds; this takes about 10, none waiting for
 // another, and a workgroup of four or eight wavefronts shares a run: 23.2 ->
-// 14.4 us at 1.5M instances in 3024 lists of 500 (pose step, 1008 x 756; 4.5 us
-// more where the kernel of the longer runs finds none), 168 -> 80 + 4.5 us at
-// 15.4M in 12096 lists of 1100-1800 (joint step), 79 -> 14.3 + 22.0 us for a
-// room with lists of up to 2400, and 706 -> 86 + 78 us for 22M in lists of up
+// 12.1 us at 1.5M instances in 3024 lists of 500 (pose step, 1008 x 756; 4.5 us
+// more where the kernel of the longer runs finds none), 168 -> 69 + 4.5 us at
+// 15.4M in 12096 lists of 1100-1800 (joint step), 79 -> 12.4 + 20.2 us for a
+// room with lists of up to 2400, and 706 -> 80 + 75 us for 22M in lists of up
 // to 6700 (eight views of three sizes), whose longer half one wavefront each
 // had sorted in global memory.
 #include "block_ops.h"
@@ -46,18 +46,6 @@ struct TileDepthArgs {
     const uint32_t *counters;
     int short_cap;              // longest run of the kernel over all tiles
 };
-
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, off, kWave));
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off, kWave));
-    return v;
-}
 
 // LDS of a workgroup of THREADS threads, ROUNDS entries each at most.
 template <int THREADS, int ROUNDS>
@@ -83,8 +71,8 @@ struct TdShared {
 template <int THREADS, int ROUNDS>
 __device__ __forceinline__ void td_reduce(TdShared<THREADS, ROUNDS> &sh, int t, uint32_t &lo, uint32_t &hi) {
     const int w = t / kWave;
-    lo = wave_min_u32(lo);
-    hi = wave_max_u32(hi);
+    lo = wave_min(lo);
+    hi = wave_max(hi);
     if (t % kWave == 0) {
         sh.part[2 * w] = lo;
         sh.part[2 * w + 1] = hi;
@@ -111,7 +99,7 @@ __device__ __forceinline__ uint32_t td_scan(TdShared<THREADS, ROUNDS> &sh, int t
         s += c[j].x + c[j].y + c[j].z + c[j].w;
     }
     const uint32_t inc = wave_inclusive_scan(s);
-    big = wave_max_u32(big);
+    big = wave_max(big);
     const int w = t / kWave;
     if (t % kWave == kWave - 1) {
         sh.part[2 * w] = inc;
