@@ -52,6 +52,14 @@ def test_loss_rgb_matches_oracle(W, H):
     assert np.max(np.abs(got - ref_grad)) <= 1e-4 * np.max(np.abs(ref_grad))
 
 
+# tiles of 64 x 16 whose halo of 5 pixels ends just inside the image's edge, on it
+# and past it (132..134 columns, 36..38 rows), at the bounds of the test above
+@pytest.mark.parametrize("W", [132, 133, 134])
+@pytest.mark.parametrize("H", [36, 37, 38])
+def test_loss_rgb_at_the_edge_of_inner_tiles(W, H):
+    test_loss_rgb_matches_oracle(W, H)
+
+
 def test_loss_rgb_identical_images_and_beta_limits():
     x, _ = _images(7, 70, 33)
     t = torch.tensor(x.ravel(), device=DEV)
