@@ -62,16 +62,20 @@ __device__ __forceinline__ void rot_vjp(double w, double x, double y, double z, 
 }
 
 // 2D gradient of each splat: the sum of its instance slots in slot order (one
-// running sum from zero, first instance to last, and within an instance its
-// rasterizer parts in order).  One block per work window: the
-// window's slots form one contiguous range, which the block copies into LDS
-// with all of each thread's loads in flight at once; the (splat, component)
-// pairs are then spread over the threads, nine neighbouring threads per
-// splat.  Slots past the first kWindow of the range -- the tail of a long last
-// splat -- are read from global memory.  A slot the backward rasterizer did
-// not write (flag 0: no pixel of that strip blended the entry) counts as zero.
-constexpr int kSlotFloats = 9 * kSplitBwd;   // one 9-float slot per backward part
-constexpr int kSlotPerThread = kWindow * kSlotFloats / kWindowThreads;
+// running sum from zero, first instance to last).  One block per work window:
+// the window's slots form one contiguous range, which the block copies into
+// LDS with all of each thread's loads in flight at once; the (splat,
+// component) pairs are then spread over the threads, nine neighbouring
+// threads per splat.  Slots past the first kWindow of the range -- the tail of
+// a long last splat -- are read from global memory.  A slot the backward
+// rasterizer did not write (flag 0: no pixel of the tile blended the entry)
+// counts as zero and is not read: at the benchmark view that is 59 % of them,
+// mostly whole splats behind others (18.2 -> 16.3 us there; 144 -> 134 us at
+// 15.4M slots and 4M splats, 560 + 140 MB if all were read).  Bound by the latency
+// of a window's chain of loads and by the many small items; windows of 256
+// or 1024 slots, one or four slots per thread, and a copy in aligned 16-byte
+// vectors (153 us) all measured slower.
+constexpr int kSlotPerThread = kWindow * 9 / kWindowThreads;
 
 __global__ __launch_bounds__(kWindowThreads) void k_slot_reduce(const uint32_t *offk,
                                                                 const uint2 *wstart,
@@ -79,8 +83,8 @@ __global__ __launch_bounds__(kWindowThreads) void k_slot_reduce(const uint32_t *
                                                                 const float *slots,
                                                                 const uint8_t *flags,
                                                                 float *grad2d, int vn) {
-    __shared__ float s_sl[kWindow * kSlotFloats];
-    __shared__ uint8_t s_fl[kWindow * kSplitBwd];
+    __shared__ float s_sl[kWindow * 9];
+    __shared__ uint8_t s_fl[kWindow];
     __shared__ uint32_t s_off[kWindow + 1];
     const int b = blockIdx.x;
     if (counters[kCntOverflow] != 0u) {
@@ -96,19 +100,18 @@ __global__ __launch_bounds__(kWindowThreads) void k_slot_reduce(const uint32_t *
     const uint32_t kb = w0.x, ke = w1.x;
     const int nk = (int)(ke - kb);   // at most kWindow
     const uint32_t e0 = w0.y, ne = w1.y - e0;
-    const uint32_t nf = (uint32_t)kSlotFloats * min(ne, (uint32_t)kWindow);
-    const float *src = slots + kSlotFloats * (size_t)e0;
-    const uint8_t *fsrc = flags + kSplitBwd * (size_t)e0;
-    const uint32_t nfl = (uint32_t)kSplitBwd * min(ne, (uint32_t)kWindow);
-    for (uint32_t f = threadIdx.x; f < nfl; f += kWindowThreads) s_fl[f] = fsrc[f];
+    const float *src = slots + 9 * (size_t)e0;
+    const uint8_t *fsrc = flags + e0;
+    for (uint32_t e = threadIdx.x; e < kWindow; e += kWindowThreads) s_fl[e] = e < ne ? fsrc[e] : (uint8_t)0;
+    for (int j = threadIdx.x; j < nk; j += kWindowThreads) s_off[j] = offk[kb + j] - e0;
+    if (threadIdx.x == 0) s_off[nk] = ne;
+    __syncthreads();
     float tmp[kSlotPerThread];
 #pragma unroll
     for (int r = 0; r < kSlotPerThread; r++) {
         const uint32_t f = (uint32_t)(r * kWindowThreads + threadIdx.x);
-        tmp[r] = f < nf ? src[f] : 0.f;
+        tmp[r] = s_fl[f / 9] ? src[f] : 0.f;
     }
-    for (int j = threadIdx.x; j < nk; j += kWindowThreads) s_off[j] = offk[kb + j] - e0;
-    if (threadIdx.x == 0) s_off[nk] = ne;
 #pragma unroll
     for (int r = 0; r < kSlotPerThread; r++) s_sl[r * kWindowThreads + threadIdx.x] = tmp[r];
     __syncthreads();
@@ -121,51 +124,30 @@ __global__ __launch_bounds__(kWindowThreads) void k_slot_reduce(const uint32_t *
         // slots in LDS, kLdsBatch reads in flight, added in slot order
         constexpr int kLdsBatch = 4;
         for (; e + kLdsBatch <= mid; e += kLdsBatch) {
-            float v[kLdsBatch][kSplitBwd];
-            bool fl[kLdsBatch][kSplitBwd];
+            float v[kLdsBatch];
 #pragma unroll
-            for (int u = 0; u < kLdsBatch; u++)
+            for (int u = 0; u < kLdsBatch; u++) v[u] = s_sl[9 * (e + u) + c];
 #pragma unroll
-                for (int p = 0; p < kSplitBwd; p++) {
-                    v[u][p] = s_sl[kSlotFloats * (e + u) + 9 * p + c];
-                    fl[u][p] = s_fl[kSplitBwd * (e + u) + p] != 0;
-                }
-#pragma unroll
-            for (int u = 0; u < kLdsBatch; u++)
-#pragma unroll
-                for (int p = 0; p < kSplitBwd; p++) d += fl[u][p] ? v[u][p] : 0.f;
+            for (int u = 0; u < kLdsBatch; u++) d += v[u];
         }
-        for (; e < mid; e++) {
-#pragma unroll
-            for (int p = 0; p < kSplitBwd; p++) {
-                const float v = s_sl[kSlotFloats * e + 9 * p + c];
-                d += s_fl[kSplitBwd * e + p] ? v : 0.f;
-            }
-        }
+        for (; e < mid; e++) d += s_sl[9 * e + c];
         // the tail past the window, from global memory: the loads of
         // kTailBatch slots are issued together, then added in slot order
         constexpr int kTailBatch = 8;
         for (; e + kTailBatch <= hi; e += kTailBatch) {
-            float v[kTailBatch][kSplitBwd];
-            uint8_t fl[kTailBatch][kSplitBwd];
+            float v[kTailBatch];
+            uint8_t fl[kTailBatch];
 #pragma unroll
-            for (int u = 0; u < kTailBatch; u++)
+            for (int u = 0; u < kTailBatch; u++) {
+                v[u] = src[9 * (size_t)(e + u) + c];
+                fl[u] = fsrc[e + u];
+            }
 #pragma unroll
-                for (int p = 0; p < kSplitBwd; p++) {
-                    v[u][p] = src[kSlotFloats * (size_t)(e + u) + 9 * p + c];
-                    fl[u][p] = fsrc[kSplitBwd * (size_t)(e + u) + p];
-                }
-#pragma unroll
-            for (int u = 0; u < kTailBatch; u++)
-#pragma unroll
-                for (int p = 0; p < kSplitBwd; p++) d += fl[u][p] ? v[u][p] : 0.f;
+            for (int u = 0; u < kTailBatch; u++) d += fl[u] ? v[u] : 0.f;
         }
         for (; e < hi; e++) {
-#pragma unroll
-            for (int p = 0; p < kSplitBwd; p++) {
-                const float v = src[kSlotFloats * (size_t)e + 9 * p + c];
-                d += fsrc[kSplitBwd * (size_t)e + p] ? v : 0.f;
-            }
+            const float v = src[9 * (size_t)e + c];
+            d += fsrc[e] ? v : 0.f;
         }
         grad2d[9 * ((size_t)kb + j) + c] = d;
     }
