@@ -305,14 +305,25 @@ __global__ __launch_bounds__(256) void k_masked_l1(MaskViewsK a, double *partial
     float *grad = a.grad[v];
     const int64_t base = ((int64_t)blockIdx.x - a.blk_base[v]) * kMaskItems;
     double s = 0.0;
-#pragma unroll 4
-    for (int r = 0; r < kMaskItems / 256; r++) {
+    // every load of the thread before its first store, and the pixel by a
+    // comparison (e < 3 P) instead of a 64-bit
+    // remainder (14.8 -> 11.8 us at 1200 x 680)
+    constexpr int kPer = kMaskItems / 256;
+    float d[kPer], al[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; r++) {
+        const int64_t e = base + (int64_t)r * 256 + threadIdx.x;
+        const int64_t pix = e - (e >= 2 * P ? 2 * P : (e >= P ? P : 0));
+        al[r] = e < count ? alpha[pix] : 0.f;
+        d[r] = e < count ? pred[e] - target[e] : 0.f;
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; r++) {
         const int64_t e = base + (int64_t)r * 256 + threadIdx.x;
         if (e < count) {
-            const bool m = (double)alpha[e % P] > 0.99;
-            const float d = pred[e] - target[e];
-            grad[e] = m ? (d > 0.f ? 1.f : (d < 0.f ? -1.f : 0.f)) : 0.f;
-            s += m ? fabs((double)d) : 0.0;
+            const bool m = (double)al[r] > 0.99;
+            grad[e] = m ? (d[r] > 0.f ? 1.f : (d[r] < 0.f ? -1.f : 0.f)) : 0.f;
+            s += m ? fabs((double)d[r]) : 0.0;
         }
     }
     if (partial) {
