@@ -119,7 +119,8 @@ __global__ __launch_bounds__(64) void k_pose_adam(int V, float *poses, const flo
 #pragma unroll
     for (int e = 0; e < 12; e++) T0[e] = poses[12 * i + e];
     if (ovf != 0u) return;
-    pose_adam_apply(i, k, gv, m0, v0, T0, poses, m, v, steps, p);
+    pose_adam_apply(i, k, pose_adam_lr(k, p), pose_adam_correction(p.beta1, k), pose_adam_correction(p.beta2, k), gv,
+                    m0, v0, T0, poses, m, v, steps, p);
 }
 
 hipError_t launch_pose_adam(int V, float *poses, const float *dpose, float *m, float *v,

@@ -88,20 +88,27 @@ __device__ inline void tso3_step(const double dc[3], const double phi[3], float 
     }
 }
 
-// One Adam step of view i from its loaded state: k is the step's count
-// (steps[i] + 1), gv the pose gradient, m0 / v0 the moments and T0 the pose
-// (updated in place, then stored); writes steps[i], m, v and poses.
-__device__ inline void pose_adam_apply(int i, int k, double gv[6], const double m0[6],
-                                       const double v0[6], float T0[12], float *poses, float *m,
-                                       float *v, int32_t *steps, const gsp_adam_params &p) {
-    steps[i] = k;
+// What a step takes from its count k alone: the learning rate, and the bias
+// corrections of the two moments.
+__device__ inline double pose_adam_lr(int k, const gsp_adam_params &p) {
     double lr = p.lr_start;
     if (p.total_steps > 1) {
         const double frac = fmin((double)(k - 1), (double)(p.total_steps - 1)) / (p.total_steps - 1);
         lr = p.lr_end + 0.5 * ((double)p.lr_start - p.lr_end) * (1.0 + cos(M_PI * frac));
     }
+    return lr;
+}
+__device__ inline double pose_adam_correction(float beta, int k) { return 1.0 - pow((double)beta, (double)k); }
+
+// One Adam step of view i from its loaded state: k is the step's count
+// (steps[i] + 1) with lr, c1 and c2 from it, gv the pose gradient, m0 / v0 the
+// moments and T0 the pose (updated in place, then stored); writes steps[i], m,
+// v and poses.
+__device__ inline void pose_adam_apply(int i, int k, double lr, double c1, double c2, double gv[6],
+                                       const double m0[6], const double v0[6], float T0[12], float *poses,
+                                       float *m, float *v, int32_t *steps, const gsp_adam_params &p) {
+    steps[i] = k;
     const double b1 = p.beta1, b2 = p.beta2;
-    const double c1 = 1.0 - pow(b1, (double)k), c2 = 1.0 - pow(b2, (double)k);
     const bool tso3 = p.parametrization == GSP_POSE_T_SO3;
     if (tso3) {   // dL/dc = -R^T dL/drho; the rotation part is unchanged
         const float *T = T0;

@@ -491,7 +491,10 @@ __global__ __launch_bounds__(kPoseReduceBlock) __attribute__((amdgpu_waves_per_e
 // dL/dtau of each view: the sum of the chain-rule kernel's per-wavefront
 // FP64 partials in a fixed order.  One 256-thread block per view; each
 // thread issues all loads of its rows before the first add (one round of
-// memory latency per kPoseFinalThreads x kPoseFinalPer rows).
+// memory latency per kPoseFinalThreads x kPoseFinalPer rows), 16 bytes each.
+// Bound by that latency, the rows' lines (one CU reads them all) and the serial
+// tail of the step: 9.7 -> 8.6 us at 3125 rows, 24.8 -> 22.6 us for 8 views of
+// 15625 (reading whole lines and turning them in LDS: 10.2 and 28.6 us).
 constexpr int kPoseFinalThreads = 256;
 constexpr int kPoseFinalPer = 16;   // partial rows per thread held in flight
 
@@ -502,16 +505,18 @@ __global__ __launch_bounds__(kPoseFinalThreads) void k_pose_final(const double *
     __shared__ float dp6[6];
     const int v = blockIdx.x, t = threadIdx.x;
     // with the Adam step: its state, read before the rows (one round of
-    // memory latency for both)
+    // memory latency for both), and what follows from the step count alone,
+    // computed by one lane of each other wave while the rows are on their way
+    __shared__ double sched[3];
     uint32_t ovf = 0u;
     int k = 0;
     double m0[6] = {0, 0, 0, 0, 0, 0}, v0[6] = {0, 0, 0, 0, 0, 0};
     float T0[12];
 #pragma unroll
     for (int e = 0; e < 12; e++) T0[e] = 0.f;
+    if (adam && t % kWave == 0) k = ad.steps[v] + 1;
     if (adam && t == 0) {
         ovf = ad.guard[kCntOverflow];
-        k = ad.steps[v] + 1;
 #pragma unroll
         for (int e = 0; e < 6; e++) {
             m0[e] = ad.m[6 * v + e];
@@ -520,7 +525,7 @@ __global__ __launch_bounds__(kPoseFinalThreads) void k_pose_final(const double *
 #pragma unroll
         for (int e = 0; e < 12; e++) T0[e] = ad.poses[12 * v + e];
     }
-    const double *src = posepart + (size_t)v * nrows * 6;
+    const double2 *src = reinterpret_cast<const double2 *>(posepart + (size_t)v * nrows * 6);
     double s[6] = {0, 0, 0, 0, 0, 0};
     for (int b0 = 0; b0 < nrows; b0 += kPoseFinalThreads * kPoseFinalPer) {
         double x[kPoseFinalPer][6];
@@ -528,8 +533,16 @@ __global__ __launch_bounds__(kPoseFinalThreads) void k_pose_final(const double *
         for (int r = 0; r < kPoseFinalPer; r++) {
             const int b = b0 + r * kPoseFinalThreads + t;
 #pragma unroll
-            for (int c = 0; c < 6; c++) x[r][c] = b < nrows ? src[(size_t)b * 6 + c] : 0.0;
+            for (int c = 0; c < 6; c += 2) {
+                const double2 y = b < nrows ? src[(size_t)b * 3 + c / 2] : make_double2(0.0, 0.0);
+                x[r][c] = y.x;
+                x[r][c + 1] = y.y;
+            }
         }
+        if (b0 == 0 && adam && t % kWave == 0 && t > 0)
+            sched[t / kWave - 1] = t == kWave       ? pose_adam_lr(k, ad.p)
+                                   : t == 2 * kWave ? pose_adam_correction(ad.p.beta1, k)
+                                                    : pose_adam_correction(ad.p.beta2, k);
 #pragma unroll
         for (int r = 0; r < kPoseFinalPer; r++)
 #pragma unroll
@@ -563,7 +576,7 @@ __global__ __launch_bounds__(kPoseFinalThreads) void k_pose_final(const double *
             double gv[6];
 #pragma unroll
             for (int e = 0; e < 6; e++) gv[e] = dp6[e];
-            pose_adam_apply(v, k, gv, m0, v0, T0, ad.poses, ad.m, ad.v, ad.steps, ad.p);
+            pose_adam_apply(v, k, sched[0], sched[1], sched[2], gv, m0, v0, T0, ad.poses, ad.m, ad.v, ad.steps, ad.p);
         }
     }
 }
