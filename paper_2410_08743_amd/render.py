@@ -24,7 +24,10 @@ def _ptr(t):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle alone: 0.4 us where making a Stream object takes 3
+    # (four times a step through autograd, whose host path bounds small scenes:
+    # 328 -> 297 us for 20k splats at 589 x 440)
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 _contexts = {}
