@@ -146,11 +146,15 @@ __device__ __forceinline__ float outside_bound(const UnprojK &a, const float4 &q
 // step rounds monotonically, so it never exceeds that of a point inside),
 // and the wave tests their blocks, 64 pixels at a time.
 // Bound by latency: 51k points (1200 x 680 at stride 4, 1 % depth noise, 0.2 %
-// holes) took 2.03 ms when all pairs were tested from LDS, 28 us now.
+// holes) took 2.03 ms when all pairs were tested from LDS, 25 us now.  A block
+// has four times the wavefronts that its points take, for the second part: the
+// depth of a render leaves it a third of the points, and 200 blocks of four
+// wavefronts took 441 us with it where these take some 140 (28 us above).
 constexpr int kKnnR = 3;
+constexpr int kKnnThreads = 1024;   // one point for each of the first kGridThreads
 constexpr int kKnnLW = kGridW + 2 * kKnnR, kKnnLH = kGridH + 2 * kKnnR;
 
-__global__ __launch_bounds__(kGridThreads) void k_knn3(UnprojK a) {
+__global__ __launch_bounds__(kKnnThreads) void k_knn3(UnprojK a) {
     __shared__ float4 tile[kKnnLH][kKnnLW];
     __shared__ int s_count;                   // points left to the second part
     __shared__ uint16_t s_open[kGridThreads]; // and their threads
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(kGridThreads) void k_knn3(UnprojK a) {
     __shared__ Near3 s_found[kGridThreads];
     const int i0 = blockIdx.x * kGridW, j0 = blockIdx.y * kGridH;
     if (threadIdx.x == 0) s_count = 0;
-    for (int e = threadIdx.x; e < kKnnLW * kKnnLH; e += kGridThreads) {
+    for (int e = threadIdx.x; e < kKnnLW * kKnnLH; e += kKnnThreads) {
         const int y = e / kKnnLW, x = e - y * kKnnLW;
         const int i = i0 + x - kKnnR, j = j0 + y - kKnnR;
         const bool in = i >= 0 && i < a.nx && j >= 0 && j < a.ny;
@@ -167,16 +171,18 @@ __global__ __launch_bounds__(kGridThreads) void k_knn3(UnprojK a) {
     __syncthreads();
     const int tx = threadIdx.x % kGridW, ty = threadIdx.x / kGridW;
     const int i = i0 + tx, j = j0 + ty;
-    const bool valid = i < a.nx && j < a.ny;
-    const float4 q = tile[ty + kKnnR][tx + kKnnR];
+    const bool valid = threadIdx.x < kGridThreads && i < a.nx && j < a.ny;
     Near3 best{INFINITY, INFINITY, INFINITY};
+    bool open = false;
+    if (valid) {
+        const float4 q = tile[ty + kKnnR][tx + kKnnR];
+#pragma unroll 1   // a row's points in flight; all 48 would take more registers than there are
+        for (int dy = -kKnnR; dy <= kKnnR; dy++)
 #pragma unroll
-    for (int dy = -kKnnR; dy <= kKnnR; dy++)
-#pragma unroll
-        for (int dx = -kKnnR; dx <= kKnnR; dx++)
-            if (dx != 0 || dy != 0) best.test(tile[ty + kKnnR + dy][tx + kKnnR + dx], q, true);
-
-    const bool open = valid && !(best.b2 < outside_bound(a, q, i, j, kKnnR));
+            for (int dx = -kKnnR; dx <= kKnnR; dx++)
+                best.test(tile[ty + kKnnR + dy][tx + kKnnR + dx], q, dx != 0 || dy != 0);
+        open = !(best.b2 < outside_bound(a, q, i, j, kKnnR));
+    }
     if (open) {
         const int k = atomicAdd(&s_count, 1);
         s_open[k] = (uint16_t)threadIdx.x;
@@ -185,7 +191,7 @@ __global__ __launch_bounds__(kGridThreads) void k_knn3(UnprojK a) {
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1);
     const int nblk = gridDim.x * gridDim.y;
-    for (int k = threadIdx.x / kWave; k < s_count; k += kGridThreads / kWave) {
+    for (int k = threadIdx.x / kWave; k < s_count; k += kKnnThreads / kWave) {
         const int src = s_open[k];
         const int si = i0 + src % kGridW, sj = j0 + src / kGridW;
         const float4 qs = tile[src / kGridW + kKnnR][src % kGridW + kKnnR];
@@ -210,10 +216,7 @@ __global__ __launch_bounds__(kGridThreads) void k_knn3(UnprojK a) {
 #pragma unroll
             for (int k = 0; k < kGridThreads / kWave; k++)
                 mine.test(p[k], qs, x != si || y0 + k * (kWave / kGridW) != sj);
-            float third = mine.b2;
-#pragma unroll
-            for (int off = kWave / 2; off > 0; off >>= 1) third = fminf(third, __shfl_xor(third, off, kWave));
-            limit = fminf(limit, third);
+            limit = fminf(limit, wave_reduce(mine.b2, [](float x, float y) { return fminf(x, y); }));
         };
         // the nearest block first: its points bring the limit down for a
         // query far from the surface its pixel's neighbours lie on
@@ -282,7 +285,7 @@ hipError_t launch_unproject(const UnprojK &a, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const dim3 grid = grid_blocks(a.nx, a.ny);
     hipLaunchKernelGGL(k_unproject, grid, dim3(kGridThreads), 0, s, a);
-    hipLaunchKernelGGL(k_knn3, grid, dim3(kGridThreads), 0, s, a);
+    hipLaunchKernelGGL(k_knn3, grid, dim3(kKnnThreads), 0, s, a);
     return hipGetLastError();
 }
 
