@@ -9,8 +9,8 @@ pose only, FP32.  The scene, camera and target image are synthetic and
 seeded (they stand in for the paper's LLFF pose-estimation scenes); the
 target is rendered at the ground-truth pose.
 
-A step is one pass of the whole hot path: preprocess, binning, radix sort,
-tile ranges, per-tile depth order, forward rasterizer with the L1 loss
+A step is one pass of the whole hot path: preprocess, binning by counting,
+per-tile depth order, forward rasterizer with the L1 loss
 gradient in its epilogue (gsp_render_fwd_l1), backward rasterizer,
 preprocess-backward with the pose reduction, and the tangent Adam update.
 `--steps K` steps of one pose solve are timed with HIP events on the stream
@@ -261,9 +261,11 @@ def main():
     param_bytes = 4 * (11 + 3 * S3)
     work = {
         "preprocess": ("hbm", (param_bytes + 64) * n),
-        "duplicate": ("hbm", 20 * n + 12 * M),
-        "tile_sort": ("hbm", 16 * M),
-        "ranges": ("hbm", 8 * M + 8 * ((cam.width + 15) // 16) * ((cam.height + 15) // 16)),
+        # counting (rects, tile counts), the lists' lengths, and the scatter (rects,
+        # counts, depths read; offsets, 8-byte entries and slot flags written)
+        "duplicate": ("hbm", 12 * n),
+        "ranges": ("hbm", 8 * ((cam.width + 15) // 16) * ((cam.height + 15) // 16)),
+        "tile_sort": ("hbm", 20 * n + 9 * M + 12 * ((cam.width + 15) // 16) * ((cam.height + 15) // 16)),
         "depth_order": ("hbm", 12 * M),
         "raster_fwd": ("alu", FWD_FLOPS_EVAL * neval + FWD_FLOPS_BLEND * nblend),
         "raster_bwd": ("alu", BWD_FLOPS_EVAL * ncontrib + BWD_FLOPS_BLEND * nblend),
@@ -619,9 +621,9 @@ def joint_section(args, dev):
     tiles = V * ((cam.width + 15) // 16) * ((cam.height + 15) // 16)
     work = {
         "preprocess": ("hbm", pb * n + 64 * V * n),
-        "duplicate": ("hbm", 20 * V * n + 12 * Mj),
-        "tile_sort": ("hbm", 16 * Mj),
-        "ranges": ("hbm", 8 * Mj + 8 * tiles),
+        "duplicate": ("hbm", 12 * V * n),
+        "ranges": ("hbm", 8 * tiles),
+        "tile_sort": ("hbm", 20 * V * n + 9 * Mj + 12 * tiles),
         "depth_order": ("hbm", 12 * Mj),
         "raster_fwd": ("alu", FWD_FLOPS_EVAL * neval + FWD_FLOPS_BLEND * nblend),
         "loss_rgb": ("hbm", 44 * 3 * P * V),

@@ -428,7 +428,7 @@ size_t gsp_loss_masked_l1_scratch_bytes(int32_t V, const gsp_view *views);
  * the conic [[A, B], [B, C]] stored as (A2, B2, C2) = -log2(e) (A/2, B, C/2)),
  * "color" (float4),
  * "rect" (uint16 x0 y0 x1 y1), "depth" (uint32 float bits), "tiles"
- * (uint32 count), "offsets" (uint32 first emission position, i.e. gradient
+ * (uint32 count), "offsets" (uint32 first instance splat by splat, i.e. gradient
  * slot, of each view-Gaussian, in index order),
  * "keys" (uint32 global tile id of each sorted instance; the depth part of
  * the 64-bit key is "depth" of its value), "values" (uint32 sorted),

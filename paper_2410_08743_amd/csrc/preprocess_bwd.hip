@@ -10,7 +10,7 @@
 // Sigma_hat = J R_c Sigma R_c^T J^T) and h = dL/do_c:
 //   dL/drho += g - R_c h,   dL/dphi += mu^c x g + vee(G_W R_c^T).
 //
-// MI355X design: a first kernel walks the instance slots in their emission
+// MI355X design: a first kernel walks the instance slots in their
 // order (visible splats in index order, each splat's slots contiguous), in
 // windows of balanced size, and sums each splat's slots in a fixed order
 // into its 2D gradient.  The chain-rule kernel then runs one thread per
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kWindowThreads) void k_slot_reduce(const uint32_t *
     __shared__ uint32_t s_off[kWindow + 1];
     const int b = blockIdx.x;
     if (counters[kCntOverflow] != 0u) {
-        // no instance was emitted: every 2D gradient is zero
+        // no instance was written: every 2D gradient is zero
         for (size_t f = (size_t)b * kWindowThreads + threadIdx.x; f < 9 * (size_t)vn;
              f += (size_t)gridDim.x * kWindowThreads)
             grad2d[f] = 0.f;
