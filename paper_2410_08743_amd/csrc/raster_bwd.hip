@@ -295,6 +295,7 @@ void k_raster_bwd(BwdArgs a, ViewsK views) {
             gslot != kNoSlot ? band_mask(u, v, g1.x, g1.y, g1.z, g1.w) : 0u;
         const unsigned long long kept = __ballot(mask != 0u);
         const int nk = __popcll(kept);
+        const bool nc_batch = __ballot(mask != 0u && !(g1.w <= kLoNoClamp)) == 0ull;
         const bool plain_batch = __ballot(mask != 0u && !plain_splat(g1.x, g1.y, g1.z, g1.w)) == 0ull;
         if (mask != 0u) {
             const int r = kept_rank(kept);
@@ -315,11 +316,12 @@ void k_raster_bwd(BwdArgs a, ViewsK views) {
             gather(lo - kBatch + lane);
             read_id(lo - 2 * kBatch + lane);
         }
-        // PLAIN: no staged entry of the batch can reach the 0.99 clamp or a
-        // positive power, whose tests then drop out of the walk (same results,
-        // fewer operations)
-        auto walk = [&](auto plain_c) __attribute__((always_inline)) {
-            constexpr bool PLAIN = decltype(plain_c)::value;
+        // NC: no staged entry of the batch can reach the 0.99 clamp; PLAIN: nor a
+        // positive power.  Their tests then drop out of the walk (fewer
+        // operations).  The walk without the clamp keeps its own arithmetic
+        // where the power is tested too: its sums round once less.
+        auto walk = [&](auto nc_c, auto plain_c) __attribute__((always_inline)) {
+            constexpr bool NC = decltype(nc_c)::value, PLAIN = decltype(plain_c)::value;
             for (int j0 = nkr - kUnroll; j0 >= 0; j0 -= kUnroll) {
                 StagedA es[kUnroll];
                 StagedB et[kUnroll];
@@ -378,7 +380,7 @@ void k_raster_bwd(BwdArgs a, ViewsK views) {
                         } else {
                             const float p2 = splat_p2(ct, t.C2, dy);
                             apre = splat_alpha_pre(p2, t.lo);
-                            a0 = PLAIN ? apre : fminf(kAlphaMax, apre);
+                            a0 = NC ? apre : fminf(kAlphaMax, apre);
                             cand = (pos < last[q]) & (PLAIN | (p2 <= 0.f)) & (a0 >= kAlphaMin);
                         }
                         if (__builtin_amdgcn_ballot_w64(cand) == 0ull) continue;
@@ -397,7 +399,7 @@ void k_raster_bwd(BwdArgs a, ViewsK views) {
                             // and the sums (plus 0) exactly as they are.
                             valid = cand;
                             alpha = valid ? a0 : 0.f;
-                            unclamped = PLAIN || apre <= kAlphaMax;
+                            unclamped = NC || apre <= kAlphaMax;
                             T[q] = T[q] * __builtin_amdgcn_rcpf(1.f - alpha);
                             wgt = alpha * T[q];
                         }
@@ -459,8 +461,9 @@ void k_raster_bwd(BwdArgs a, ViewsK views) {
                 }
             }
         };
-        if (!STORED && plain_batch) walk(std::true_type{});
-        else walk(std::false_type{});
+        if (!STORED && plain_batch) walk(std::true_type{}, std::true_type{});
+        else if (!STORED && nc_batch) walk(std::true_type{}, std::false_type{});
+        else walk(std::false_type{}, std::false_type{});
         __syncthreads();
     }
     if (npend > 0) flush();
