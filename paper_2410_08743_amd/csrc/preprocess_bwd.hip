@@ -527,7 +527,8 @@ __global__ __launch_bounds__(kPoseFinalThreads) void k_pose_final(const double *
     }
     const double2 *src = reinterpret_cast<const double2 *>(posepart + (size_t)v * nrows * 6);
     double s[6] = {0, 0, 0, 0, 0, 0};
-    for (int b0 = 0; b0 < nrows; b0 += kPoseFinalThreads * kPoseFinalPer) {
+    int b0 = 0;
+    do {   // once for a scene without rows too, for the schedule
         double x[kPoseFinalPer][6];
 #pragma unroll
         for (int r = 0; r < kPoseFinalPer; r++) {
@@ -547,7 +548,8 @@ __global__ __launch_bounds__(kPoseFinalThreads) void k_pose_final(const double *
         for (int r = 0; r < kPoseFinalPer; r++)
 #pragma unroll
             for (int c = 0; c < 6; c++) s[c] += x[r][c];
-    }
+        b0 += kPoseFinalThreads * kPoseFinalPer;
+    } while (b0 < nrows);
     // the 256 x 6 thread sums through LDS in one step: lane 8 c + h of the
     // first wave adds 32 of component c's, then 8-lane shuffles finish
     // (every sum in a fixed order)

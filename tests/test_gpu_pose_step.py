@@ -71,3 +71,34 @@ def test_fused_pose_step_skips_an_overflowed_render():
     P, _, m, v, st = trace[0]
     assert np.array_equal(P, init.cpu().numpy())
     assert not m.any() and not v.any() and not st.any()
+
+
+# an empty scene has no partial sums to add: the step is Adam's with a zero
+# gradient, so that moments in flight still move the pose and zero ones do not
+@pytest.mark.parametrize("param", ["se3", "t_so3"])
+@pytest.mark.parametrize("live", [False, True])
+def test_fused_pose_step_of_an_empty_scene(param, live):
+    _, cams, target, init = _setup(2)
+    empty = R.GaussianParams(*[torch.zeros((0,) + s, device=DEV) for s in ((3,), (3,), (4,), (), (1, 3))], 0)
+    rng = np.random.default_rng(74)
+    m0 = torch.tensor(1e-3 * live * rng.standard_normal((2, 6)), dtype=torch.float32, device=DEV)
+    v0 = torch.tensor(1e-5 * live * rng.uniform(0.1, 1.0, (2, 6)), dtype=torch.float32, device=DEV)
+    out = []
+    for fused in (True, False):
+        rast = R.Rasterizer(0)
+        P, m, v = init.clone(), m0.clone(), v0.clone()
+        st = torch.full((2,), 3, dtype=torch.int32, device=DEV)
+        dpose = torch.ones((2, 6), device=DEV)
+        _, dl, _ = rast.forward_l1(empty, cams, P, target, check=False)
+        if fused:
+            rast.backward_pose_step(empty, cams, P, dl, dpose, m, v, st, 1e-2, 1e-4, 50, parametrization=param)
+        else:
+            rast.backward(empty, cams, P, dl, want=(), pose=True, out={"pose": dpose})
+            R.pose_adam(P, dpose, m, v, st, 1e-2, 1e-4, 50, guard=rast.ws, parametrization=param)
+        out.append([t.cpu().numpy() for t in (P, dpose, m, v, st)])
+    for name, x, y in zip(("poses", "dpose", "m", "v", "steps"), *out):
+        assert np.isfinite(x).all() and np.array_equal(x, y), name
+    assert not out[0][1].any() and (out[0][4] == 4).all()
+    # (a T x SO(3) step forms the translation from the centre anew, and rounds it)
+    if live or param == "se3":
+        assert np.array_equal(out[0][0], init.cpu().numpy()) != live
