@@ -131,10 +131,14 @@ struct SplatForm {
 // wherever power <= 0, and whose form is definite enough that splat_p2 is never
 // positive in float32: with B^2 <= 4 A C (1 - 1e-4), the sum in it stays
 // negative under the relative errors (2^-24 each) of its three roundings, and
-// the last rounding keeps the sign.  The rasterizers walk a batch of such splats
-// without the two tests.
+// the last rounding keeps the sign.  The errors are relative only above the
+// smallest normal numbers, hence the floor under A C: it leaves out splats of
+// some 1e5 pixels in both directions, whose products underflow at offsets below
+// 1e-12 pixels at most.  The rasterizers walk a batch of such splats without the
+// two tests.
 __device__ __forceinline__ bool plain_splat(float A2, float B2, float C2, float lo) {
-    return (lo <= kLoNoClamp) & (A2 < 0.f) & (C2 < 0.f) & (B2 * B2 <= 3.9996f * (A2 * C2));
+    const float ac = A2 * C2;
+    return (lo <= kLoNoClamp) & (A2 < 0.f) & (ac >= 1e-20f) & (B2 * B2 <= 3.9996f * ac);
 }
 
 // Bit q of the result is set when some pixel of the 16 x 4 band q of the tile
