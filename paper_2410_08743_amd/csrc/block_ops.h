@@ -16,6 +16,13 @@ constexpr int kWave = 64;
 // (no round trip of the predicate through a vector register).
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
+// Orders a wavefront's LDS accesses before this point against those after it
+// for the compiler (the hardware executes them in program order).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A 4- or 8-byte value through a 32-bit lane exchange.
 template <typename T, typename F>
 __device__ __forceinline__ T by_words(T v, F exchange) {

@@ -42,13 +42,6 @@ namespace gsp {
 constexpr int kQuad = kTile / 2;   // edge of a quadrant
 constexpr int kFwdThreads = 2 * kWave;   // the two quadrants of a half tile
 
-// Orders a wavefront's LDS accesses before this point against those after it
-// for the compiler (the hardware executes them in program order).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 struct FwdArgs {
     const uint32_t *order;
     const uint2 *ranges;

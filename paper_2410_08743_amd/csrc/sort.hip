@@ -14,8 +14,12 @@
 // so that any one cluster is spread as well.  The entries go to their buckets
 // in any order, and each finds its place by comparing itself with the others
 // of its bucket by (depth, value), which is exact.  A run that stays crowded
-// (more than kTdCrowdMax equal depths), or one that does not fit, is sorted in
-// global memory by a stable radix sort over value and depth.
+// with equal depths (more than kTdCrowdMax, as of a wall that faces the camera)
+// is ranked by value first, and the ranks cut its buckets: 3225 lists of 760
+// entries in three walls take 69 us (19 us where the depths differ), and took 139
+// in the global-memory sort.  Crowds of different depths go through a bitonic
+// network in LDS, and a run that does not fit is sorted in global memory by a
+// stable radix sort over value and depth.
 //
 // Bound by latency (loads, then some eight steps through LDS with a barrier
 // each).  An LSD radix sort in one wavefront's LDS took some 25 LDS operations
@@ -56,6 +60,7 @@ struct TdShared {
             uint32_t item[kCap];                      // (key bits below the bucket's, position)
             __align__(16) uint32_t bucket[kCap];      // counts, starts, ends
         };
+        unsigned long long pair[kCap];                // (depth key, value), bitonic network
         struct {                                      // radix sort in global memory
             unsigned long long msk[kWaves][kTdBins];  // lanes of a round by digit
             uint32_t run[kWaves][kTdBins];            // digit counts, then starts
@@ -83,6 +88,18 @@ __device__ __forceinline__ void td_reduce(TdShared<THREADS, ROUNDS> &sh, int t, 
         lo = min(lo, sh.part[2 * v]);
         hi = max(hi, sh.part[2 * v + 1]);
     }
+}
+
+// Whether the condition holds in some thread of the block (which waits here).
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ bool td_any(TdShared<THREADS, ROUNDS> &sh, int t, bool p) {
+    const uint32_t any = wave_any(p) ? 1u : 0u;
+    if (t % kWave == 0) sh.part[t / kWave] = any;
+    __syncthreads();
+    uint32_t all = 0u;
+#pragma unroll
+    for (int v = 0; v < THREADS / kWave; v++) all |= sh.part[v];
+    return all != 0u;
 }
 
 // Bucket counts -> exclusive starts, in place; returns the largest count.
@@ -128,11 +145,209 @@ __device__ __forceinline__ void td_zero(TdShared<THREADS, ROUNDS> &sh, int t) {
         reinterpret_cast<uint4 *>(sh.bucket)[j * THREADS + t] = make_uint4(0, 0, 0, 0);
 }
 
+// Counts of the entries' bins -> starts of the buckets; returns the largest
+// count.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ uint32_t td_buckets(TdShared<THREADS, ROUNDS> &sh, int &t, int L,
+                                               const uint32_t (&bin)[ROUNDS]) {
+    __syncthreads();
+    td_zero(sh, t);
+    __syncthreads();
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) atomicAdd(&sh.bucket[bin[r]], 1u);
+    __syncthreads();
+    return td_scan(sh, t);
+}
+
+// Start and number of entries of bucket b, from the starts.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_bucket(const TdShared<THREADS, ROUNDS> &sh, int L, uint32_t b, uint32_t &s,
+                                          uint32_t &m) {
+    s = sh.bucket[b];
+    m = (b + 1 < (uint32_t)TdShared<THREADS, ROUNDS>::kCap ? sh.bucket[b + 1] : (uint32_t)L) - s;
+}
+
+// The entries' places: each goes to its bucket, in any order, with a word that
+// none shares (key), and counts the words below its own there.  bin becomes the
+// place.  (bucket[b] ends as the end of b.)
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_places(TdShared<THREADS, ROUNDS> &sh, int &t, int L, const uint32_t (&key)[ROUNDS],
+                                          uint32_t (&bin)[ROUNDS]) {
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) sh.item[atomicAdd(&sh.bucket[bin[r]], 1u)] = key[r];
+    __syncthreads();
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            const uint32_t s = bin[r] > 0 ? sh.bucket[bin[r] - 1] : 0u, e = sh.bucket[bin[r]];
+            bin[r] = s;
+            for (uint32_t j = s; j < e; j++) bin[r] += sh.item[j] < key[r] ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+}
+
+// A run that td_sort_buckets left with crowded buckets (in `bin`, and their starts
+// in LDS; with 16 entries per thread they are formed anew): equal depths.  The
+// entries' ranks by value come from buckets of the values, cut like those of the
+// depths; the values of a run differ, so no more than the square root of 2^(bits
+// of the values' range - kLog) of them meet in a bucket (32 for a million splats
+// and 1024 entries).  A bucket of the depths whose m entries are of one depth is
+// then cut by rank, which leaves at most L / m + 1 of them together.  Returns
+// false, with nothing changed, if a crowded bucket holds different depths.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ bool td_sort_ties(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh, int t,
+                                             uint32_t rgx, int L, uint32_t kmin, int sft, uint32_t (&bin)[ROUNDS]) {
+    constexpr int kLog = 31 - __builtin_clz((uint32_t)TdShared<THREADS, ROUNDS>::kCap);
+    constexpr bool kMany = ROUNDS > 8;
+    const uint2 *const run = a.pairs + rgx;
+    uint32_t *const aside = reinterpret_cast<uint32_t *>(a.spare + rgx);
+    uint32_t key[ROUNDS], val[ROUNDS];
+    auto phase = [&]() { asm volatile("" : "+v"(t)); };
+    // (with 16 entries per thread, no more than four entries' loads in flight)
+    auto pace = [&](int r) __attribute__((always_inline)) {
+        if (kMany && r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_keys = [&](int bits) __attribute__((always_inline)) {   // the lowest bits
+        phase();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++)
+            key[r] = r * THREADS + t < L ? (run[r * THREADS + t].x - kmin) & ((1u << bits) - 1u) : 0u;
+    };
+    if constexpr (kMany) {   // the buckets of the depths, cut, once more
+        load_keys(31);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            bin[r] = key[r] >> sft;
+            key[r] &= (1u << sft) - 1u;
+        }
+        td_buckets(sh, t, L, bin);
+        phase();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * THREADS + t < L) {
+                uint32_t s, m;
+                td_bucket(sh, L, bin[r], s, m);
+                bin[r] = s + __umulhi(sft > 0 ? key[r] << (32 - sft) : 0u, m);
+            }
+            pace(r);
+        }
+        td_buckets(sh, t, L, bin);
+    } else {
+        load_keys(sft);
+    }
+    // a bucket's word: some key of it, or ~0 (no key) if it has others too (bit
+    // 31 of an entry's bin: its key is not the word, then: the word is a key)
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) sh.item[bin[r]] = key[r];
+    __syncthreads();
+    bool differ = false;
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            uint32_t s, m;
+            td_bucket(sh, L, bin[r], s, m);
+            const bool other = sh.item[bin[r]] != key[r];
+            differ |= other && m > kTdCrowdMax;
+            bin[r] |= other ? 0x80000000u : 0u;
+        }
+        pace(r);
+    }
+    if (td_any(sh, t, differ)) return false;
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L && (bin[r] >> 31) != 0u) sh.item[bin[r] &= 0x7fffffffu] = 0xffffffffu;
+    __syncthreads();
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) bin[r] |= sh.item[bin[r]] != 0xffffffffu ? 0x80000000u : 0u;
+    if constexpr (kMany) {   // put aside: they would not fit the registers beside the values
+        phase();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++)
+            if (r * THREADS + t < L) aside[r * THREADS + t] = bin[r];
+    }
+    // ranks by value
+    uint32_t vmin = 0xffffffffu, vmax = 0u;
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        val[r] = r * THREADS + t < L ? run[r * THREADS + t].y : 0u;
+        if (r * THREADS + t < L) {
+            vmin = min(vmin, val[r]);
+            vmax = max(vmax, val[r]);
+        }
+    }
+    td_reduce(sh, t, vmin, vmax);
+    const int vb = vmax > vmin ? 32 - __clz(vmax - vmin) : 0, vsft = vb > kLog ? vb - kLog : 0;
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        val[r] -= vmin;
+        key[r] = val[r] >> vsft;
+    }
+    if (td_buckets(sh, t, L, key) > kTdCrowd) {
+        phase();
+#pragma unroll
+        for (int r = 0; r < ROUNDS; r++) {
+            if (r * THREADS + t < L) {
+                uint32_t s, m;
+                td_bucket(sh, L, key[r], s, m);
+                key[r] = s + __umulhi(vsft > 0 ? val[r] << (32 - vsft) : 0u, m);
+            }
+            pace(r);
+        }
+        td_buckets(sh, t, L, key);
+    }
+    td_places(sh, t, L, val, key);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) val[r] = key[r];   // the rank
+    // the buckets of the depths again, those of one depth cut by rank
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if constexpr (kMany) bin[r] = r * THREADS + t < L ? aside[r * THREADS + t] : 0u;
+        key[r] = bin[r] & 0x7fffffffu;
+    }
+    td_buckets(sh, t, L, key);
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) {
+        if (r * THREADS + t < L) {
+            uint32_t s, m;
+            td_bucket(sh, L, key[r], s, m);
+            bin[r] = s + (bin[r] >> 31 ? val[r] * m / (uint32_t)L : 0u);
+        }
+        pace(r);
+    }
+    td_buckets(sh, t, L, bin);
+    load_keys(sft);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++) key[r] = key[r] << kLog | val[r];
+    td_places(sh, t, L, key, bin);
+    phase();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; r++)
+        if (r * THREADS + t < L) a.vals[rgx + bin[r]] = run[r * THREADS + t].y;
+    return true;
+}
+
 // Sorts a run of at most THREADS ROUNDS entries in LDS.  Returns false, with
 // nothing changed, if a bucket stays crowded.
 template <int THREADS, int ROUNDS>
-__device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh,
-                                            int t, uint32_t rgx, int L) {
+__device__ __forceinline__ bool td_sort_buckets(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh,
+                                                int t, uint32_t rgx, int L, uint32_t &kmin, int &sft,
+                                                uint32_t (&bin)[ROUNDS]) {
     constexpr uint32_t kCap = TdShared<THREADS, ROUNDS>::kCap;
     constexpr int kLog = 31 - __builtin_clz(kCap);   // bits of a bucket, and of a position in the run
     static_assert(kCap == 1u << kLog, "a power of two");
@@ -144,7 +359,7 @@ __device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THR
     // (with 16 entries per thread the values are read again at the end: held,
     // they would cost registers spilled to memory)
     constexpr bool kReload = ROUNDS > 8;
-    uint32_t key[ROUNDS], val[ROUNDS], bin[ROUNDS];
+    uint32_t key[ROUNDS], val[ROUNDS];
 #pragma unroll
     for (int r = 0; r < ROUNDS; r++) {
         const int k = r * THREADS + t;
@@ -153,7 +368,8 @@ __device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THR
         val[r] = p.y;
     }
     td_zero(sh, t);
-    uint32_t kmin = 0xffffffffu, kmax = 0u;
+    uint32_t kmax = 0u;
+    kmin = 0xffffffffu;
     phase();
 #pragma unroll
     for (int r = 0; r < ROUNDS; r++) {
@@ -166,7 +382,8 @@ __device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THR
     // Depths lie between the near plane and infinity, so a relative key has
     // at most 31 bits, and those below the bucket's leave room for a position
     // in an entry's word.
-    const int B = kmax > kmin ? 32 - __clz(kmax - kmin) : 0, sft = B > kLog ? B - kLog : 0;
+    const int B = kmax > kmin ? 32 - __clz(kmax - kmin) : 0;
+    sft = B > kLog ? B - kLog : 0;
     phase();
 #pragma unroll
     for (int r = 0; r < ROUNDS; r++) {
@@ -189,15 +406,7 @@ __device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THR
                 bin[r] = s + __umulhi(sft > 0 ? key[r] << (32 - sft) : 0u, e - s);
             }
         }
-        __syncthreads();
-        td_zero(sh, t);
-        __syncthreads();
-        phase();
-#pragma unroll
-        for (int r = 0; r < ROUNDS; r++)
-            if (r * THREADS + t < L) atomicAdd(&sh.bucket[bin[r]], 1u);
-        __syncthreads();
-        if (td_scan(sh, t) > kTdCrowdMax) return false;
+        if (td_buckets(sh, t, L, bin) > kTdCrowdMax) return false;
     }
     // to the buckets, in any order; bucket[b] ends as the end of b
     phase();
@@ -243,6 +452,55 @@ __device__ __forceinline__ bool td_sort_lds(const TileDepthArgs &a, TdShared<THR
     for (int r = 0; r < ROUNDS; r++)
         if (r * THREADS + t < L) a.vals[rgx + r * THREADS + t] = sh.item[r * THREADS + t];
     return true;
+}
+
+// Sorts a run of 2 to THREADS ROUNDS entries in LDS, whatever its keys: a bitonic
+// network over the (depth key, value) pairs, padded to a power of two.  At
+// distances of 64 and less a wavefront's comparisons take 128 neighbouring entries
+// of its own, so that between two such steps a wave waits for no other.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_sort_bitonic(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh,
+                                                int t, uint32_t rgx, int L) {
+    const uint2 *const run = a.pairs + rgx;
+    const int P = 1 << (32 - __clz(L - 1));
+    for (int k = t; k < P; k += THREADS) {
+        const uint2 p = k < L ? run[k] : make_uint2(0xffffffffu, 0xffffffffu);
+        sh.pair[k] = (unsigned long long)p.x << 32 | p.y;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int size = 2; size <= P; size *= 2) {
+#pragma unroll 1
+        for (int d = size / 2; d > 0; d /= 2) {
+            for (int i = t; i < P / 2; i += THREADS) {
+                const int k = 2 * i - (i & (d - 1));
+                const unsigned long long x = sh.pair[k], y = sh.pair[k + d];
+                if ((x > y) == ((k & size) == 0)) {
+                    sh.pair[k] = y;
+                    sh.pair[k + d] = x;
+                }
+            }
+            // (the next step's distance: d / 2, or size behind the last)
+            if (d > kWave || (d == 1 && size > kWave)) __syncthreads();
+            else wave_sync();
+        }
+    }
+    __syncthreads();
+    for (int k = t; k < L; k += THREADS) a.vals[rgx + k] = (uint32_t)sh.pair[k];
+}
+
+// Sorts a run of at most THREADS ROUNDS entries in LDS.
+template <int THREADS, int ROUNDS>
+__device__ __forceinline__ void td_sort_lds(const TileDepthArgs &a, TdShared<THREADS, ROUNDS> &sh, int t,
+                                            uint32_t rgx, int L) {
+    uint32_t kmin;
+    int sft;
+    // (where the ties are put in buckets anew, their bins are other registers:
+    // kept from here, they would be spilled from run to run)
+    uint32_t bin[ROUNDS], ties[ROUNDS];
+    if (!td_sort_buckets(a, sh, t, rgx, L, kmin, sft, bin) &&
+        !td_sort_ties(a, sh, t, rgx, L, kmin, sft, ROUNDS > 8 ? ties : bin))
+        td_sort_bitonic(a, sh, t, rgx, L);
 }
 
 // Rank of the lane's item among the lanes of its round with the same digit,
@@ -354,7 +612,7 @@ __global__ __launch_bounds__(THREADS) void k_tile_depth_sort(TileDepthArgs a) {
     const int L = (int)(rg.y - rg.x);
     if (L < 1 || L > THREADS * ROUNDS) return;
     const int t = threadIdx.x;
-    if (!td_sort_lds(a, sh, t, rg.x, L)) td_sort_global(a, sh, t, rg.x, L);
+    td_sort_lds(a, sh, t, rg.x, L);
 }
 
 // The longer runs, at the front of the launch order.
@@ -368,8 +626,8 @@ __global__ __launch_bounds__(kTdLongThreads) __attribute__((amdgpu_waves_per_eu(
         int t = threadIdx.x;
         asm volatile("" : "+v"(t));
         __syncthreads();
-        if (L > kTdLongThreads * kTdLongRounds || !td_sort_lds(a, sh, t, rg.x, L))
-            td_sort_global(a, sh, t, rg.x, L);
+        if (L > kTdLongThreads * kTdLongRounds) td_sort_global(a, sh, t, rg.x, L);
+        else td_sort_lds(a, sh, t, rg.x, L);
     }
 }
 

@@ -243,6 +243,49 @@ def test_tile_depth_order_bit_exact(n, cap, kind):
     assert np.array_equal(keys, rkeys) and np.array_equal(vals, rvals)
 
 
+# one tile again, with more equal depths than are compared one by one: walls whose
+# splats follow each other in rows, copies of them at the end of the scene (their
+# indices in clusters far apart), in random order among others, and crowds of a
+# few neighbouring depths (no order by index alone)
+@pytest.mark.parametrize("n,cap", [(65, 100), (300, 400), (1023, 1500), (1024, 1500), (1500, 4000), (2048, 4000),
+                                   (5000, 9000), (8192, 9000)])
+@pytest.mark.parametrize("kind", ["wall", "clones", "layers", "mixed", "ulps"])
+def test_tile_depth_order_of_walls_bit_exact(n, cap, kind):
+    rng = S.rng_for(n, 4)
+    far = 40 * n   # the splats of the tile lie among others that are out of view
+    z = np.full(n, 3.0)
+    if kind == "wall":
+        at = (np.arange(n) // 8) * 300 % far + np.arange(n) % 8
+    elif kind == "clones":
+        at = np.concatenate([np.arange(n // 2), far - (n - n // 2) + np.arange(n - n // 2)])
+    elif kind == "layers":
+        at = rng.permutation(far)[:n]
+        z = np.array([2.0, 2.5, 5.0])[np.arange(n) % 3]
+    elif kind == "mixed":
+        at = rng.permutation(far)[:n]
+        z = np.where(rng.random(n) < 0.5, 3.0, rng.uniform(1.0, 9.0, n))
+    else:
+        at = rng.permutation(far)[:n]
+        z = np.where(np.arange(n) % 50 == 0, 1e6, 3.0 + 2.0 ** -22 * rng.integers(0, 5, n))
+    at = np.unique(at)
+    cam = f32_camera(S.Camera(16, 16, 14.0, 14.0, 8.0, 8.0))
+    sc = S.random_scene(n, far, 0, cam)
+    sc.means[:] = [0.0, 0.0, -1.0]
+    m = len(at)
+    z = z[:m].astype(np.float32)
+    sc.means[at] = np.concatenate([rng.uniform(-0.3, 0.3, (m, 2)) * z[:, None], z[:, None]], 1)
+    sc.scales[at] = 0.05 * z[:, None]
+    pose = S.identity_pose()
+    run = _gpu(sc, [cam], [pose], cap=cap)
+    ref = oracle.preprocess(sc, cam, pose)
+    assert not ref["fragile"].any()
+    rkeys, rvals = oracle.bin_sort([ref], [(1, 1)])
+    M, ovf = run["rast"].instances()
+    assert M == m and not ovf
+    keys, vals = _sorted_instances(run["rast"], run["g"], [cam], M)
+    assert np.array_equal(keys, rkeys) and np.array_equal(vals, rvals)
+
+
 def test_keys_bit_exact_two_views():
     sc, cam0, pose0 = random_case(16, 2, 96, 64, 700)
     cam1 = f32_camera(S.Camera(80, 48, 75.0, 70.0, 40.5, 23.75, roi=(16, 16, 50, 32)))

@@ -1,0 +1,61 @@
+"""Stages whose work can be uneven, timed against the same amount of even work on
+the same card: the least of several runs of each, with a factor between them that
+holds easily where the work is shared out and fails where one workgroup, or a
+slower way for all, has it."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2410_08743_amd import render as R
+from paper_2410_08743_amd import synthetic as S
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _params(means, scales, opacity=0.7):
+    n = len(means)
+    f = lambda a: torch.tensor(np.ascontiguousarray(a), dtype=torch.float32, device=DEV)
+    quats = np.zeros((n, 4))
+    quats[:, 0] = 1.0
+    return R.GaussianParams(f(means), f(scales), f(quats), f(np.full(n, opacity)),
+                            f(S.rng_for(n, 8).random((n, 1, 3))), 0)
+
+
+def _stage_us(g, cam, names, runs=12):
+    """Least time of the stages together, over forwards of one view."""
+    pose = torch.tensor(S.identity_pose(), dtype=torch.float32, device=DEV)[None].contiguous()
+    rast = R.Rasterizer(0)
+    rast.forward(g, [cam], pose)
+    rast.capacity = int(1.5 * rast.instances()[0]) + 4096
+    rast.ws = None
+    rast.forward(g, [cam], pose)
+    best = np.inf
+    R.profile_enable(0, R.PROFILE_TIMING)
+    try:
+        R.profile_read(0)
+        for _ in range(runs):
+            rast.forward(g, [cam], pose, check=False)
+            st = R.profile_read(0)
+            best = min(best, sum(st[k][1] for k in names))
+    finally:
+        R.profile_enable(0, 0)
+    return 1e3 * best
+
+
+def test_depth_order_of_walls():
+    """Three walls that face the camera, 70 splats of each in every tile: with
+    equal depths, and with depths that differ."""
+    w, h, f, step = 1200, 680, 600.0, 2
+    y, x = np.mgrid[0:h:step, 0:w:step]
+    z0 = np.concatenate([np.full(x.size, z) for z in (2.5, 3.0, 3.5)])
+    spread = z0 * (1 + 0.06 * S.rng_for(1, 8).uniform(-1, 1, len(z0)))
+    cam = S.Camera(w, h, f, f, w / 2, h / 2)
+    us = []
+    for z in (z0, spread):
+        means = np.stack([(np.tile(x.ravel(), 3) + 0.5 - w / 2) / f * z, (np.tile(y.ravel(), 3) + 0.5 - h / 2) / f * z,
+                          z], 1)
+        us.append(_stage_us(_params(means, np.repeat((1.1 * step / f * z)[:, None], 3, 1)), cam, ["depth_order"]))
+    print(f"depth order: equal {us[0]:.1f}, different {us[1]:.1f} us")
+    assert us[0] < 5.5 * us[1]
