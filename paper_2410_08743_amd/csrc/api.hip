@@ -422,7 +422,7 @@ gsp_status render_fwd(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gsp
     if ((e = stage(ctx, "duplicate", st, [&] { return gsp::launch_bin_count(p.views, p.L, ws, st); })) !=
         hipSuccess)
         return hip_fail(e, "duplicate");
-    if ((e = stage(ctx, "ranges", st, [&] { return gsp::launch_bin_scan(p.L, ws, st); })) != hipSuccess)
+    if ((e = stage(ctx, "ranges", st, [&] { return gsp::launch_bin_scan(p.views, p.L, ws, st); })) != hipSuccess)
         return hip_fail(e, "ranges");
     if ((e = stage(ctx, "tile_sort", st, [&] { return gsp::launch_bin_scatter(p.views, p.L, ws, st); })) !=
         hipSuccess)

@@ -24,6 +24,8 @@
 // 5.0 + 16.3, 25 + 6 + 117 and 45 + 8 + 213 us.  The first is bound by latency
 // and its row atomics, the last by the LDS atomic, the depth's gather and the
 // scattered store that each entry takes.
+#include <cstring>
+
 #include "block_ops.h"
 #include "gsp_internal.h"
 
@@ -46,30 +48,9 @@ __host__ __device__ inline int2 bin_window_shape(int gw, int gh) {
     return make_int2(gw, (gh + nwy - 1) / nwy);   // windows of equal height
 }
 
-__host__ __device__ inline int bin_windows_of(int gw, int gh) {
+static int bin_windows_of(int gw, int gh) {
     const int2 s = bin_window_shape(gw, gh);
     return ((gw + s.x - 1) / s.x) * ((gh + s.y - 1) / s.y);
-}
-
-__device__ __forceinline__ BinWindow bin_window(const ViewsK &views, int w) {
-    BinWindow b;
-    b.view = 0;
-    int nw = bin_windows_of(views.v[0].gw, views.v[0].gh);
-    while (w >= nw) {
-        w -= nw;
-        b.view++;
-        nw = bin_windows_of(views.v[b.view].gw, views.v[b.view].gh);
-    }
-    const ViewK &vw = views.v[b.view];
-    const int2 s = bin_window_shape(vw.gw, vw.gh);
-    const int nwx = (vw.gw + s.x - 1) / s.x;
-    b.x0 = (w % nwx) * s.x;
-    b.y0 = (w / nwx) * s.y;
-    b.x1 = min(b.x0 + s.x, vw.gw);
-    b.y1 = min(b.y0 + s.y, vw.gh);
-    b.t0 = vw.tile_base + b.y0 * vw.gw + b.x0;
-    b.nt = (b.y1 - b.y0) * (b.x1 - b.x0);
-    return b;
 }
 
 struct BinArgs {
@@ -90,7 +71,36 @@ struct BinArgs {
     uint8_t *slot_flags;           // [cap][kSplitBwd], cleared here for slots < M
     unsigned long long cap;
     int n, V, chunks, chunk_splats, total_tiles, groups;
+    int windows;                   // of all views
+    int first[GSP_MAX_VIEWS];      // first window of each view
 };
+
+// Window w of all; the lanes look at a view each for the one that has it (32
+// views one after the other, whose sizes each wait for a scalar load, took 10 us).
+__device__ __forceinline__ BinWindow bin_window(const BinArgs &a, const ViewsK &views, int w) {
+    BinWindow b;
+    if (a.windows == a.V) {   // one each
+        const ViewK &vw = views.v[w];
+        b.view = w;
+        b.x0 = b.y0 = 0;
+        b.x1 = vw.gw;
+        b.y1 = vw.gh;
+        b.t0 = vw.tile_base;
+    } else {
+        const int lane = threadIdx.x % kWave;
+        b.view = __popcll(__ballot(lane < a.V && a.first[lane < a.V ? lane : 0] <= w)) - 1;
+        const ViewK &vw = views.v[b.view];
+        const int2 s = bin_window_shape(vw.gw, vw.gh);
+        const int nwx = (vw.gw + s.x - 1) / s.x, k = w - a.first[b.view];
+        b.x0 = (k % nwx) * s.x;
+        b.y0 = (k / nwx) * s.y;
+        b.x1 = min(b.x0 + s.x, vw.gw);
+        b.y1 = min(b.y0 + s.y, vw.gh);
+        b.t0 = vw.tile_base + b.y0 * vw.gw + b.x0;
+    }
+    b.nt = (b.y1 - b.y0) * (b.x1 - b.x0);
+    return b;
+}
 
 // Workgroup -> (window, chunk): chunks / 8 neighbouring chunks to an XCD.
 // chunk may lie past the last one (the grid has whole eights).
@@ -148,7 +158,7 @@ __global__ __launch_bounds__(kBinCountThreads) void k_bin_count(BinArgs a, Views
     int wi, chunk;
     bin_block(a, blockIdx.x, wi, chunk);
     if (chunk >= a.chunks) return;
-    const BinWindow w = bin_window(views, wi);
+    const BinWindow w = bin_window(a, views, wi);
     const int t = threadIdx.x, lane = t % kWave, cols = w.x1 - w.x0, rows = w.y1 - w.y0;
     const int begin = chunk * a.chunk_splats, end = min(a.n, begin + a.chunk_splats);
     for (int k = t; k < w.nt; k += NT) diff[k] = 0;
@@ -490,7 +500,7 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
     int wi, chunk;
     bin_block(a, blockIdx.x - 1, wi, chunk);
     if (chunk >= a.chunks) return;
-    const BinWindow w = bin_window(views, wi);
+    const BinWindow w = bin_window(a, views, wi);
     // Everything the block needs before its splats, in one round of memory
     // latency: the lists in front of the window; the window's lists and this
     // chunk's place in each; the first splats.
@@ -648,8 +658,9 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
     }
 }
 
-static BinArgs bin_args(const Layout &L, char *ws) {
+static BinArgs bin_args(const ViewsK &views, const Layout &L, char *ws) {
     BinArgs a;
+    std::memset(&a, 0, sizeof a);
     a.rect = region<uint2>(ws, L.rect);
     a.tiles = region<uint32_t>(ws, L.tiles);
     a.depth = region<uint32_t>(ws, L.depth);
@@ -673,31 +684,31 @@ static BinArgs bin_args(const Layout &L, char *ws) {
     a.chunk_splats = L.bin_chunk_splats;
     a.total_tiles = L.total_tiles;
     a.groups = (L.total_tiles + kWave - 1) / kWave;
+    for (int v = 0; v < views.count; v++) {
+        a.first[v] = a.windows;
+        a.windows += bin_windows_of(views.v[v].gw, views.v[v].gh);
+    }
     return a;
 }
 
-static unsigned bin_blocks(const ViewsK &views, const Layout &L) {
-    int64_t windows = 0;
-    for (int v = 0; v < views.count; v++) windows += bin_windows_of(views.v[v].gw, views.v[v].gh);
-    return (unsigned)(windows * 8 * ((L.bin_chunks + 7) / 8));
-}
+static unsigned bin_blocks(const BinArgs &a) { return (unsigned)a.windows * 8u * (unsigned)((a.chunks + 7) / 8); }
 
 hipError_t launch_bin_count(const ViewsK &views, const Layout &L, char *ws, hipStream_t s) {
-    const unsigned blocks = bin_blocks(views, L);
-    if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_bin_count, dim3(blocks), dim3(kBinCountThreads), 0, s, bin_args(L, ws), views);
+    const BinArgs a = bin_args(views, L, ws);
+    if (bin_blocks(a) == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_bin_count, dim3(bin_blocks(a)), dim3(kBinCountThreads), 0, s, a, views);
     return hipGetLastError();
 }
 
-hipError_t launch_bin_scan(const Layout &L, char *ws, hipStream_t s) {
-    const BinArgs a = bin_args(L, ws);
+hipError_t launch_bin_scan(const ViewsK &views, const Layout &L, char *ws, hipStream_t s) {
+    const BinArgs a = bin_args(views, L, ws);
     hipLaunchKernelGGL(k_bin_scan, dim3(a.groups + 1), dim3(kBinScanThreads), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_bin_scatter(const ViewsK &views, const Layout &L, char *ws, hipStream_t s) {
-    hipLaunchKernelGGL(k_bin_scatter, dim3(bin_blocks(views, L) + 1), dim3(kBinScatterThreads), 0, s,
-                       bin_args(L, ws), views);
+    const BinArgs a = bin_args(views, L, ws);
+    hipLaunchKernelGGL(k_bin_scatter, dim3(bin_blocks(a) + 1), dim3(kBinScatterThreads), 0, s, a, views);
     return hipGetLastError();
 }
 

@@ -170,7 +170,7 @@ hipError_t launch_preprocess(const GaussiansK &g, const ViewsK &views, const flo
                              const Layout &L, char *ws, hipStream_t s);
 // binning.hip
 hipError_t launch_bin_count(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
-hipError_t launch_bin_scan(const Layout &L, char *ws, hipStream_t s);
+hipError_t launch_bin_scan(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
 hipError_t launch_bin_scatter(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
 // Writes the tile id of every sorted instance over the pairs region.
 hipError_t launch_tile_ids(const Layout &L, char *ws, hipStream_t s);

@@ -23,20 +23,21 @@ def _params(means, scales, opacity=0.7):
                             f(S.rng_for(n, 8).random((n, 1, 3))), 0)
 
 
-def _stage_us(g, cam, names, runs=12):
-    """Least time of the stages together, over forwards of one view."""
-    pose = torch.tensor(S.identity_pose(), dtype=torch.float32, device=DEV)[None].contiguous()
+def _stage_us(g, cam, names, views=1, runs=12):
+    """Least time of the stages together, over forwards of the same view."""
+    pose = torch.tensor(np.stack([S.identity_pose()] * views), dtype=torch.float32, device=DEV).contiguous()
+    cams = [cam] * views
     rast = R.Rasterizer(0)
-    rast.forward(g, [cam], pose)
+    rast.forward(g, cams, pose)
     rast.capacity = int(1.5 * rast.instances()[0]) + 4096
     rast.ws = None
-    rast.forward(g, [cam], pose)
+    rast.forward(g, cams, pose)
     best = np.inf
     R.profile_enable(0, R.PROFILE_TIMING)
     try:
         R.profile_read(0)
         for _ in range(runs):
-            rast.forward(g, [cam], pose, check=False)
+            rast.forward(g, cams, pose, check=False)
             st = R.profile_read(0)
             best = min(best, sum(st[k][1] for k in names))
     finally:
@@ -59,3 +60,15 @@ def test_depth_order_of_walls():
         us.append(_stage_us(_params(means, np.repeat((1.1 * step / f * z)[:, None], 3, 1)), cam, ["depth_order"]))
     print(f"depth order: equal {us[0]:.1f}, different {us[1]:.1f} us")
     assert us[0] < 5.5 * us[1]
+
+
+def test_binning_of_many_small_views():
+    """32 views fit the chip side by side: they take hardly longer than one."""
+    cam = S.Camera(128, 128, 100.0, 100.0, 64.0, 64.0)
+    rng = S.rng_for(3, 8)
+    z = rng.uniform(1.5, 8.0, 1000)
+    means = np.stack([rng.uniform(-0.7, 0.7, 1000) * z, rng.uniform(-0.7, 0.7, 1000) * z, z], 1)
+    g = _params(means, np.exp(rng.uniform(np.log(0.01), np.log(0.1), (1000, 3))))
+    us = [_stage_us(g, cam, ["duplicate", "ranges", "tile_sort"], views) for views in (1, 32)]
+    print(f"binning: one view {us[0]:.1f}, 32 views {us[1]:.1f} us")
+    assert us[1] < 2.0 * us[0]
