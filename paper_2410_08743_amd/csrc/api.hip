@@ -197,9 +197,14 @@ Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views,
     for (int v = 0; v < V; v++) pix += (int64_t)views.v[v].roi_w * views.v[v].roi_h;
     L.total_pix = pix;
     L.nblk_pre = (int)((n + kPreprocessBlock - 1) / kPreprocessBlock);
-    int64_t most_tiles = 1;
-    for (int v = 0; v < V; v++) most_tiles = std::max(most_tiles, (int64_t)views.v[v].gw * views.v[v].gh);
-    L.bin_chunks = bin_chunks_for(n, V, L.cap, most_tiles, std::max(L.total_tiles, 1));
+    int64_t windows = 0;
+    double share = 0.0;   // of the capacity, by tiles: the largest window's
+    for (int v = 0; v < V; v++) {
+        const int w = bin_windows_of(views.v[v].gw, views.v[v].gh);
+        share = std::max(share, (double)views.v[v].gw * views.v[v].gh / w / views.total_tiles);
+        windows += w;
+    }
+    L.bin_chunks = bin_chunks_for(n, L.cap, windows, share);
     L.bin_chunk_splats = L.bin_chunks > 0 ? (int)((n + L.bin_chunks - 1) / L.bin_chunks) : 0;
     L.nwin_max = (int)((L.vn + L.cap + kWindow - 1) / kWindow + 1);
     const size_t vn = (size_t)L.vn, capz = (size_t)L.cap;

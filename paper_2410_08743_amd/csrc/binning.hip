@@ -48,7 +48,7 @@ __host__ __device__ inline int2 bin_window_shape(int gw, int gh) {
     return make_int2(gw, (gh + nwy - 1) / nwy);   // windows of equal height
 }
 
-static int bin_windows_of(int gw, int gh) {
+int bin_windows_of(int gw, int gh) {
     const int2 s = bin_window_shape(gw, gh);
     return ((gw + s.x - 1) / s.x) * ((gh + s.y - 1) / s.y);
 }
@@ -307,20 +307,23 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
             len[r] = k < a.total_tiles ? (ovf ? 0 : (int)a.total[k]) : -1;
         }
     };
+    // The next step's lengths and group sums are loaded before a step's work.
+    int len[kOrderRounds], ahead[kOrderRounds];
+    auto load_group = [&](int k0) {
+        const int g = k0 / kWave + lane;
+        return w == 0 && g < a.groups && !ovf ? a.gsum[g] : 0ull;
+    };
+    static_assert(kGroups == kWave, "a lane per group of a step");
+    load(0, len);
+    unsigned long long gs = load_group(0);
     for (int k0 = 0; k0 < a.total_tiles; k0 += kStep) {
-        int len[kOrderRounds];
-        load(k0, len);
+        load(k0 + kStep, ahead);
+        const unsigned long long gs_ahead = load_group(k0 + kStep);
         // first entry of each group of the step
         if (w == 0) {
-            unsigned long long run = s.carry;
-            for (int g0 = 0; g0 < kGroups; g0 += kWave) {
-                const int g = k0 / kWave + g0 + lane;
-                const unsigned long long x = g < a.groups && !ovf ? a.gsum[g] : 0ull;
-                const unsigned long long inc = wave_inclusive_scan(x);
-                s.gstart[g0 + lane] = run + inc - x;
-                run += wave_lane(inc, kWave - 1);
-            }
-            if (lane == 0) s.carry = run;
+            const unsigned long long run = s.carry, inc = wave_inclusive_scan(gs);
+            s.gstart[lane] = run + inc - gs;
+            if (lane == kWave - 1) s.carry = run + inc;
         }
         __syncthreads();
         uint32_t full = 0;   // this thread's full chunks in the step
@@ -340,6 +343,9 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
         const uint32_t wfull = wave_sum(full);
         if (lane == 0 && wfull > 0) atomicAdd(&s.cnt[1][kFull], wfull);
         __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kOrderRounds; r++) len[r] = ahead[r];
+        gs = gs_ahead;
     }
     // exclusive scans of the two bucket histograms: one wave, eight buckets per lane
     constexpr int kPer = kOrderBuckets / kWave;
@@ -367,10 +373,10 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
             a.counters[kCntOver2048] = s.base[0][order_bucket(2048)];
         }
     }
+    load(0, len);
     __syncthreads();
     for (int k0 = 0; k0 < a.total_tiles; k0 += kStep) {
-        int len[kOrderRounds];
-        load(k0, len);
+        load(k0 + kStep, ahead);
         uint32_t full = 0;
 #pragma unroll
         for (int r = 0; r < kOrderRounds; r++) full += len[r] >= 0 ? (uint32_t)(chunks_of(len[r]) - 1) : 0u;
@@ -398,6 +404,8 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
                 wb += (uint32_t)__popcll(m);
             }
         }
+#pragma unroll
+        for (int r = 0; r < kOrderRounds; r++) len[r] = ahead[r];
     }
 }
 

@@ -29,23 +29,29 @@ constexpr double kLog2e = 1.4426950408889634;
 
 constexpr int kPreprocessBlock = 256;    // Gaussians per preprocess block
 // Chunks of a view's splats in the binning: one workgroup counts and writes the
-// instances of one chunk, one workgroup to a CU.  The chunks of all views fill
-// whole rounds of 248 CUs (the chip's 256 but for the one that orders the tiles
-// meanwhile and what whole eights of chunks leave over): two rounds, or as many
-// as it takes that the chunks of the largest view, by its share of the
-// capacity (1.25 to 1.5 times the instances), stay in LDS (kBinStage entries,
-// binning.hip).  A view has at most 248, and fewer where they would hold less
-// than 256 splats (a workgroup's fixed work is a few microseconds, and every
-// chunk has a count per tile).
+// instances of one chunk in one window of the view's tiles (all of them, up to
+// 4096 tiles), one workgroup to a CU.  The chunks of all windows fill whole rounds
+// of 248 CUs (the chip's 256 but for the one that orders the tiles meanwhile and
+// what whole eights of chunks leave over): two rounds, or as many as it takes that
+// the chunks of the largest window, by its share of the capacity (1.25 to 1.5
+// times the instances), stay in LDS (kBinStage entries, binning.hip).  A view has
+// at most 248, and fewer where they would hold less than 256 splats (a workgroup's
+// fixed work is a few microseconds, and every chunk has a count per tile).
+// Windows counted like views keep the counts of a large image small: at 16384 x
+// 16384 (256 windows, 200k splats, 19.7M instances) 3 chunks and 13 MB instead of
+// 248 and 1 GB, and the three kernels take 2.3 ms instead of 4.0.
 constexpr int kBinChunks = 248;
-inline int bin_chunks_for(int64_t n, int V, int64_t cap, int64_t most_tiles, int64_t total_tiles) {
-    const double need = (double)cap * (double)most_tiles / (double)total_tiles / 36000.0;
-    const int64_t rounds = (int64_t)(need * V / kBinChunks) + 1;
-    int64_t c = kBinChunks * (rounds < 2 ? 2 : rounds) / V;
+inline int bin_chunks_for(int64_t n, int64_t cap, int64_t windows, double window_share) {
+    const double need = (double)cap * window_share / 36000.0;
+    const int64_t rounds = (int64_t)(need * (double)windows / kBinChunks) + 1;
+    int64_t c = kBinChunks * (rounds < 2 ? 2 : rounds) / windows;
+    if (c < 1) c = 1;
     const int64_t by_n = (n + 255) / 256;
     if (c > by_n) c = by_n;
     return (int)(c < kBinChunks ? c : kBinChunks);
 }
+// Windows of a view of gw x gh tiles (binning.hip).
+int bin_windows_of(int gw, int gh);
 constexpr int kPoseReduceBlock = 256;
 // Rows of per-wavefront pose partials per preprocess-backward block.
 constexpr int kPoseRowsPerBlock = kPoseReduceBlock / 64;

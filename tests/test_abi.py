@@ -103,3 +103,19 @@ def test_product_package_does_not_import_the_oracle():
                 text = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in text and "from oracle" not in text, f
                 assert "gso_" not in text and "liboracle" not in text, f
+
+
+def test_workspace_of_a_large_image_is_not_counts_of_chunks(lib):
+    """What splats add to the workspace of an image of a million tiles is their
+    own records (some 150 bytes each) and a few counts per tile, not one for
+    every chunk of splats that a small image is worth."""
+    from paper_2410_08743_amd import _native as N
+    from paper_2410_08743_amd.synthetic import Camera
+    view = N.view_array([Camera(16384, 16384, 13000.0, 13000.0, 8192.0, 8192.0)])
+    size = []
+    for n in (1, 200_000):
+        sz = ctypes.c_size_t()
+        assert lib.gsp_workspace_size(n, 3, 1, view, 30_000_000, ctypes.byref(sz)) == N.GSP_OK
+        size.append(sz.value)
+    tiles = 1024 * 1024
+    assert size[1] - size[0] < 150 * 200_000 + 8 * 4 * tiles
