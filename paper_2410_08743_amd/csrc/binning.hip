@@ -71,6 +71,12 @@ struct BinArgs {
     uint8_t *slot_flags;           // [cap][kSplitBwd], cleared here for slots < M
     unsigned long long cap;
     int n, V, chunks, chunk_splats, total_tiles, groups;
+    // chunks with more entries in a window than a workgroup stages: first piece,
+    // window, chunk, -; and, per such chunk, the entries written so far per tile of
+    // the window (both in the gradient slots, which are the backward's)
+    uint4 *heavy;
+    uint32_t *written;             // [max_heavy][kBinTiles]
+    uint32_t max_heavy;
     int windows;                   // of all views
     int first[GSP_MAX_VIEWS];      // first window of each view
 };
@@ -143,6 +149,9 @@ __device__ __forceinline__ BinRect bin_clip(const BinWindow &w, const BinSplat &
     return r;
 }
 
+constexpr int kBinStage = 32256;   // entries of a chunk (in a window) that are staged in LDS
+constexpr int kBinPiece = 16384;   // entries of a piece of a chunk that has more (+- a splat's)
+
 constexpr int kBinCountThreads = 512;
 
 // mat[chunk][tile] = splats of the chunk that touch the tile; csum[view][chunk]
@@ -155,6 +164,7 @@ __global__ __launch_bounds__(kBinCountThreads) void k_bin_count(BinArgs a, Views
     constexpr int NT = kBinCountThreads;
     __shared__ int diff[kBinTiles];
     __shared__ unsigned long long red[NT / kWave];
+    __shared__ uint32_t row;
     int wi, chunk;
     bin_block(a, blockIdx.x, wi, chunk);
     if (chunk >= a.chunks) return;
@@ -163,13 +173,14 @@ __global__ __launch_bounds__(kBinCountThreads) void k_bin_count(BinArgs a, Views
     const int begin = chunk * a.chunk_splats, end = min(a.n, begin + a.chunk_splats);
     for (int k = t; k < w.nt; k += NT) diff[k] = 0;
     __syncthreads();
-    unsigned long long sum = 0;
+    unsigned long long sum = 0, own = 0;   // entries, and those in the window
 #pragma unroll 2
     for (int i = begin + t; i < end; i += NT) {
         const BinSplat p = bin_fetch(a, w, i, end);
         sum += p.full;
         const BinRect r = bin_clip(w, p);
         if (r.any()) {
+            own += (uint32_t)(r.x1 - r.x0) * (uint32_t)(r.y1 - r.y0);
             for (int y = r.y0; y < r.y1; y++) {
                 atomicAdd(&diff[y * cols + r.x0], 1);
                 if (r.x1 < cols) atomicAdd(&diff[y * cols + r.x1], -1);
@@ -187,9 +198,24 @@ __global__ __launch_bounds__(kBinCountThreads) void k_bin_count(BinArgs a, Views
             run = wave_lane(v, kWave - 1);
         }
     }
+    own = block_sum<unsigned long long, NT>(own, red);
     if (w.x0 == 0 && w.y0 == 0) {   // the view's first window
         sum = block_sum<unsigned long long, NT>(sum, red);
         if (t == 0) a.csum[(size_t)w.view * a.chunks + chunk] = sum;
+    }
+    if (own > (unsigned long long)kBinStage) {
+        // (counts past what the capacity has room for overflow it: the chunks are
+        // not written then)
+        if (t == 0) {
+            const unsigned long long pieces = min((own + kBinPiece - 1) / kBinPiece, 1ull << 18);
+            const unsigned long long at =
+                atomicAdd(reinterpret_cast<unsigned long long *>(a.counters + kCntPieces), 1ull << 32 | pieces);
+            row = (uint32_t)(at >> 32);
+            if (row < a.max_heavy) a.heavy[row] = make_uint4((uint32_t)at, (uint32_t)wi, (uint32_t)chunk, 0u);
+        }
+        __syncthreads();
+        if (row < a.max_heavy)
+            for (int k = t; k < w.nt; k += NT) a.written[(size_t)row * kBinTiles + k] = 0u;
     }
 }
 
@@ -415,7 +441,6 @@ __device__ __forceinline__ void bin_order(const BinArgs &a, OrderShared &s, bool
 // starts in.  The window's tiles: next position of this chunk's entries, first
 // in `entry` (staged) or in the list; then what to add to a staged position
 // for that in the list.
-constexpr int kBinStage = 32256;         // entries of a chunk that are staged in LDS
 constexpr int kBinLocalBits = 20;        // bits of a splat within its chunk, above them the tile
 static_assert(kBinTiles <= 1 << (32 - kBinLocalBits), "a tile's bits");
 struct ScatterShared {
@@ -425,7 +450,9 @@ struct ScatterShared {
     uint16_t start[kBinScatterThreads];
     uint2 pack[2][kBinScatterThreads / kWave];
     uint32_t scratch[kBinScatterThreads / kWave];
+    unsigned long long scratch2[kBinScatterThreads / kWave];
     uint32_t part[3][kBinScatterThreads / kWave];
+    uint32_t piece;
     uint32_t entry[kBinStage];
 };
 
@@ -480,40 +507,121 @@ __device__ __forceinline__ void bin_walk(ScatterShared &s, uint32_t cols, uint32
     }
 }
 
-// Workgroup 0 orders the tiles; the others write their chunk's entries to the
-// tiles' lists.  Those of a view's first window also write what goes by splat:
-// the first slot of each splat's instances (in index order, rows of the rect
-// outer and columns inner: the backward's gradient slots), the work windows of
-// the slot reduction, and the cleared slot flags.  Splat k's entry sits at
-// position h = k + offsets[k] of the sequence (splat, its instances, next
-// splat, ...), the next at h + 1 + count; work window b starts at the first
-// splat whose entry is at or after b kWindow.
+// A batch's splat with entries (mine of them, the first at e0, the j-th packed
+// one), for the walk: its place among the batch's entries, its tiles, and the
+// threads whose shares start in it.
+__device__ __forceinline__ void bin_pack(ScatterShared &s, const BinRect &r, uint32_t mine, uint32_t e0, uint32_t j,
+                                         uint32_t per) {
+    if (mine == 0u) return;
+    s.off[j] = e0;
+    s.rect[j] = make_uint2((uint32_t)r.x0 | (uint32_t)(r.x1 - r.x0) << 16, (uint32_t)r.y0 | threadIdx.x << 16);
+    for (uint32_t q = (e0 + per - 1) / per; q * per < e0 + mine; q++) s.start[q] = (uint16_t)j;
+}
+
+// The heavy chunks' pieces, shared out over the workgroups as they come free.
+// Piece p of a chunk is the splats whose first entry lies in the p-th kBinPiece
+// entries of the chunk in its window (a splat has no more than the window's
+// tiles).  It is walked twice: to count its entries per tile and reserve their
+// places in the chunk's part of the lists, and to write them there.  Every
+// workgroup comes to its end when the pieces are taken; none waits for another.
+__device__ __forceinline__ void bin_pieces(const BinArgs &a, const ViewsK &views, ScatterShared &s, uint32_t pieces,
+                                           uint32_t heavy) {
+    constexpr int NT = kBinScatterThreads, kPer = kBinTiles / NT;
+    const int t = threadIdx.x;
+    for (;;) {
+        __syncthreads();
+        if (t == 0) s.piece = atomicAdd(a.counters + kCntNextPiece, 1u);
+        __syncthreads();
+        const uint32_t p = s.piece;
+        if (p >= pieces) return;
+        uint32_t h = 0;   // the last chunk whose first piece is p or before it
+        for (uint32_t past = heavy; past - h > 1;) {
+            const uint32_t mid = (h + past) / 2;
+            if (a.heavy[mid].x <= p) h = mid;
+            else past = mid;
+        }
+        const uint4 rec = a.heavy[h];
+        const BinWindow w = bin_window(a, views, (int)rec.y);
+        const int chunk = (int)rec.z, begin = chunk * a.chunk_splats, end = min(a.n, begin + a.chunk_splats);
+        const uint32_t x0 = (p - rec.x) * kBinPiece, cols = (uint32_t)(w.x1 - w.x0);
+        const uint32_t idc = (uint32_t)((size_t)w.view * a.n + begin);
+        // where the chunk's entries of each tile start: the lists in front of the
+        // window, those in front of the tile, and the chunks in front
+        uint32_t front = 0, first[kPer], sum = 0;
+        const int g0 = w.t0 / kWave;
+        for (int g = t; g < g0; g += NT) front += (uint32_t)a.gsum[g];
+        if (g0 * kWave + t < w.t0) front += a.total[g0 * kWave + t];
+#pragma unroll
+        for (int j = 0; j < kPer; j++) {
+            const int k = kPer * t + j;
+            first[j] = sum + (k < w.nt ? a.mat[(size_t)chunk * a.total_tiles + w.t0 + k] : 0u);
+            sum += k < w.nt ? a.total[w.t0 + k] : 0u;
+            if (k < w.nt) s.cur[k] = 0u;
+        }
+        uint32_t all;
+        front = block_sum<uint32_t, NT>(front, s.scratch) + block_exclusive_scan<uint32_t, NT>(sum, s.scratch, &all);
+#pragma unroll 1
+        for (int pass = 0; pass < 2; pass++) {
+            uint32_t run = 0;
+            for (int i0 = begin; i0 < end && (run < x0 || run - x0 < kBinPiece); i0 += NT) {
+                const BinRect r = bin_clip(w, bin_fetch(a, w, i0 + t, end));
+                const uint32_t area = r.any() ? (uint32_t)(r.x1 - r.x0) * (uint32_t)(r.y1 - r.y0) : 0u;
+                uint32_t batch;
+                const uint32_t e = run + block_exclusive_scan<uint32_t, NT>(area, s.scratch, &batch);
+                run += batch;
+                if (run <= x0) continue;
+                const uint32_t mine = e >= x0 && e - x0 < kBinPiece ? area : 0u;
+                unsigned long long both;   // entries and splats of the piece
+                const unsigned long long at = block_exclusive_scan<unsigned long long, NT>(
+                    (unsigned long long)mine << 32 | (mine > 0 ? 1u : 0u), s.scratch2, &both);
+                const uint32_t total = (uint32_t)(both >> 32), per = (total + NT - 1) / NT;
+                if (t == 0) s.off[(uint32_t)both] = total;
+                bin_pack(s, r, mine, (uint32_t)(at >> 32), (uint32_t)at, per);
+                __syncthreads();
+                const uint32_t id0 = idc + (uint32_t)(i0 - begin);
+                bin_walk(s, cols, total, per, [&](uint32_t pos, uint32_t k, uint32_t) {
+                    if (pass == 1) a.pairs[pos] = make_uint2(a.depth[id0 + k], id0 + k);
+                });
+                __syncthreads();
+            }
+            if (pass == 0) {
+#pragma unroll
+                for (int j = 0; j < kPer; j++) {
+                    const int k = kPer * t + j;
+                    const uint32_t c = k < w.nt ? s.cur[k] : 0u;
+                    if (c > 0u) s.cur[k] = front + first[j] + atomicAdd(&a.written[(size_t)h * kBinTiles + k], c);
+                }
+                __syncthreads();
+            }
+        }
+    }
+}
+
+// Writes the entries of a chunk in a window to the tiles' lists.  The view's first
+// window also has what goes by splat: the first slot of each splat's instances (in
+// index order, rows of the rect outer and columns inner: the backward's gradient
+// slots), the work windows of the slot reduction, and the cleared slot flags.  Splat
+// k's entry sits at position h = k + offsets[k] of the sequence (splat, its
+// instances, next splat, ...), the next at h + 1 + count; work window b starts at
+// the first splat whose entry is at or after b kWindow.
 //
 // Entries of the same tile are brought together in LDS first, so that a store
 // covers runs of them: written one by one, each would be a partial line of its
 // own wherever the lists being written exceed the L2 (190 -> 121 us at 15.4M
-// instances in 12096 lists; 97 -> 62 us at 6.7M in 9600).  A chunk with too
-// many entries writes them one by one.
-__global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, ViewsK views) {
-    __shared__ union {
-        OrderShared o;
-        ScatterShared s;
-    } sh;
+// instances in 12096 lists; 97 -> 62 us at 6.7M in 9600).  A chunk with too many
+// entries (neighbouring splats that are large: a scene in an order of its own)
+// leaves them to all workgroups, in pieces: 300 splats over a whole 1008 x 756 view
+// in front of 200k small ones take 56 us, and took 554 where that chunk's workgroup
+// wrote them alone.
+__device__ __forceinline__ void bin_chunk(const BinArgs &a, const ViewsK &views, ScatterShared &s, int wi, int chunk,
+                                          bool ovf) {
     constexpr int NT = kBinScatterThreads, NW = NT / kWave;
     const int t = threadIdx.x, lane = t % kWave, wv = t / kWave;
-    if (blockIdx.x == 0) {
-        bin_order(a, sh.o, a.counters[kCntOverflow] != 0u);
-        return;
-    }
-    int wi, chunk;
-    bin_block(a, blockIdx.x - 1, wi, chunk);
-    if (chunk >= a.chunks) return;
     const BinWindow w = bin_window(a, views, wi);
     // Everything the block needs before its splats, in one round of memory
     // latency: the lists in front of the window; the window's lists and this
     // chunk's place in each; the first splats.
     const int begin = chunk * a.chunk_splats, end = min(a.n, begin + a.chunk_splats);
-    const bool ovf = a.counters[kCntOverflow] != 0u;
     const uint32_t before = a.cstart[w.view * a.chunks + chunk];
     constexpr int kPer = kBinTiles / NT;
     uint32_t front = 0, c[kPer], row[kPer], cnt[kPer];
@@ -546,7 +654,7 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
         mine = r.any() ? (uint32_t)(r.x1 - r.x0) * (uint32_t)(r.y1 - r.y0) : 0u;
         has = __ballot(mine > 0);
         inc = wave_inclusive_scan(mine);
-        if (lane == kWave - 1) sh.s.pack[parity][wv] = make_uint2(inc, (uint32_t)__popcll(has));
+        if (lane == kWave - 1) s.pack[parity][wv] = make_uint2(inc, (uint32_t)__popcll(has));
     };
     announce(0);
     // sum of front, and the scans of the lists and of this chunk's entries
@@ -561,24 +669,25 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
     const uint32_t sinc = wave_inclusive_scan(sum), minc = wave_inclusive_scan(msum);
     front = wave_sum(front);
     if (lane == kWave - 1) {
-        sh.s.part[0][wv] = sinc;
-        sh.s.part[1][wv] = minc;
-        sh.s.part[2][wv] = front;
+        s.part[0][wv] = sinc;
+        s.part[1][wv] = minc;
+        s.part[2][wv] = front;
     }
     __syncthreads();
     uint32_t e = sinc - sum, le = minc - msum, entries = 0;
 #pragma unroll
     for (int v = 0; v < NW; v++) {
-        e += (v < wv ? sh.s.part[0][v] : 0u) + sh.s.part[2][v];
-        le += v < wv ? sh.s.part[1][v] : 0u;
-        entries += sh.s.part[1][v];
+        e += (v < wv ? s.part[0][v] : 0u) + s.part[2][v];
+        le += v < wv ? s.part[1][v] : 0u;
+        entries += s.part[1][v];
     }
-    const bool staged = entries <= (uint32_t)kBinStage && a.chunk_splats <= 1 << kBinLocalBits;
+    const bool whose = entries <= (uint32_t)kBinStage;   // this workgroup's to write
+    const bool staged = whose && a.chunk_splats <= 1 << kBinLocalBits;
     // c becomes what takes a staged position to that in the list
 #pragma unroll
     for (int j = 0; j < kPer; j++) {
         const int k = kPer * t + j;
-        if (k < w.nt) sh.s.cur[k] = staged ? le : e + row[j];
+        if (k < w.nt) s.cur[k] = staged ? le : e + row[j];
         const uint32_t len = c[j];
         c[j] = e + row[j] - le;
         e += len;
@@ -591,39 +700,34 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
     const uint32_t idc = (uint32_t)((size_t)w.view * a.n + begin);   // the chunk's first view-Gaussian
     uint32_t at = before;
     int parity = 0;
-    for (int i0 = begin; i0 < end; i0 += NT, parity ^= 1) {
+    for (int i0 = begin; i0 < (whose || first ? end : begin); i0 += NT, parity ^= 1) {
         const int i = i0 + t;
         uint32_t total = 0, nj = 0, e0 = inc - mine, j = (uint32_t)__popcll(has & ((1ull << lane) - 1ull));
 #pragma unroll
         for (int v = 0; v < NW; v++) {
-            const uint2 q = sh.s.pack[parity][v];
+            const uint2 q = s.pack[parity][v];
             e0 += v < wv ? q.x : 0u;
             j += v < wv ? q.y : 0u;
             total += q.x;
             nj += q.y;
         }
         const uint32_t per = (total + NT - 1) / NT;
-        if (t == 0) sh.s.off[nj] = total;
-        if (mine > 0) {
-            sh.s.off[j] = e0;
-            sh.s.rect[j] = make_uint2((uint32_t)r.x0 | (uint32_t)(r.x1 - r.x0) << 16, (uint32_t)r.y0 | (uint32_t)t << 16);
-            // the threads whose shares start in this splat's entries
-            for (uint32_t q = (e0 + per - 1) / per; q * per < e0 + mine; q++) sh.s.start[q] = (uint16_t)j;
-        }
+        if (t == 0) s.off[nj] = total;
+        bin_pack(s, r, mine, e0, j, per);
         const uint32_t splat_full = full;
         __syncthreads();
         p = bin_fetch(a, w, i + NT, end);
         const uint32_t j0 = (uint32_t)(i0 - begin);
         if (staged)
-            bin_walk(sh.s, cols, total, per, [&](uint32_t pos, uint32_t k, uint32_t tile) {
-                sh.s.entry[pos] = tile << kBinLocalBits | (j0 + k);
+            bin_walk(s, cols, total, per, [&](uint32_t pos, uint32_t k, uint32_t tile) {
+                s.entry[pos] = tile << kBinLocalBits | (j0 + k);
             });
-        else
-            bin_walk(sh.s, cols, total, per, [&](uint32_t pos, uint32_t k, uint32_t) {
+        else if (whose)
+            bin_walk(s, cols, total, per, [&](uint32_t pos, uint32_t k, uint32_t) {
                 a.pairs[pos] = make_uint2(a.depth[idc + j0 + k], idc + j0 + k);
             });
         if (first) {
-            if (!whole) e0 = block_exclusive_scan<uint32_t, NT>(splat_full, sh.s.scratch, &total);
+            if (!whole) e0 = block_exclusive_scan<uint32_t, NT>(splat_full, s.scratch, &total);
             e0 += at;
             at += total;
             if (i < end) {
@@ -648,12 +752,12 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
     if (staged) {
 #pragma unroll
         for (int j = 0; j < kPer; j++)
-            if (kPer * t + j < w.nt) sh.s.cur[kPer * t + j] = c[j];
+            if (kPer * t + j < w.nt) s.cur[kPer * t + j] = c[j];
         __syncthreads();
 #pragma unroll 4
         for (uint32_t k = t; k < entries; k += NT) {
-            const uint32_t x = sh.s.entry[k], id = idc + (x & ((1u << kBinLocalBits) - 1u));
-            a.pairs[sh.s.cur[x >> kBinLocalBits] + k] = make_uint2(a.depth[id], id);
+            const uint32_t x = s.entry[k], id = idc + (x & ((1u << kBinLocalBits) - 1u));
+            a.pairs[s.cur[x >> kBinLocalBits] + k] = make_uint2(a.depth[id], id);
         }
     }
     if (first) {   // the flags of the chunk's slots
@@ -664,6 +768,25 @@ __global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, V
             *reinterpret_cast<uint4 *>(a.slot_flags + k) = make_uint4(0, 0, 0, 0);
         for (unsigned long long k = v1 + t; k < f1; k += NT) a.slot_flags[k] = 0;
     }
+}
+
+// Workgroup 0 orders the tiles; the others write a chunk's entries in a window
+// each, and then share out the pieces of the heavy chunks.
+__global__ __launch_bounds__(kBinScatterThreads) void k_bin_scatter(BinArgs a, ViewsK views) {
+    __shared__ union {
+        OrderShared o;
+        ScatterShared s;
+    } sh;
+    const bool ovf = a.counters[kCntOverflow] != 0u;
+    if (blockIdx.x == 0) {
+        bin_order(a, sh.o, ovf);
+        return;
+    }
+    int wi, chunk;
+    bin_block(a, blockIdx.x - 1, wi, chunk);
+    const uint32_t pieces = a.counters[kCntPieces], heavy = a.counters[kCntHeavy];
+    if (chunk < a.chunks) bin_chunk(a, views, sh.s, wi, chunk, ovf);
+    if (!ovf && pieces > 0u) bin_pieces(a, views, sh.s, pieces, heavy);
 }
 
 static BinArgs bin_args(const ViewsK &views, const Layout &L, char *ws) {
@@ -686,6 +809,12 @@ static BinArgs bin_args(const ViewsK &views, const Layout &L, char *ws) {
     a.pairs = region<uint2>(ws, L.pairs);
     a.slot_flags = region<uint8_t>(ws, L.slot_flags);
     a.cap = (unsigned long long)L.cap;
+    // a heavy chunk has more than kBinStage instances of the capacity's, which
+    // bring 36 bytes of slots each: room for its counts and its record
+    static_assert(36ll * kBinStage >= 4 * kBinTiles + 16, "a heavy chunk's share of the slots");
+    a.max_heavy = (uint32_t)(L.cap / (kBinStage + 1));
+    a.written = region<uint32_t>(ws, L.slots);
+    a.heavy = reinterpret_cast<uint4 *>(a.written + (size_t)a.max_heavy * kBinTiles);
     a.n = (int)L.n;
     a.V = L.V;
     a.chunks = L.bin_chunks;

@@ -35,8 +35,10 @@ constexpr int kPreprocessBlock = 256;    // Gaussians per preprocess block
 // what whole eights of chunks leave over): two rounds, or as many as it takes that
 // the chunks of the largest window, by its share of the capacity (1.25 to 1.5
 // times the instances), stay in LDS (kBinStage entries, binning.hip).  A view has
-// at most 248, and fewer where they would hold less than 256 splats (a workgroup's
-// fixed work is a few microseconds, and every chunk has a count per tile).
+// at most 248, and fewer where they would hold less than 256 splats and less than
+// 8192 instances, again by the capacity (a workgroup's fixed work is a few
+// microseconds, and every chunk has a count per tile; 30 splats over a whole 1008 x
+// 756 view took 63 us in one chunk).
 // Windows counted like views keep the counts of a large image small: at 16384 x
 // 16384 (256 windows, 200k splats, 19.7M instances) 3 chunks and 13 MB instead of
 // 248 and 1 GB, and the three kernels take 2.3 ms instead of 4.0.
@@ -46,8 +48,9 @@ inline int bin_chunks_for(int64_t n, int64_t cap, int64_t windows, double window
     const int64_t rounds = (int64_t)(need * (double)windows / kBinChunks) + 1;
     int64_t c = kBinChunks * (rounds < 2 ? 2 : rounds) / windows;
     if (c < 1) c = 1;
-    const int64_t by_n = (n + 255) / 256;
-    if (c > by_n) c = by_n;
+    const int64_t by_n = (n + 255) / 256, by_cap = (int64_t)((double)cap * window_share / 8192.0);
+    const int64_t most = by_n > by_cap ? by_n : (by_cap < n ? by_cap : n);
+    if (c > most) c = most;
     return (int)(c < kBinChunks ? c : kBinChunks);
 }
 // Windows of a view of gw x gh tiles (binning.hip).
@@ -136,10 +139,13 @@ struct Layout {
 // kCntSticky keeps the OR of every overflow since the workspace was zeroed;
 // kCntWin is the number of work windows of this call; kCntItems the number of
 // backward work items; kCntOver1024 and kCntOver2048 the numbers of tile lists
-// longer than that.
+// longer than that; kCntPieces and kCntHeavy (one 64-bit word) the numbers of
+// pieces of heavy chunks in the binning and of those chunks, and kCntNextPiece the
+// pieces taken so far (all three cleared by the preprocess).
 enum Counter : int {
     kCntMLo = 0, kCntMHi = 1, kCntOverflow = 2, kCntMEff = 3, kCntSticky = 4, kCntWin = 5,
-    kCntItems = 6, kCntOver1024 = 7, kCntOver2048 = 8, kCntCount = 16
+    kCntItems = 6, kCntOver1024 = 7, kCntOver2048 = 8, kCntPieces = 10, kCntHeavy = 11, kCntNextPiece = 12,
+    kCntCount = 16
 };
 
 Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views, int64_t cap);

@@ -27,6 +27,7 @@ struct PreArgs {
     uint2 *rect;                   // [vn]: x0 | y0 << 16, x1 | y1 << 16
     uint32_t *depth;               // [vn]: float bits of the key depth
     uint32_t *tiles;               // [vn]: tiles touched
+    uint32_t *counters;
 };
 
 template <int D>
@@ -35,6 +36,7 @@ __global__ __launch_bounds__(kPreprocessBlock) void k_preprocess(PreArgs a, View
     const int n = a.g.n;
     const int i = blockIdx.x * kPreprocessBlock + threadIdx.x;
     const bool valid = i < n;
+    if (i == 0) a.counters[kCntPieces] = a.counters[kCntHeavy] = a.counters[kCntNextPiece] = 0u;
 
     double mu[3] = {0, 0, 0};
     double Sig[6] = {0, 0, 0, 0, 0, 0};  // xx xy xz yy yz zz
@@ -186,6 +188,7 @@ hipError_t launch_preprocess(const GaussiansK &g, const ViewsK &views, const flo
     a.rect = region<uint2>(ws, L.rect);
     a.depth = region<uint32_t>(ws, L.depth);
     a.tiles = region<uint32_t>(ws, L.tiles);
+    a.counters = region<uint32_t>(ws, L.counters);
     dim3 grid(L.nblk_pre), block(kPreprocessBlock);
     switch (g.sh_degree) {
         case 0: hipLaunchKernelGGL(k_preprocess<0>, grid, block, 0, s, a, views); break;

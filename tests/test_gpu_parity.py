@@ -209,6 +209,47 @@ def test_binning_bit_exact(n, sizes, scale):
                               oracle.tile_ranges(rkeys, sum(w * h for w, h in grids)))
 
 
+# chunks with more entries than a workgroup stages, shared out in pieces: large
+# splats that neighbour each other in front of, behind and among small ones, in one
+# window of tiles, in several (more than 4096 tiles) and in views of several sizes;
+# a capacity that the instances fill exactly, and one instance less
+@pytest.mark.parametrize("n,big,at,sizes", [
+    (20000, 40, 0, [(1008, 756)]), (20000, 40, 19960, [(1008, 756)]), (3000, 17, 1500, [(1040, 1030)]),
+    (9000, 30, 100, [(640, 480), (1040, 1030), (200, 100)]), (40, 40, 0, [(1008, 756)]), (1, 1, 0, [(1040, 1030)])])
+@pytest.mark.parametrize("cap", ["margin", "exact", "short"])
+def test_binning_of_heavy_chunks_bit_exact(n, big, at, sizes, cap):
+    cams = [f32_camera(S.Camera(w, h, 0.9 * w, 0.9 * w, 0.5 * w, 0.5 * h)) for w, h in sizes]
+    sc = S.random_scene(n + 7, n, 0, cams[0], depth=(0.5, 6.0), log_scale=(np.log(0.002), np.log(0.02)))
+    rng = S.rng_for(n + 7, 8)
+    sc.means[at:at + big, :2] *= 0.2
+    sc.scales[at:at + big] = rng.uniform(4.0, 30.0, (big, 3))
+    poses = [S.random_pose_near_identity(n + k, 3.0, 0.1) for k in range(len(cams))]
+    refs = [oracle.preprocess(sc, c, p) for c, p in zip(cams, poses)]
+    M = oracle.count_instances(refs)
+    fragile = np.concatenate([np.nonzero(r["fragile"])[0] + k * n for k, r in enumerate(refs)])
+    if cap == "margin":
+        run = _gpu(sc, cams, poses, cap=int(1.5 * M) + 4096)
+        M = run["rast"].instances()[0]
+    else:
+        M = _gpu(sc, cams, poses)["rast"].instances()[0]
+        g = R.GaussianParams.from_set(sc, DEV)
+        rast = R.Rasterizer(0, capacity=M - (cap == "short"))
+        for _ in range(2):   # (and on a workspace that holds a forward already)
+            rast.forward(g, cams, torch.tensor(np.stack(poses), device=DEV, dtype=torch.float32), check=False)
+        run = {"rast": rast, "g": g}
+    assert run["rast"].instances() == (M, cap == "short")
+    insp = lambda name: run["rast"].inspect(run["g"], cams, name, torch.int32).cpu().numpy().view(np.uint32)
+    if cap == "short":
+        assert not insp("ranges").any()
+        return
+    grids = [oracle.tiles_of(c) for c in cams]
+    rkeys, rvals = oracle.bin_sort(refs, grids)
+    keys, vals = _sorted_instances(run["rast"], run["g"], cams, M)
+    assert_sorted_match(keys, vals, rkeys, rvals, fragile.astype(np.uint32))
+    tiles = insp("tiles").astype(np.int64)
+    assert np.array_equal(insp("offsets"), (np.cumsum(tiles) - tiles).astype(np.uint32))
+
+
 # one tile: list lengths at the edges of the per-tile sort's kernels (1024 or
 # 2048 entries by the capacity, 8192, beyond), with depths spread evenly,
 # crowded in two thin layers, crowded in layers of a few values (equal depths),

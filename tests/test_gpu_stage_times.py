@@ -72,3 +72,23 @@ def test_binning_of_many_small_views():
     us = [_stage_us(g, cam, ["duplicate", "ranges", "tile_sort"], views) for views in (1, 32)]
     print(f"binning: one view {us[0]:.1f}, 32 views {us[1]:.1f} us")
     assert us[1] < 2.0 * us[0]
+
+
+@pytest.mark.parametrize("first", [True, False])
+def test_binning_of_neighbouring_large_splats(first):
+    """300 splats over the whole view, in front of or behind 100k small ones: next
+    to each other and spread over the scene."""
+    w, h, f, n, big = 1008, 756, 815.0, 100_000, 300
+    rng = S.rng_for(4, 8)
+    z = rng.uniform(1.5, 8.0, n)
+    means = np.stack([rng.uniform(-0.6, 0.6, n) * z, rng.uniform(-0.45, 0.45, n) * z, z], 1)
+    scales = np.exp(rng.uniform(np.log(0.01), np.log(0.05), (n, 3)))
+    at = slice(0, big) if first else slice(n - big, n)
+    means[at, :2] *= 0.2
+    scales[at] = 5.0
+    cam = S.Camera(w, h, f, f, w / 2, h / 2)
+    us = []
+    for order in (np.arange(n), rng.permutation(n)):
+        us.append(_stage_us(_params(means[order], scales[order], 0.02), cam, ["duplicate", "ranges", "tile_sort"]))
+    print(f"binning: together {us[0]:.1f}, spread {us[1]:.1f} us")
+    assert us[0] < 4.0 * us[1]
