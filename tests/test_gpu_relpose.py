@@ -71,6 +71,34 @@ def test_neighbour_search_matches_oracle(w, h, kind):
     assert np.max(np.abs(raw.log_scales.cpu().numpy() - ref["log_scales"])) <= 1e-5
 
 
+# where most blocks of pixels can hold a neighbour of most points, all pairs are
+# tested: depths over forty octaves pixel by pixel, few valid points, none; more
+# points than two and a half blocks' and fewer than 128 open ones in some blocks
+@pytest.mark.parametrize("w,h", [(32, 8), (64, 16), (101, 67), (160, 40), (33, 90)])
+@pytest.mark.parametrize("kind", ["octaves", "sparse", "none", "one"])
+def test_neighbour_search_by_all_pairs(w, h, kind):
+    rng = np.random.default_rng(w * h)
+    cam = S.Camera(w, h, 0.9 * w + 7.0, 0.8 * w + 9.0, 0.4 * w, 0.55 * h)
+    depth = np.exp2(rng.uniform(-20, 20, (h, w))) if kind == "octaves" else np.full((h, w), 3.0)
+    valid = {"octaves": rng.random((h, w)) < 0.97, "sparse": rng.random((h, w)) < 0.02, "none": np.zeros((h, w), bool),
+             "one": np.arange(w * h).reshape(h, w) == w * h // 2}[kind]
+    depth = np.where(valid, depth, rng.choice([0.0, -1.0, np.inf, np.nan], (h, w))).astype(np.float32)
+    image = rng.uniform(0, 1, (3, h, w)).astype(np.float32)
+    raw = RP.unproject(cam, torch.tensor(depth, device=DEV), torch.tensor(image, device=DEV), 1)
+    m = raw.means.cpu().numpy().astype(np.float64)
+    ok = valid.ravel()
+    d2 = np.full((len(m), int(ok.sum())), np.inf)
+    for c0 in range(0, len(m), 512):
+        d2[c0:c0 + 512] = ((m[c0:c0 + 512, None, :] - m[ok][None]) ** 2).sum(-1)
+    d2[np.nonzero(ok)[0], np.arange(int(ok.sum()))] = np.inf
+    near = np.sqrt(np.sort(np.pad(d2, ((0, 0), (0, 3)), constant_values=np.inf), axis=1)[:, :3])
+    found = np.isfinite(near)
+    mean = np.where(found, near, 0.0).sum(1) / np.maximum(found.sum(1), 1)
+    ref = np.log(np.where(found.any(1), mean, 0.01))
+    # the float32 differences, their squares and the sum are within a few 2^-24
+    assert np.max(np.abs(raw.log_scales.cpu().numpy() - ref[:, None])) <= 3e-6 * max(1.0, np.abs(ref).max())
+
+
 def test_masked_l1_matches_oracle():
     sc, cam, pose = random_case(41, 1, 90, 70, 3000)
     g = R.GaussianParams.from_set(sc, DEV)

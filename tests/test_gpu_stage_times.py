@@ -92,3 +92,33 @@ def test_binning_of_neighbouring_large_splats(first):
         us.append(_stage_us(_params(means[order], scales[order], 0.02), cam, ["duplicate", "ranges", "tile_sort"]))
     print(f"binning: together {us[0]:.1f}, spread {us[1]:.1f} us")
     assert us[0] < 4.0 * us[1]
+
+
+@pytest.mark.parametrize("kind,factor", [("none", 30.0), ("octaves", 170.0)])
+def test_unprojection_without_near_neighbours(kind, factor):
+    """A frame without any depth, and one whose depths are spread over forty octaves
+    pixel by pixel, against a smooth one."""
+    from paper_2410_08743_amd import relpose as RP
+    w, h = 1200, 680
+    cam = S.Camera(w, h, 600.0, 600.0, w / 2, h / 2)
+    image = torch.rand(3, h, w, device=DEV)
+    y, x = torch.meshgrid(torch.arange(h, device=DEV), torch.arange(w, device=DEV), indexing="ij")
+    smooth = (3.0 + 0.001 * x + 0.002 * y).contiguous()
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    depth = {"none": torch.zeros(h, w, device=DEV),
+             "octaves": torch.exp2(40 * torch.rand(h, w, device=DEV, generator=gen) - 20)}[kind]
+    us = []
+    R.profile_enable(0, R.PROFILE_TIMING)
+    try:
+        for d in (depth, smooth):
+            best = np.inf
+            R.profile_read(0)
+            for _ in range(8):
+                RP.unproject(cam, d, image, 4)
+                best = min(best, 1e3 * R.profile_read(0)["unproject"][1])
+            us.append(best)
+    finally:
+        R.profile_enable(0, 0)
+    print(f"unproject: {kind} {us[0]:.1f}, smooth {us[1]:.1f} us")
+    assert us[0] < factor * us[1]
