@@ -229,6 +229,7 @@ Layout make_layout(int64_t n, int32_t sh_degree, int32_t V, const ViewsK &views,
     L.chunkstart = take((size_t)V * L.bin_chunks * 4);
     L.pairs = take(capz * 8);
     L.vals = take(capz * 4);
+    L.keys = take(capz * 4);
     L.ranges = take((size_t)L.total_tiles * 8);
     L.tile_order = take((size_t)L.total_tiles * 4);
     // Every chunk in front of a cut holds kChunk entries, so there are at
@@ -631,7 +632,7 @@ gsp_status gsp_inspect(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gs
         {"depth", L.depth, L.vn},
         {"tiles", L.tiles, L.vn},
         {"offsets", L.offsets, L.vn},
-        {"keys", L.pairs, L.cap},
+        {"keys", L.keys, L.cap},
         {"values", L.vals, L.cap},
         {"ranges", L.ranges, L.total_tiles},
         {"tfinal", L.tfinal, L.total_pix},
@@ -643,14 +644,6 @@ gsp_status gsp_inspect(gsp_ctx *ctx, const gsp_gaussians *g, int32_t V, const gs
     };
     for (const Entry &en : table) {
         if (std::strcmp(en.n, name) == 0) {
-            if (en.off == L.pairs) {
-                // the instances carry no tile id: written now, from the
-                // ranges that whatever stream filled
-                hipError_t e = hipDeviceSynchronize();
-                if (e == hipSuccess) e = gsp::launch_tile_ids(L, ws, nullptr);
-                if (e == hipSuccess) e = hipDeviceSynchronize();
-                if (e != hipSuccess) return hip_fail(e, "tile ids");
-            }
             *ptr = ws + en.off;
             *count = en.cnt;
             return GSP_OK;

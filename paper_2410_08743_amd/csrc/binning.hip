@@ -849,17 +849,4 @@ hipError_t launch_bin_scatter(const ViewsK &views, const Layout &L, char *ws, hi
     return hipGetLastError();
 }
 
-// Tile id of every instance, for inspection: the pairs are free by then.
-__global__ __launch_bounds__(256) void k_tile_ids(const uint2 *ranges, uint32_t *ids) {
-    const uint2 r = ranges[blockIdx.x];
-    for (uint32_t k = r.x + threadIdx.x; k < r.y; k += 256) ids[k] = blockIdx.x;
-}
-
-hipError_t launch_tile_ids(const Layout &L, char *ws, hipStream_t s) {
-    if (L.total_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_ids, dim3(L.total_tiles), dim3(256), 0, s, region<uint2>(ws, L.ranges),
-                       region<uint32_t>(ws, L.pairs));
-    return hipGetLastError();
-}
-
 }  // namespace gsp

@@ -128,7 +128,7 @@ struct Layout {
     int32_t V, S, total_tiles, nblk_pre, bin_chunks, bin_chunk_splats, nwin_max;
     size_t geom, color, rect, depth, tiles, offsets, wstart, counters;
     size_t binmat, tiletotal, groupsum, chunksum, chunkstart;   // counts of the binning
-    size_t pairs, vals, ranges, tile_order;
+    size_t pairs, vals, keys, ranges, tile_order;
     size_t items, ckpt, cfinal;   // backward work items, states at the cuts, final colours
     int64_t max_items;
     size_t tfinal, ncontrib, tile_last, stats, slots, slot_flags, grad2d, posepart, l1part;
@@ -184,8 +184,6 @@ hipError_t launch_preprocess(const GaussiansK &g, const ViewsK &views, const flo
 hipError_t launch_bin_count(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
 hipError_t launch_bin_scan(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
 hipError_t launch_bin_scatter(const ViewsK &views, const Layout &L, char *ws, hipStream_t s);
-// Writes the tile id of every sorted instance over the pairs region.
-hipError_t launch_tile_ids(const Layout &L, char *ws, hipStream_t s);
 // sort.hip
 hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s);
 // raster_fwd.hip

@@ -47,6 +47,7 @@ struct TileDepthArgs {
     uint2 *pairs;               // (depth key, value) of the instances, grouped by tile
     uint2 *spare;               // [cap] scratch of the radix sort
     uint32_t *vals;             // the values in (tile, depth, value) order
+    uint32_t *keys;             // the tile of each of them
     const uint32_t *counters;
     int short_cap;              // longest run of the kernel over all tiles
 };
@@ -602,6 +603,14 @@ __device__ __forceinline__ void td_sort_global(const TileDepthArgs &a, TdShared<
     __syncthreads();
 }
 
+// The tile of each entry of a run: for inspection alone (4 bytes per instance, 10 of
+// 83 us at 15.4M of them), but written here, where every forward of a stream or a
+// graph has it in its order.
+template <int THREADS>
+__device__ __forceinline__ void td_keys(const TileDepthArgs &a, uint32_t tile, const uint2 &rg) {
+    for (uint32_t k = rg.x + threadIdx.x; k < rg.y; k += THREADS) a.keys[k] = tile;
+}
+
 // Workgroup b takes tile b, so that its first load is its range.  An
 // overflowing forward emits no instance and leaves every range empty, so
 // neither kernel needs an overflow test.
@@ -613,6 +622,7 @@ __global__ __launch_bounds__(THREADS) void k_tile_depth_sort(TileDepthArgs a) {
     if (L < 1 || L > THREADS * ROUNDS) return;
     const int t = threadIdx.x;
     td_sort_lds(a, sh, t, rg.x, L);
+    td_keys<THREADS>(a, blockIdx.x, rg);
 }
 
 // The longer runs, at the front of the launch order.
@@ -621,13 +631,15 @@ __global__ __launch_bounds__(kTdLongThreads) __attribute__((amdgpu_waves_per_eu(
     __shared__ TdShared<kTdLongThreads, kTdLongRounds> sh;
     const uint32_t nlong = a.counters[a.short_cap == 1024 ? kCntOver1024 : kCntOver2048];
     for (uint32_t r = blockIdx.x; r < nlong; r += gridDim.x) {
-        const uint2 rg = a.ranges[a.order[r]];
+        const uint32_t tile = a.order[r];
+        const uint2 rg = a.ranges[tile];
         const int L = (int)(rg.y - rg.x);
         int t = threadIdx.x;
         asm volatile("" : "+v"(t));
         __syncthreads();
         if (L > kTdLongThreads * kTdLongRounds) td_sort_global(a, sh, t, rg.x, L);
         else td_sort_lds(a, sh, t, rg.x, L);
+        td_keys<kTdLongThreads>(a, tile, rg);
     }
 }
 
@@ -641,6 +653,7 @@ hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s) {
     static_assert(9 * 4 * kSplitBwd >= 8, "a slot holds a pair");
     a.spare = region<uint2>(ws, L.slots);
     a.vals = region<uint32_t>(ws, L.vals);
+    a.keys = region<uint32_t>(ws, L.keys);
     a.counters = region<uint32_t>(ws, L.counters);
     // Lists longer than 1024 on average (at the 1.5x capacity margin) take
     // eight entries per thread, which keep them in this launch; for lists of

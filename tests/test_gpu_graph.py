@@ -3,6 +3,8 @@ captured once in a HIP graph and replayed: every replay must give the same
 pose as the eager step it stands for.  The library's kernels allocate
 nothing and clear buffers with kernels (no memset nodes), so the step is
 capturable as is."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -85,3 +87,53 @@ def test_graph_replayed_solve_equals_eager_solve(views, masked):
     graphed = R.solve_poses(g, [cam] * views, targets, inits, steps=30, masked=masked, graph=True)
     assert torch.equal(eager, graphed)
     assert not torch.equal(eager, inits)
+
+
+def _keys(rast, g, cam):
+    """The tile ids of the last forward, as the region of the workspace that
+    gsp_inspect names (no copy)."""
+    p, cnt = ctypes.c_void_p(), ctypes.c_int64()
+    gs, views = g.struct(), R.N.view_array([cam])
+    nbytes = rast._ws_bytes(g.n, g.sh_degree, views, rast.capacity)
+    R.N.check(R.N.lib().gsp_inspect(R.context(0), ctypes.byref(gs), 1, views, R._ptr(rast.ws), nbytes, rast.capacity,
+                                    b"keys", ctypes.byref(p), ctypes.byref(cnt)), "gsp_inspect")
+    off = p.value - rast.ws.data_ptr()
+    return rast.ws[off:off + 4 * cnt.value].view(torch.int32)
+
+
+def _expected_keys(rast, g, cam):
+    rg = rast.inspect(g, [cam], "ranges", torch.int32).cpu().numpy().view(np.uint32).reshape(-1, 2)
+    return np.repeat(np.arange(len(rg), dtype=np.int32), (rg[:, 1] - rg[:, 0]).astype(np.int64))
+
+
+def test_inspected_keys_follow_every_forward():
+    """gsp_inspect names a region; what lies there is the last forward's."""
+    wl = S.tiny()
+    cam = wl.camera
+    g = R.GaussianParams.from_set(wl.scene, DEV)
+    rast = R.Rasterizer(0)
+    pose = torch.tensor(wl.pose[None], device=DEV)
+    rast.forward(g, [cam], pose)
+    keys = _keys(rast, g, cam)
+    for p in (wl.pose, wl.init_pose):
+        rast.forward(g, [cam], torch.tensor(p[None], device=DEV), check=False)
+        ref = _expected_keys(rast, g, cam)
+        assert len(ref) == rast.instances()[0] and np.array_equal(keys[:len(ref)].cpu().numpy(), ref)
+
+
+def test_keys_are_inspected_while_a_stream_captures():
+    wl = S.tiny()
+    cam = wl.camera
+    g = R.GaussianParams.from_set(wl.scene, DEV)
+    st = _state(wl, g, cam)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        _step(g, cam, st)
+        keys = _keys(st["rast"], g, cam)
+    for _ in range(3):   # the pose moves from replay to replay
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = _expected_keys(st["rast"], g, cam)
+        assert len(ref) > 0 and np.array_equal(keys[:len(ref)].cpu().numpy(), ref)
