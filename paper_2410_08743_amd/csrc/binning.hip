@@ -68,7 +68,7 @@ struct BinArgs {
     uint2 *ranges;                 // [total_tiles]
     uint32_t *order, *items;       // launch order of the tiles, backward work items
     uint2 *pairs;                  // [cap] (depth key, view * n + i) of each instance
-    uint8_t *slot_flags;           // [cap][kSplitBwd], cleared here for slots < M
+    uint8_t *slot_flags;           // [cap], cleared here for slots < M
     unsigned long long cap;
     int n, V, chunks, chunk_splats, total_tiles, groups;
     // chunks with more entries in a window than a workgroup stages: first piece,
@@ -761,7 +761,7 @@ __device__ __forceinline__ void bin_chunk(const BinArgs &a, const ViewsK &views,
         }
     }
     if (first) {   // the flags of the chunk's slots
-        const unsigned long long f0 = (unsigned long long)kSplitBwd * before, f1 = (unsigned long long)kSplitBwd * at;
+        const unsigned long long f0 = before, f1 = at;
         const unsigned long long v0 = min((f0 + 15) & ~15ull, f1), v1 = max(f1 & ~15ull, v0);
         for (unsigned long long k = f0 + t; k < v0; k += NT) a.slot_flags[k] = 0;
         for (unsigned long long k = v0 + 16ull * t; k < v1; k += 16ull * NT)

@@ -69,14 +69,12 @@ constexpr int kPoseRowsPerBlock = kPoseReduceBlock / 64;
 #endif
 constexpr int kWindow = GSP_WINDOW;
 constexpr int kWindowThreads = 256;
-// Wavefronts per 16 x 16 tile in the forward rasterizer (one per 8 x 8
-// quadrant), and 9-float gradient slots per instance: one, since the backward
-// takes whole tiles (one wave, four pixels per lane): its chunked work
-// items already fill the chip, and one wave per entry reduces the nine sums
-// once instead of once per strip and halves the slots (measured: two strips
-// 0.544 ms, whole tiles 0.503 ms per single-view step).
+// Wavefronts per 16 x 16 tile in the forward rasterizer: one per 8 x 8 quadrant.
+// (The backward takes whole tiles, one wave with four pixels per lane, and an
+// instance has one 9-float gradient slot: the chunked work items already fill the
+// chip, and the nine sums of an entry are reduced once.  Two strips per tile
+// measured 0.544 ms against 0.503 per single-view step.)
 constexpr int kSplitFwd = 4;
-constexpr int kSplitBwd = 1;
 // Backward work items: a tile's list longer than kChunk entries is cut at
 // multiples of kChunk into at most kMaxChunks chunks (the last one takes the
 // rest), each walked by its own workgroups, so that no work item is long

@@ -650,7 +650,6 @@ hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s) {
     a.order = region<uint32_t>(ws, L.tile_order);
     a.pairs = region<uint2>(ws, L.pairs);
     // the gradient slots (36 bytes per instance) are the backward's
-    static_assert(9 * 4 * kSplitBwd >= 8, "a slot holds a pair");
     a.spare = region<uint2>(ws, L.slots);
     a.vals = region<uint32_t>(ws, L.vals);
     a.keys = region<uint32_t>(ws, L.keys);
