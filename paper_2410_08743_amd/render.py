@@ -23,11 +23,17 @@ def _ptr(t):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(None)
 
 
+# The current stream's handle alone: 0.4 us where making a Stream object takes 3
+# (four times a step through autograd, whose host path bounds small scenes: 328 ->
+# 297 us for 20k splats at 589 x 440).  The function is not part of torch's public
+# interface: without it, the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the current stream's handle alone: 0.4 us where making a Stream object takes 3
-    # (four times a step through autograd, whose host path bounds small scenes:
-    # 328 -> 297 us for 20k splats at 589 x 440)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 _contexts = {}
