@@ -469,14 +469,14 @@ void k_raster_bwd(BwdArgs a, ViewsK views) {
     if (npend > 0) flush();
 }
 
-// Launches of more tiles than this take the MANY shape: -5 % over 4 views of
-// 1008 x 756 and 1M splats (764 -> 730 us), -5 % over 8 views of three sizes
-// (955 -> 905 us), and of whole pose steps -1.7 % for 5376 tiles (8 of 480 x
-// 336), -1.6 % for 4800, -0.8 % for 3600, within 1 % either way for 6048.  Fewer
-// tiles lose: +2 % for 3024 (a step at 1008 x 756), +3 % for 1200, +8 % of the
-// kernel at 128 x 128, and +5 to 8 % where few tiles have lists so long that
-// their last chunks run alone (8 views of 320 x 240 with 1M splats).
-constexpr int kManyTiles = 4096;
+// Launches of more tiles than this take the MANY shape.  Time of the kernel in it
+// against the other: 0.95 to 0.98 for 4800 to 12096 tiles (one to eight views),
+// 0.97 to 1.00 for 3750 to 3888, 0.99 to 1.00 for 3312, 1.00 to 1.03 for 3024 (a
+// view of 1008 x 756) and 3225 (1200 x 680), and 1.04 to 1.09 for 300 and 64, where
+// a few work items run alone for much of the launch.  Between 1200 and 3000 tiles
+// it goes by the lists more than by the tiles (0.96 to 1.03: eight views of 320 x
+// 240 0.97, one of 640 x 480 0.96 to 1.08), which the host does not know.
+constexpr int kManyTiles = 3584;
 
 hipError_t launch_raster_bwd(const ViewsK &views, const Layout &L, char *ws, const uint32_t *vals,
                              bool want_opacity, hipStream_t s) {

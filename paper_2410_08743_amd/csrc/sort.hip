@@ -654,12 +654,13 @@ hipError_t launch_tile_depth_sort(const Layout &L, char *ws, hipStream_t s) {
     a.vals = region<uint32_t>(ws, L.vals);
     a.keys = region<uint32_t>(ws, L.keys);
     a.counters = region<uint32_t>(ws, L.counters);
-    // Lists longer than 1024 on average (at the 1.5x capacity margin) take
-    // eight entries per thread, which keep them in this launch; for lists of
-    // 500 four per thread measured 15.8 us against 16.3, of 700 42.8 against
-    // 45.4 us (and 128 threads of eight 15.5 and 46.9 us), before the keys came
-    // with the values.
-    const bool mid = L.cap > (int64_t)1536 * L.total_tiles;
+    // Eight entries per thread keep lists of up to 2048 in this launch, where four
+    // leave those above 1024 to the long kernel: 1.1 times four's time for lists of
+    // 450 to 500 on average, 1.02 to 1.06 for 600 to 750, 1.01 for 800 and 900 in a
+    // few even tiles, but 0.75 for 860, 0.66 to 0.79 for 940 to 990 and 0.4 to 0.5
+    // above 1000, as the first lists pass 1024.  The instances' number is not known
+    // here; the line is at 850 for a capacity of 1.5 times as many.
+    const bool mid = L.cap > (int64_t)1280 * L.total_tiles;
     a.short_cap = mid ? 2048 : 1024;
     if (mid)
         hipLaunchKernelGGL((k_tile_depth_sort<256, 8>), dim3(L.total_tiles), dim3(256), 0, s, a);
