@@ -55,9 +55,11 @@ struct StagedB { float C2, lo, r, g; };
 struct StagedF { float b; uint32_t jp1; };
 struct StagedC { float b, inv_o; uint32_t slot, pm; };   // pm: list position
 
-// Row offset that marks a pixel as done: every splat's p2 there is -inf, so
-// the candidate test (p2 >= lim) fails without a separate flag.
-constexpr float kInactiveRow = 1e30f;
+// Row that marks a pixel as done: every splat's p2 there is -inf (alpha 0), +inf, or
+// not a number where the form has no extent in y (C2 = 0), and the tests on alpha and
+// on the power's sign fail without a separate flag.  Batches walked without the
+// latter have C2 < 0.
+constexpr float kInactiveRow = INFINITY;
 
 // Centre of a splat relative to pixel (px0, py0), from its (hi, lo) pair.
 __device__ __forceinline__ float rel_coord(float hi, float lo, int origin) {

@@ -401,6 +401,49 @@ def test_forward_at_quadrant_edges(size, kind):
     assert np.array_equal(nc.reshape(ok.shape)[ok], ref["n_contrib"][ok])
 
 
+def test_stopped_pixels_blend_no_splat_without_extent():
+    """A splat so large that its conic is zero in float32 has power 0 everywhere;
+    pixels that stopped in front of it do not blend it all the same, while their
+    neighbours, in the same quadrants, do.  (The oracle's radii are integers, too
+    small for it: the composite is formed here.)"""
+    w, h, f, n = 48, 32, 50.0, 40
+    cam = f32_camera(S.Camera(w, h, f, f, w / 2, h / 2))
+    rng = S.rng_for(5, 8)
+    z = np.concatenate([1.0 + 0.01 * np.arange(12), 2.0 + 0.1 * np.arange(28)]).astype(np.float32)
+    sc = S.random_scene(5, n, 0, cam)
+    sc.means[:] = 0.0
+    sc.means[:12, 0] = -0.25   # opaque, over the left part; the others lie behind it, everywhere
+    sc.means[:, 2] = z
+    sc.scales[:12] = [0.03, 0.6, 0.03]
+    sc.scales[12:] = 1e24
+    sc.quats[:] = [1.0, 0.0, 0.0, 0.0]
+    sc.opacities[:12] = 0.97
+    sc.opacities[12:] = rng.uniform(0.02, 0.4, 28)
+    run = _gpu(sc, [cam], [S.identity_pose()], up=[_upstream(5, cam)])
+    y, x = np.mgrid[0:h, 0:w].astype(np.float64)
+    T, last, done, near = np.ones((h, w)), np.zeros((h, w), int), np.zeros((h, w), bool), np.zeros((h, w), bool)
+    for k in range(n):
+        a = np.full((h, w), np.float64(sc.opacities[k]))
+        if k < 12:
+            m, s2, zz = sc.means[k].astype(np.float64), sc.scales[k].astype(np.float64) ** 2, np.float64(z[k])
+            J = np.array([[f / zz, 0, -f * m[0] / zz ** 2], [0, f / zz, -f * m[1] / zz ** 2]])
+            C = np.linalg.inv(J @ np.diag(s2) @ J.T + 0.3 * np.eye(2))
+            dx, dy = x - (f * m[0] / zz + w / 2 - 0.5), y - (f * m[1] / zz + h / 2 - 0.5)
+            a = a * np.exp(-0.5 * (C[0, 0] * dx * dx + C[1, 1] * dy * dy) - C[0, 1] * dx * dy)
+        near |= ~done & ((abs(255 * a - 1) < 1e-3) | (abs(T * (1 - a) / 1e-4 - 1) < 1e-3))
+        hit = ~done & (a >= 1 / 255)
+        done |= hit & (T * (1 - a) < 1e-4)
+        hit &= ~done
+        T = np.where(hit, T * (1 - a), T)
+        last = np.where(hit, k + 1, last)
+    ok = ~near
+    nc = run["rast"].inspect(run["g"], [cam], "ncontrib", torch.int32).cpu().numpy().reshape(h, w)
+    stopped = done & (last <= 12)
+    assert ok.mean() > 0.9 and (ok & stopped).sum() > 50 and (ok & ~done).sum() > 50
+    assert np.array_equal(nc[ok], last[ok])
+    assert np.max(np.abs((1 - run["alpha"].reshape(h, w) - T)[ok])) <= 1e-5
+
+
 @pytest.mark.parametrize("name", CASES)
 def test_backward_parity(name):
     sc, cam, pose = _case(name)
