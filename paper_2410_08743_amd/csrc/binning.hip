@@ -20,8 +20,8 @@
 // A radix sort by tile id (scan, emission, two passes of three kernels, ranges
 // and launch order: eleven launches that wrote and read every entry three
 // times) took 66 us at 1.5M instances in one 1008 x 756 view, 414 us at 15.4M
-// in four and 657 us at 22M in eight views; the three kernels here take 7.0 +
-// 5.0 + 16.3, 25 + 6 + 117 and 45 + 8 + 213 us.  The first is bound by latency
+// in four and 657 us at 22M in eight views; the three kernels here take 6.1 +
+// 5.0 + 15.2, 21 + 6 + 108 and 32 + 8 + 178 us.  The first is bound by latency
 // and its row atomics, the last by the LDS atomic, the depth's gather and the
 // scattered store that each entry takes.
 #include <cstring>
@@ -159,7 +159,8 @@ constexpr int kBinCountThreads = 512;
 // behind its last column in each of its rows, and a scan along the rows makes
 // counts of that: two LDS atomics per row of a splat instead of one per tile
 // found by a search (79 -> 25 us at 15.4M instances
-// of 4 x 1M splats, 10.1 -> 8.5 us at 1.5M).
+// of 4 x 1M splats, 10.1 -> 8.5 us at 1.5M; 21 and 6.1 since a workgroup finds its
+// window without a walk).
 __global__ __launch_bounds__(kBinCountThreads) void k_bin_count(BinArgs a, ViewsK views) {
     constexpr int NT = kBinCountThreads;
     __shared__ int diff[kBinTiles];
@@ -608,7 +609,7 @@ __device__ __forceinline__ void bin_pieces(const BinArgs &a, const ViewsK &views
 // Entries of the same tile are brought together in LDS first, so that a store
 // covers runs of them: written one by one, each would be a partial line of its
 // own wherever the lists being written exceed the L2 (190 -> 121 us at 15.4M
-// instances in 12096 lists; 97 -> 62 us at 6.7M in 9600).  A chunk with too many
+// instances in 12096 lists, 108 by now; 97 -> 62 us at 6.7M in 9600, now 47).  A chunk with too many
 // entries (neighbouring splats that are large: a scene in an order of its own)
 // leaves them to all workgroups, in pieces: 300 splats over a whole 1008 x 756 view
 // in front of 200k small ones take 56 us, and took 554 where that chunk's workgroup

@@ -45,7 +45,8 @@ __device__ __forceinline__ int rgb_view_of(const RgbViewsK &a, int tile) {
 // the column sums in LDS.  A horizontal item is a run of kSsimHRun outputs
 // of one row, read from LDS as aligned vectors.  Each output is still the
 // sum over the taps in tap order.  Only the column sums live in LDS (24 KB
-// for the forward's five moments), so five blocks fit a CU.
+// for the forward's five moments, room for six blocks on a CU; the registers, 81 and
+// 92, leave five).
 //
 // Bound by VALU issue: tiles whose halo lies inside the image (nearly all)
 // read at 32-bit offsets from one base and test no bounds, and the forward

@@ -30,9 +30,9 @@
 // bit-reproducible.
 //
 // Bound by VALU issue: the VALUs are busy 93 % of the time over 4 views of
-// 1008 x 756; 77 % over one, whose last items leave the chip half empty for the
-// last 40 of its 170 us (chunks of 64 entries shorten that, but cost 10 % more
-// over several views, whose items all read their pixels' state).
+// 1008 x 756; some 75 % over one, whose last items leave the chip half empty for
+// the last quarter of the kernel (chunks of 64 entries shorten that, but cost 10 %
+// more over several views, whose items all read their pixels' state).
 #include <cstring>
 #include <type_traits>
 
@@ -95,7 +95,7 @@ constexpr uint32_t kPadPos = 0xfffffffeu;
 // MANY chooses between two shapes of the same walk, with the same results: for
 // many tiles one entry per step and five pending entries, which fit 84
 // registers and 7.5 KB of LDS, five waves per SIMD; for few, where waves run
-// alone and latency counts, two entries per step and seven pending ones (113
+// alone and latency counts, two entries per step and seven pending ones (111
 // registers, 9.1 KB, four waves).  (The stored-list variant spills with either's
 // registers, and takes the first at four waves.)
 template <bool STORED, bool OPA, bool MANY>

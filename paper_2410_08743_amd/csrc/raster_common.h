@@ -36,9 +36,11 @@ constexpr int kUnroll = GSP_FWD_UNROLL;   // entries per step of the inner loop
 
 constexpr float kLn2 = 0.6931471805599453f;
 // A splat can reach alpha >= 1/255 at a pixel only if p2 + log2(o) is at least
-// log2(1/255); the 0.01 margin keeps the test (taken as p2 >= this - log2(o))
-// conservative with respect to v_exp_f32's and the subtraction's rounding, so
-// skipping on it never changes a decision.
+// log2(1/255).  Both rasterizers decide by alpha >= 1/255 and p2 <= 0; this is the
+// bound that entries are culled by (SplatForm) and the stored lists' walk tests
+// first, as p2 >= this - log2(o).  The 0.01 margin keeps it conservative with
+// respect to v_exp_f32's and the subtraction's rounding, so skipping on it never
+// changes a decision.
 constexpr float kLog2AlphaMinLoose = -7.994353436858858f - 0.01f;
 // log2 of an opacity that keeps every unclamped alpha of its splat below the
 // 0.99 clamp: exp2(-0.0155) = 0.98931, so with power <= 0 the alpha stays
@@ -100,9 +102,9 @@ __device__ __forceinline__ float splat_alpha_pre(float p2, float lo) {
 // A, C < 0 make it concave and largest at the edge's clamped stationary point
 // (this holds too where rounding left a long thin form indefinite, since a
 // pixel with p2 > 0 is never blended).
-// reaches() is true when some pixel of the rectangle may reach alpha >= 1/255,
-// i.e. when the rasterizer's own candidate test (p2 >= kLog2AlphaMinLoose - lo)
-// may pass there; false is a proof that it fails at every pixel.  The margin
+// reaches() is true when some pixel of the rectangle may reach alpha >= 1/255:
+// where p2 >= kLog2AlphaMinLoose - lo may hold, without which alpha stays below;
+// false is a proof that it fails at every pixel.  The margin
 // covers the float32 rounding of the conic, of this bound and of the
 // rasterizer's evaluation: 0.02 plus 1e-5 times the largest magnitude the three
 // terms of p2 take in the rectangle, some forty times the error of either

@@ -186,11 +186,10 @@ void k_raster_fwd(FwdArgs a, ViewsK views) {
                 for (int u2 = 0; u2 < kUnroll; u2++) {
                     const int jp1 = (int)ef[u2].jp1;   // list position + 1
                     const ColTerms ct = col_terms(es[u2], fxl);
-                    // hit: still compositing (finite fy; otherwise p2 = -inf and
-                    // alpha = 0) with power <= 0 and alpha >= 1/255.  (No
-                    // separate p2 bound first: the staging cull already dropped
-                    // the entries that reach 1/255 nowhere in the quadrant, and
-                    // the backward's looser bound on p2 accepts every hit.)
+                    // hit: still compositing (finite fy; see kInactiveRow) with
+                    // power <= 0 and alpha >= 1/255, by which the backward decides
+                    // too.  (No bound on p2 first: the staging cull already dropped
+                    // the entries that reach 1/255 nowhere in the quadrant.)
                     const float p2 = splat_p2(ct, et[u2].C2, es[u2].v - fy);
                     const float apre = splat_alpha_pre(p2, et[u2].lo);
                     const float alpha = PLAIN ? apre : fminf(kAlphaMax, apre);

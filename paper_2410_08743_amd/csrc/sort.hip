@@ -25,12 +25,12 @@
 // each).  An LSD radix sort in one wavefront's LDS took some 25 LDS operations
 // per entry in a chain of ranking rounds; this takes about 10, none waiting for
 // another, and a workgroup of four or eight wavefronts shares a run: 23.2 ->
-// 12.1 us at 1.5M instances in 3024 lists of 500 (pose step, 1008 x 756; 4.5 us
-// more where the kernel of the longer runs finds none), 168 -> 69 + 4.5 us at
-// 15.4M in 12096 lists of 1100-1800 (joint step), 79 -> 12.4 + 20.2 us for a
-// room with lists of up to 2400, and 706 -> 80 + 75 us for 22M in lists of up
+// 13.0 us at 1.5M instances in 3024 lists of 500 (pose step, 1008 x 756; 4.5 us
+// more where the kernel of the longer runs finds none), 168 -> 76 + 4.5 us at
+// 15.4M in 12096 lists of 1100-1800 (joint step), 79 -> 13.8 + 23 us for a
+// room with lists of up to 2400, and 706 -> 87 + 78 us for 22M in lists of up
 // to 6700 (eight views of three sizes), whose longer half one wavefront each
-// had sorted in global memory.
+// had sorted in global memory.  (The tile ids for inspection are 1 to 9 us of it.)
 #include "block_ops.h"
 #include "gsp_internal.h"
 
